@@ -314,6 +314,10 @@ hipError_t conv_fwd(const ConvShape& cs, const float* x, const float* w, const f
                                       nullptr, bf16, in_bn);
         if (e != hipErrorNotSupported || in_bn) return e;
     }
+    {
+        const hipError_t e = conv_general(cs, 0, x, w, bias, relu, y, 0, bf16, st);
+        if (e != hipErrorNotSupported) return e;
+    }
     IgArgs a = make_args(cs);
     a.A = w; a.B = x; a.C = y; a.bias = bias; a.relu = relu;
     a.M = cs.k; a.N = cs.n * cs.p * cs.q; a.Kd = cs.c * cs.r * cs.s;
@@ -350,6 +354,10 @@ hipError_t conv_bwd_data(const ConvShape& cs, const float* w, const float* dy, f
     }
     if (cs.r == 3 && cs.s == 3 && cs.pad == 1 && cs.stride == 2 && cs.h == 2 * cs.p && cs.w == 2 * cs.q) {
         hipError_t e = conv3x3_dgrad_s2(cs.n, cs.c, cs.h, cs.w, cs.k, w, dy, dx, accumulate, st, nullptr, bf16);
+        if (e != hipErrorNotSupported) return e;
+    }
+    {
+        const hipError_t e = conv_general(cs, 1, dy, w, nullptr, 0, dx, accumulate, bf16, st);
         if (e != hipErrorNotSupported) return e;
     }
     IgArgs a = make_args(cs);

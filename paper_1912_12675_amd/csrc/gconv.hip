@@ -1,0 +1,511 @@
+// Convolution forward and backward-data for the shapes without a kernel of
+// their own (any channel counts, plane sizes, kernel, stride and padding), on
+// the bf16 matrix cores: fp32 operands as three bfloat16 parts (split.h), or
+// rounded once in bf16 mode.
+//
+// Both passes are one computation: an output position (i, j) of a plane grid
+// sums, over reduction channels c and taps t, weight(m, c, t) times the input
+// at (i is + dr_t, j is + ds_t).  Forward: the grid is the output plane and
+// is the stride.  Backward data of a stride-st convolution: the input pixels
+// fall into st x st classes by (h mod st, w mod st); a class is a grid of its
+// own whose taps are every st-th row and column of the kernel, is = 1, so no
+// product with an inserted zero is formed (blockIdx.z is the class).
+//
+// A workgroup owns BM output channels of BP grid positions (TI images x TH
+// rows x TW columns, powers of two chosen on the host for the least padding).
+// Reduction channels come in chunks of 8 OC.  A chunk's input tile with its
+// halo is loaded once, split once and kept in LDS as 16-byte units [octet of
+// channels][pixel], so that a tap is only another pixel offset: nothing is
+// gathered or split again per tap.  Weights are staged per group of KG matrix
+// steps as 16-byte units [channel m][slot], a slot being one tap of one
+// octet; a matrix step takes four slots (lane group g the g-th), its A
+// operand one unit per lane and its B operand one unit per lane.  The next
+// group's weights and the next chunk's input are loaded into registers while
+// the matrix cores work.  WK waves share one tile and take the steps in turn
+// (deep reductions over few positions); their sums meet in LDS in wave order.
+//
+// Measured against the implicit GEMM that gathered (and, for each tap, divided
+// indices) element by element, fp32 unless stated: backward data 512 -> 512
+// 3x3 at 4x4, batch 128, 1,382 us on average over VGG-16's layers there ->
+// 160 us; forward 185 us; 5x5 64 -> 192 at 16x16 b128 bf16 forward 751 -> 80,
+// backward data 1,330 -> 164 us; VGG-16 b128 step 18.9 -> 6.0 ms.
+#include "internal.h"
+#include "split.h"
+
+namespace psw {
+namespace {
+
+struct GcArgs {
+    const float* x;     // input [n][C][IH][IW]
+    const float* w;
+    const float* bias;  // per output channel or null
+    float* y;           // output [n][M][OH][OW]
+    int n, C, M;
+    int IH, IW, OH, OW;
+    int R, S, pad;
+    int is, os;         // input step per grid position; output step (classes per dimension)
+    int bwd;
+    int wm, wc;         // weight strides (floats) of an output and of a reduction channel
+    int lw, lh;         // log2 of the tile's columns and rows
+    int tiles_h, tiles_w, tiles, mblocks;
+    int relu, accumulate;
+};
+
+// taps of one class along one dimension: kernel index r = r0 + k * step for
+// k < count, at input offset org + (bwd ? count - 1 - k : k)
+struct Taps {
+    int r0, step, count, org;
+};
+__host__ __device__ inline Taps class_taps(int R, int pad, int os, int bwd, int phase)
+{
+    if (!bwd) return Taps{0, 1, R, -pad};
+    const int r0 = (phase + pad) % os;
+    const int cnt = r0 < R ? (R - r0 + os - 1) / os : 0;
+    return Taps{r0, os, cnt, (phase + pad - r0) / os - (cnt - 1)};
+}
+
+// one output in plain fp32, in the order of the definition (zero outside the
+// input): the value wherever the split products give NaN.  A sum that has
+// become NaN stays one, so it ends there.
+__device__ __forceinline__ float plain_sum(const GcArgs& a, int img, int m, int oh, int ow)
+{
+    float acc = 0.f;
+    for (int c = 0; c < a.C && acc == acc; ++c)
+        for (int r = 0; r < a.R; ++r)
+            for (int s = 0; s < a.S; ++s) {
+                int ih, iw;
+                bool ok;
+                if (a.bwd) {
+                    ih = oh + a.pad - r;
+                    iw = ow + a.pad - s;
+                    ok = ih >= 0 && iw >= 0 && ih % a.os == 0 && iw % a.os == 0;
+                    ih /= a.os;
+                    iw /= a.os;
+                } else {
+                    ih = oh * a.is + r - a.pad;
+                    iw = ow * a.is + s - a.pad;
+                    ok = ih >= 0 && iw >= 0;
+                }
+                ok = ok && ih < a.IH && iw < a.IW;
+                const float v = ok ? a.x[((img * a.C + c) * a.IH + ih) * a.IW + iw] : 0.f;
+                acc = fmaf(a.w[m * a.wm + c * a.wc + r * a.S + s], v, acc);
+            }
+    return acc;
+}
+
+template <int NS, int BM, int BP, int WP, int WK, int OC, int KG>
+__global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
+{
+    constexpr int NT = 64 * WP * WK;
+    constexpr int MT = BM / 16, NTL = BP / WP / 16;  // 16x16 tiles of a wave
+    constexpr int SLOTS = 4 * KG, TG = SLOTS / OC;   // slots and taps of a weight group
+    constexpr int AROW = SLOTS + 1;                  // units per weight row: odd, so the 16 rows spread over the banks
+    constexpr int AI = BM * SLOTS, AV = (AI + NT - 1) / NT;
+    constexpr int BV = 3;                            // input units per thread and staging pass
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+
+    // this workgroup's class, channel block and tile.  Consecutive workgroups
+    // go to the 8 XCDs in turn: the channel blocks of one tile run on one XCD,
+    // one after another, and find its input in that L2
+    const int slot8 = (int)(blockIdx.x >> 3);
+    const int tile = (slot8 / a.mblocks) * 8 + (int)(blockIdx.x & 7);
+    const int m0 = (slot8 % a.mblocks) * BM;
+    if (tile >= a.tiles) return;
+    const int ph = (int)blockIdx.z / a.os, pw = (int)blockIdx.z % a.os;
+    const Taps tr = class_taps(a.R, a.pad, a.os, a.bwd, ph), ts = class_taps(a.S, a.pad, a.os, a.bwd, pw);
+    const int GH = a.bwd ? (a.OH - ph + a.os - 1) / a.os : a.OH, GW = a.bwd ? (a.OW - pw + a.os - 1) / a.os : a.OW;
+    const int TW = 1 << a.lw, TH = 1 << a.lh;
+    const int tw0 = (tile % a.tiles_w) * TW;
+    const int th0 = (tile / a.tiles_w % a.tiles_h) * TH;
+    const int img0 = tile / (a.tiles_w * a.tiles_h) * (BP >> (a.lw + a.lh));
+    if (th0 >= GH || tw0 >= GW) return;  // a class with a smaller grid
+    const int ntaps = tr.count * ts.count, ngroups = (ntaps + TG - 1) / TG;
+    const int HC = (TW - 1) * a.is + ts.count, HR = (TH - 1) * a.is + tr.count;
+    const int HP = (BP >> (a.lw + a.lh)) * HR * HC;  // staged pixels
+    const int BI = OC * HP;                          // staged units
+
+    sp_v8b* const Bs = reinterpret_cast<sp_v8b*>(smem);
+    sp_v8b* const As = Bs + NS * BI;
+    int* const tapo = reinterpret_cast<int*>(As + NS * BM * AROW);  // per slot: byte offset of its unit of pixel 0
+    int* const wtab = tapo + ngroups * SLOTS;                       // per tap: weight offset
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wp = wave % WP, wk = wave / WP;
+    const int g = lane >> 4, j = lane & 15;
+
+    for (int i = tid; i < ngroups * SLOTS; i += NT) {
+        const int t = i / OC, o = i % OC;
+        const int kr = t / (ts.count ? ts.count : 1), ks = t - kr * ts.count;
+        const int hr = a.bwd ? tr.count - 1 - kr : kr, hc = a.bwd ? ts.count - 1 - ks : ks;
+        tapo[i] = t < ntaps ? (o * HP + hr * HC + hc) * 16 : 0;
+        if (o == 0) wtab[t] = t < ntaps ? (tr.r0 + kr * tr.step) * a.S + ts.r0 + ks * ts.step : 0;
+    }
+
+    // B operand: byte offset of this lane's position of each 16-position block
+    int boff[NTL];
+#pragma unroll
+    for (int nt = 0; nt < NTL; ++nt) {
+        const int p = (wp * NTL + nt) * 16 + j;
+        const int tw = p & (TW - 1), th = (p >> a.lw) & (TH - 1), ti = p >> (a.lw + a.lh);
+        boff[nt] = ((ti * HR + th * a.is) * HC + tw * a.is) * 16;
+    }
+    sp_v4f acc[MT][NTL];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NTL; ++nt) acc[mt][nt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
+
+    // input units: unit idx = octet * HP + staged pixel; src is the byte
+    // offset of its first channel (chunk 0) from the tile's first image
+    const int plane = a.IH * a.IW;
+    const Buffer xb = make_buffer(a.x + (size_t)img0 * a.C * plane, (int64_t)(a.n - img0) * a.C * plane * 4);
+    const Buffer wb = make_buffer(a.w, (int64_t)a.M * a.C * a.R * a.S * 4);
+    auto unit_at = [&](int idx, int* c) -> int {  // c: its first channel within the chunk
+        const int o = idx / HP, hp = idx - o * HP;
+        const int ti = hp / (HR * HC), rem = hp - ti * (HR * HC);
+        const int hr = rem / HC, hc = rem - hr * HC;
+        const int ih = th0 * a.is + tr.org + hr, iw = tw0 * a.is + ts.org + hc;
+        const bool in = idx < BI && img0 + ti < a.n && ih >= 0 && ih < a.IH && iw >= 0 && iw < a.IW;
+        *c = o * 8;
+        return in ? (((ti * a.C + o * 8) * a.IH + ih) * a.IW + iw) * 4 : kOutside;
+    };
+    int bsrc[BV], bch[BV];
+#pragma unroll
+    for (int v = 0; v < BV; ++v) bsrc[v] = unit_at(tid + v * NT, &bch[v]);
+    float br[BV][8];
+    auto load_unit = [&](int src, int ch, int c0, float(&r)[8]) {
+        if (c0 + 8 * OC <= a.C) {  // every channel of the chunk exists
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = buffer_load(xb, src, (c0 + e) * plane * 4);
+        } else {
+            const int left = src >= 0 ? a.C - c0 - ch : 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = buffer_load(xb, e < left ? src + (c0 + e) * plane * 4 : kOutside, 0);
+        }
+    };
+    auto load_b = [&](int c0) {
+#pragma unroll
+        for (int v = 0; v < BV; ++v)
+            if (v * NT < BI) load_unit(bsrc[v], bch[v], c0, br[v]);
+    };
+    auto put_unit = [&](sp_v8b* dst, int plane_units, const float(&r)[8]) {
+        sp_v8b parts[NS];
+        split8<NS>(r, parts);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) dst[s * plane_units] = parts[s];
+    };
+    auto store_b = [&](int c0) {
+#pragma unroll
+        for (int v = 0; v < BV; ++v)
+            if (tid + v * NT < BI) put_unit(Bs + tid + v * NT, BI, br[v]);
+        for (int idx = tid + BV * NT; idx < BI; idx += NT) {  // a tile of more units than the registers hold
+            float r[8];
+            int ch;
+            const int src = unit_at(idx, &ch);
+            load_unit(src, ch, c0, r);
+            put_unit(Bs + idx, BI, r);
+        }
+    };
+    // weight units: idx = channel * SLOTS + slot
+    float ar[AV][8];
+    auto load_a = [&](int c0, int grp) {
+#pragma unroll
+        for (int u = 0; u < AV; ++u) {
+            const int idx = tid + u * NT;
+            const int m = idx / SLOTS, sl = idx % SLOTS;
+            const int t = grp * TG + sl / OC, c = sl % OC * 8;
+            const bool in = t < ntaps && m0 + m < a.M && (AI % NT == 0 || idx < AI);
+            const int src = in ? ((m0 + m) * a.wm + c * a.wc + wtab[t]) * 4 : kOutside;
+            if (c0 + 8 * OC <= a.C) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) ar[u][e] = buffer_load(wb, src, (c0 + e) * a.wc * 4);
+            } else {
+                const int left = in ? a.C - c0 - c : 0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    ar[u][e] = buffer_load(wb, e < left ? src + (c0 + e) * a.wc * 4 : kOutside, 0);
+            }
+        }
+    };
+    auto store_a = [&]() {
+#pragma unroll
+        for (int u = 0; u < AV; ++u) {
+            const int idx = tid + u * NT;
+            if (AI % NT == 0 || idx < AI) put_unit(As + idx / SLOTS * AROW + idx % SLOTS, BM * AROW, ar[u]);
+        }
+    };
+
+    __syncthreads();  // the tables
+    if (ntaps > 0) {
+        load_a(0, 0);
+        load_b(0);
+        for (int c0 = 0; c0 < a.C; c0 += 8 * OC)
+            for (int grp = 0; grp < ngroups; ++grp) {
+                __syncthreads();  // the previous group's operands are read
+                store_a();
+                if (grp == 0) store_b(c0);
+                __syncthreads();
+                if (grp + 1 < ngroups) {
+                    load_a(c0, grp + 1);
+                } else if (c0 + 8 * OC < a.C) {
+                    load_a(c0 + 8 * OC, 0);
+                    load_b(c0 + 8 * OC);
+                }
+                for (int ks = wk; ks < KG; ks += WK) {
+                    if ((grp * TG) * OC + ks * 4 >= ntaps * OC) break;
+                    const char* bp = reinterpret_cast<const char*>(Bs) + tapo[grp * SLOTS + ks * 4 + g];
+                    const sp_v8b* ap = As + j * AROW + ks * 4 + g;
+                    sp_v8b av[MT][NS];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) av[mt][s] = ap[(s * BM + mt * 16) * AROW];
+#pragma unroll
+                    for (int nt = 0; nt < NTL; ++nt) {
+                        sp_v8b bv[NS];
+#pragma unroll
+                        for (int s = 0; s < NS; ++s)
+                            bv[s] = *reinterpret_cast<const sp_v8b*>(bp + boff[nt] + s * BI * 16);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma_split<NS>(av[mt], bv, acc[mt][nt]);
+                    }
+                }
+            }
+    }
+
+    if constexpr (WK > 1) {  // the waves' sums, in wave order
+        float* red = reinterpret_cast<float*>(smem);
+        __syncthreads();
+        if (wk > 0)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NTL; ++nt)
+                    *reinterpret_cast<sp_v4f*>(red + ((((wk - 1) * WP + wp) * MT + mt) * NTL + nt) * 256 + lane * 4) =
+                        acc[mt][nt];
+        __syncthreads();
+        if (wk > 0) return;
+        for (int q = 0; q < WK - 1; ++q)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NTL; ++nt)
+                    acc[mt][nt] += *reinterpret_cast<const sp_v4f*>(
+                        red + (((q * WP + wp) * MT + mt) * NTL + nt) * 256 + lane * 4);
+    }
+
+    const int oplane = a.OH * a.OW;
+    // grid position p of this tile: its offset in channel 0 of the output, -1
+    // outside the grid
+    struct Pos {
+        int img, oh, ow;
+    };
+    auto pos_at = [&](int p, Pos* q) -> bool {
+        const int gi = th0 + ((p >> a.lw) & (TH - 1)), gj = tw0 + (p & (TW - 1));
+        *q = Pos{img0 + (p >> (a.lw + a.lh)), gi * a.os + ph, gj * a.os + pw};
+        return gi < GH && gj < GW && q->img < a.n;
+    };
+    if constexpr (NS == 3) {
+        // sums that came out as NaN (an infinity or NaN among their operands)
+        // are formed again in plain fp32 and stored here; the loop below
+        // leaves them alone
+        float t = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t = fmaf(acc[mt][nt][i], 0.f, t);
+        if (t != t) {
+            uint64_t bad = 0;
+            static_assert(MT * NTL * 4 <= 64, "one bit per sum");
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        bad |= (uint64_t)(acc[mt][nt][i] != acc[mt][nt][i]) << ((mt * NTL + nt) * 4 + i);
+#pragma unroll 1
+            for (; bad; bad &= bad - 1) {
+                const int k = __ffsll((unsigned long long)bad) - 1;
+                const int m = m0 + (k >> 2) / NTL * 16 + 4 * g + (k & 3);
+                Pos q;
+                if (!pos_at((wp * NTL + (k >> 2) % NTL) * 16 + j, &q) || m >= a.M) continue;
+                float v = plain_sum(a, q.img, m, q.oh, q.ow);
+                float* dst = a.y + ((q.img * a.M + m) * a.OH + q.oh) * a.OW + q.ow;
+                if (a.bias) v += a.bias[m];
+                if (a.relu) v = fmaxf(v, 0.f);
+                *dst = a.accumulate ? *dst + v : v;
+            }
+        }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NTL; ++nt) {
+        Pos q;
+        if (!pos_at((wp * NTL + nt) * 16 + j, &q)) continue;
+        float* dst = a.y + ((q.img * a.M + m0 + 4 * g) * a.OH + q.oh) * a.OW + q.ow;
+        float old[MT][4];
+        if (a.accumulate)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    old[mt][i] = m0 + mt * 16 + 4 * g + i < a.M ? dst[(mt * 16 + i) * oplane] : 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = m0 + mt * 16 + 4 * g + i;
+                float v = acc[mt][nt][i];
+                if (m >= a.M || (NS == 3 && v != v)) continue;
+                if (a.bias) v += a.bias[m];
+                if (a.relu) v = fmaxf(v, 0.f);
+                if (a.accumulate) v += old[mt][i];
+                store_stream(dst + (mt * 16 + i) * oplane, v);
+            }
+    }
+}
+
+struct Tiling {
+    int lw, lh, tiles_h, tiles_w;
+    int64_t tiles;
+    int hp;  // staged pixels
+};
+
+// tile of bp positions over n planes of gh x gw: fewest tiles, then the
+// smallest halo
+Tiling pick_tile(int n, int gh, int gw, int bp, int is, int rs, int ss)
+{
+    Tiling best{};
+    for (int lw = 0; (1 << lw) <= bp; ++lw)
+        for (int lh = 0; (1 << (lw + lh)) <= bp; ++lh) {
+            const int tw = 1 << lw, th = 1 << lh, ti = bp >> (lw + lh);
+            if ((tw >> 1) >= gw && lw) continue;
+            if ((th >> 1) >= gh && lh) continue;
+            Tiling t{lw, lh, (gh + th - 1) / th, (gw + tw - 1) / tw, 0, 0};
+            t.tiles = (int64_t)t.tiles_h * t.tiles_w * ((n + ti - 1) / ti);
+            t.hp = ti * ((th - 1) * is + rs) * ((tw - 1) * is + ss);
+            if (!best.tiles || t.tiles < best.tiles || (t.tiles == best.tiles && t.hp < best.hp)) best = t;
+        }
+    return best;
+}
+
+constexpr size_t kLdsMax = 160 * 1024;
+
+struct Plan {
+    GcArgs a;
+    int gh, gw, rs, ss, classes;
+};
+
+// LDS bytes of one configuration
+template <int NS, int BM, int BP, int WP, int WK, int OC, int KG>
+size_t lds_bytes(const Plan& p, const Tiling& t)
+{
+    constexpr int SLOTS = 4 * KG, TG = SLOTS / OC;
+    const size_t groups = (size_t)(p.rs * p.ss + TG - 1) / TG;
+    const size_t main = (size_t)NS * 16 * ((size_t)OC * t.hp + BM * (SLOTS + 1)) + groups * (SLOTS + TG) * 4;
+    const size_t red = (size_t)(WK - 1) * BM * BP * 4;
+    return main > red ? main : red;
+}
+
+template <int NS, int BM, int BP, int WP, int WK, int OC, int KG>
+hipError_t launch_cfg(Plan& p, const Tiling& t, const Work& wk, hipStream_t st)
+{
+    GcArgs a = p.a;
+    a.lw = t.lw;
+    a.lh = t.lh;
+    a.tiles_h = t.tiles_h;
+    a.tiles_w = t.tiles_w;
+    a.tiles = (int)t.tiles;
+    a.mblocks = (a.M + BM - 1) / BM;
+    const int64_t blocks = (t.tiles + 7) / 8 * 8 * a.mblocks;
+    // byte offsets within a tile's images and within the weights are 31 bits
+    if ((int64_t)(BP >> (t.lw + t.lh)) * a.C * a.IH * a.IW * 4 > INT32_MAX || (int64_t)a.M * a.C * a.R * a.S * 4 > INT32_MAX)
+        return hipErrorNotSupported;
+    if (t.tiles > INT32_MAX / 8 || blocks > INT32_MAX) return hipErrorNotSupported;
+    const size_t lds = lds_bytes<NS, BM, BP, WP, WK, OC, KG>(p, t);
+    if (lds > kLdsMax) return hipErrorNotSupported;
+    PSW_LAUNCH(kname("conv_split", NS, BM, BP, WP, WK, OC, KG), wk, (conv_split<NS, BM, BP, WP, WK, OC, KG>),
+               dim3((unsigned)blocks, 1, (unsigned)p.classes), dim3(64 * WP * WK), lds, st, a);
+    return hipGetLastError();
+}
+
+template <int NS>
+hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
+{
+    const GcArgs& a = p.a;
+    const int taps = p.rs * p.ss;
+    auto tile = [&](int bp) { return pick_tile(a.n, p.gh, p.gw, bp, a.is, p.rs, p.ss); };
+    auto blocks = [&](const Tiling& t, int bm) { return t.tiles * ((a.M + bm - 1) / bm) * p.classes; };
+    const Tiling t256 = tile(256), t64 = tile(64), t32 = tile(32);
+#define PSW_GC(T_, ...)                                                                    \
+    do {                                                                                   \
+        if (lds_bytes<NS, __VA_ARGS__>(p, T_) <= kLdsMax) return launch_cfg<NS, __VA_ARGS__>(p, T_, wk, st); \
+    } while (0)
+    if (a.C <= 8) {  // an image net's first layer (forward): one octet, four taps per matrix step
+        if (a.M <= 16) PSW_GC(t256, 16, 256, 4, 1, 1, 2);
+        if (a.M <= 32) PSW_GC(t256, 32, 256, 4, 1, 1, 2);
+        PSW_GC(t256, 64, 256, 4, 1, 1, 2);
+    }
+    if (taps == 1) {
+        if (a.M <= 16) PSW_GC(t256, 16, 256, 4, 1, 4, 1);
+        PSW_GC(t64, 64, 64, 4, 1, 4, 1);
+    }
+    if (a.M <= 16 && blocks(t256, 16) >= 256) PSW_GC(t256, 16, 256, 4, 1, 2, 2);
+    if (a.M <= 32 && blocks(t256, 32) >= 256) PSW_GC(t256, 32, 256, 4, 1, 2, 2);
+    if (a.M > 32 && blocks(t256, 64) >= 384) PSW_GC(t256, 64, 256, 4, 1, 2, 2);
+    if (a.M > 32 && blocks(t64, 64) >= 192) {
+        if (taps % 3 == 0) PSW_GC(t64, 64, 64, 1, 3, 4, 3);
+        PSW_GC(t64, 64, 64, 1, 4, 4, 4);
+    }
+    if (taps % 3 == 0) PSW_GC(t32, 32, 32, 1, 3, 4, 3);
+    PSW_GC(t32, 32, 32, 1, 4, 4, 4);
+#undef PSW_GC
+    return hipErrorNotSupported;
+}
+
+}  // namespace
+
+// Forward (bwd == 0) or backward data (bwd == 1) of any convolution;
+// hipErrorNotSupported (nothing launched) when a tile's halo exceeds the LDS.
+hipError_t conv_general(const ConvShape& cs, int bwd, const float* x, const float* w, const float* bias, int relu,
+                        float* y, int accumulate, int bf16, hipStream_t st)
+{
+    if (cs.r > 32 || cs.s > 32) return hipErrorNotSupported;
+    Plan p{};
+    GcArgs& a = p.a;
+    a.x = x;
+    a.w = w;
+    a.bias = bias;
+    a.y = y;
+    a.n = cs.n;
+    a.R = cs.r;
+    a.S = cs.s;
+    a.pad = cs.pad;
+    a.bwd = bwd;
+    a.relu = relu;
+    a.accumulate = accumulate;
+    if (bwd) {
+        a.C = cs.k; a.M = cs.c;
+        a.IH = cs.p; a.IW = cs.q; a.OH = cs.h; a.OW = cs.w;
+        a.is = 1; a.os = cs.stride;
+        a.wm = cs.r * cs.s; a.wc = cs.c * cs.r * cs.s;
+    } else {
+        a.C = cs.c; a.M = cs.k;
+        a.IH = cs.h; a.IW = cs.w; a.OH = cs.p; a.OW = cs.q;
+        a.is = cs.stride; a.os = 1;
+        a.wm = cs.c * cs.r * cs.s; a.wc = cs.r * cs.s;
+    }
+    p.gh = (a.OH + a.os - 1) / a.os;
+    p.gw = (a.OW + a.os - 1) / a.os;
+    p.rs = (cs.r + a.os - 1) / a.os;
+    p.ss = (cs.s + a.os - 1) / a.os;
+    if ((int64_t)a.os * a.os > 65535) return hipErrorNotSupported;
+    p.classes = a.os * a.os;
+    Work wk = conv_work(cs);
+    if (accumulate) wk.bytes += kF * (double)cs.n * cs.c * cs.h * cs.w;
+    return bf16 ? launch_ns<1>(p, wk, st) : launch_ns<3>(p, wk, st);
+}
+
+}  // namespace psw

@@ -257,6 +257,12 @@ constexpr int kWgradGroupMax = 8;
 hipError_t conv3x3_wgrad_group(int n, int C, int H, int W, int K, int stride, const float* const* x,
                                const float* const* dy, float* const* part, int count, hipStream_t st,
                                bool bf16 = false, const float* const* in_bn = nullptr);
+// Forward (bwd = 0: x the input, y the output, with bias and ReLU) or backward
+// data (bwd = 1: x the output gradient, y the input gradient, overwritten or
+// accumulated) of any convolution on the bf16 matrix cores;
+// hipErrorNotSupported (nothing launched) for kernels too large for its tiles.
+hipError_t conv_general(const ConvShape& cs, int bwd, const float* x, const float* w, const float* bias, int relu,
+                        float* y, int accumulate, int bf16, hipStream_t st);
 // in_bn (may be null): x is the raw input of a BN + ReLU whose output is not
 // stored, in_bn its per-channel scale [c] and shift [c] (DirArgs::in_bn);
 // only the direct kernel takes it (conv_fwd_in_bn_ok), otherwise

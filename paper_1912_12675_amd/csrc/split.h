@@ -1,0 +1,88 @@
+// Matrix products of float32 operands on the bf16 matrix cores.
+//
+// A float is the exact sum of three bfloat16 numbers (8 significant bits
+// each, rounded to nearest, so the parts' signs differ and cover all 24
+// bits): x = h + m + l.  Of the nine products of two such sums the six of
+// relative size 2^-18 and above are formed,
+//   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + O(2^-26 |a b|),
+// each an exact product accumulated in fp32 by v_mfma_f32_16x16x32_bf16.
+// Six of those take 6/16 of the time of the fp32 matrix instructions for the
+// same product (2.5 PFLOP/s against 157 TFLOP/s), and the sums are rounded
+// as often as theirs: the measured error against 64 bits is the fp32
+// instructions' or smaller (conv 256 -> 256 3x3: 5.7e-7 there).
+// The split of an infinity, a NaN or a float that rounds to infinity in
+// bfloat16 holds a NaN, so every sum such an operand enters comes out as
+// NaN; the kernels form those sums again in plain fp32 (their epilogues).
+//
+// bf16 mode is the same with the first part only: operands rounded to
+// nearest even, one product.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace psw {
+
+typedef float sp_v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 sp_v8b __attribute__((ext_vector_type(8)));
+
+// two floats to bfloat16 (nearest even), the first in the low half
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, b2));
+}
+
+// parts[0] = h, parts[1] = m, parts[2] = l of eight floats (NS = 1: h alone)
+template <int NS>
+__device__ __forceinline__ void split8(const float (&v)[8], sp_v8b (&parts)[NS])
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    u4 p[NS];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = v[2 * i], b = v[2 * i + 1];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint32_t u = bf16_pair(a, b);
+            p[s][i] = u;
+            if (s + 1 < NS) {
+                a -= __uint_as_float(u << 16);
+                b -= __uint_as_float(u & 0xffff0000u);
+            }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) parts[s] = __builtin_bit_cast(sp_v8b, p[s]);
+}
+
+// Loads of a tensor through a buffer descriptor: a lane offset (bytes) of
+// kOutside, or any at or past `bytes`, reads zero, so what lies outside a
+// tensor needs neither a branch nor a select; the second offset is uniform,
+// at most `bytes`, and costs no vector register per load.
+constexpr int kOutside = (int)0x80000000;
+using Buffer = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ Buffer make_buffer(const float* p, int64_t bytes)
+{
+    const int n = bytes > 0x7fffffff ? 0x7fffffff : (int)bytes;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, n, 0x00020000);
+}
+__device__ __forceinline__ float buffer_load(Buffer b, int lane_bytes, int uniform_bytes)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, lane_bytes, uniform_bytes, 0));
+}
+
+// acc += A B for one 16x16x32 block, smallest products first
+template <int NS>
+__device__ __forceinline__ sp_v4f mfma_split(const sp_v8b (&a)[NS], const sp_v8b (&b)[NS], sp_v4f acc)
+{
+    if constexpr (NS == 3) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
+    }
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
+}
+
+}  // namespace psw

@@ -1,0 +1,131 @@
+"""GPU parity of the general kernels (the shapes without a kernel of their own)
+against the oracle at the edges of their tiles: one element more and less than
+a tile of positions, channels and reduction chunks, every stride class of a
+backward pass, planes smaller than a tile, and operands that are not finite.
+
+Bound: both sides form the same fp32 (or bf16-rounded) products; the GPU adds
+them in fp32, so the error of a sum of L products is at most L 2^-24 of the
+sum of their magnitudes and typically sqrt(L) 2^-24 of their root mean square:
+2e-5 of the largest result covers every L here (at most 12,800)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-5
+
+
+@pytest.fixture(scope="module")
+def P():
+    from paper_1912_12675_amd import psw
+    psw.lib()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return psw
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a)).float().cuda()
+
+
+def close(gpu, ref, what):
+    torch.cuda.synchronize()
+    g, r = gpu.double().cpu().numpy(), np.asarray(ref, dtype=np.float64)
+    err = np.abs(g - r).max() / max(np.abs(r).max(), 1e-30)
+    assert g.shape == r.shape and err <= TOL, f"{what}: max err {err:.3e}"
+
+
+CONV = [
+    # N, C, H, W, K, R, S, stride, pad
+    (1, 1, 1, 1, 1, 1, 1, 1, 0),
+    (2, 3, 17, 15, 6, 5, 5, 1, 2),       # one octet of channels, 16 output channels
+    (1, 8, 32, 33, 33, 3, 3, 1, 1),      # 33 output channels: a second block of 64 is not needed, 32 is passed
+    (3, 9, 31, 8, 64, 3, 3, 1, 1),       # 9 channels: two octets, the second nearly empty
+    (2, 17, 15, 16, 65, 3, 3, 1, 1),     # one past a 16-channel chunk and a 64-channel block
+    (2, 31, 16, 17, 63, 3, 3, 1, 1),
+    (130, 33, 4, 4, 70, 3, 3, 1, 1),     # several images per tile, one past a 32-channel chunk
+    (129, 64, 2, 2, 40, 3, 3, 1, 1),
+    (40, 40, 1, 1, 48, 3, 3, 1, 1),
+    (2, 24, 29, 23, 56, 3, 3, 2, 1),     # stride 2: four classes backward, odd plane
+    (2, 20, 13, 14, 24, 5, 5, 3, 2),     # stride 3: nine classes
+    (2, 20, 9, 9, 24, 1, 1, 2, 0),       # classes without a tap
+    (2, 12, 6, 7, 20, 2, 3, 1, 2),       # a rectangular kernel, padding past it
+    (2, 40, 12, 12, 17, 1, 1, 1, 0),
+    (2, 64, 16, 16, 96, 5, 5, 1, 2),
+    (1, 512, 4, 4, 512, 3, 3, 1, 1),
+    (64, 16, 32, 32, 20, 3, 3, 1, 1),    # wide tiles of 32 output channels
+    (64, 40, 32, 32, 64, 3, 3, 1, 0),    # wide tiles of 64
+    (33, 16, 30, 30, 16, 3, 3, 1, 1),    # wide tiles of 16
+    (1, 4, 40, 40, 4, 9, 9, 4, 4),
+]
+
+
+def conv_data(case):
+    N, C, H, W, K, R, S, st, pad = case
+    rng = np.random.default_rng(sum(case) * 7 + K)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)  # noqa: E731
+    Pq, Qq = (H + 2 * pad - R) // st + 1, (W + 2 * pad - S) // st + 1
+    return f(N, C, H, W), f(K, C, R, S) * 0.3, f(K), f(N, K, Pq, Qq), f(N, C, H, W)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("case", CONV, ids=lambda c: "x".join(map(str, c)))
+def test_conv_edges(P, case, bf16):
+    print("conv", case, bf16, flush=True)
+    N, C, H, W, K, R, S, st, pad = case
+    x, w, b, dy, base = conv_data(case)
+    rd = lambda a: (torch.from_numpy(a).bfloat16() if bf16 else torch.from_numpy(a)).double()  # noqa: E731
+    y = torch.empty(dy.shape, device="cuda")
+    ref = torch.nn.functional.conv2d(rd(x), rd(w), None, st, pad).numpy()
+    xg, wg, dyg = dev(x), dev(w), dev(dy)
+    P.psw_conv_fwd(xg, wg, y, st, pad, bf16=bf16)
+    close(y, ref, "fwd")
+    P.psw_conv_fwd(xg, wg, y, st, pad, bias=dev(b), relu=True, bf16=bf16)
+    close(y, np.maximum(ref + b[None, :, None, None], 0), "fwd + bias + relu")
+    refdx = torch.nn.grad.conv2d_input(x.shape, rd(w), rd(dy), st, pad).numpy()
+    dx = torch.full(x.shape, 7.0, device="cuda")
+    P.psw_conv_bwd_data(x.shape, wg, dyg, dx, st, pad, bf16=bf16)
+    close(dx, refdx, "bwd_data")
+    dx = dev(base)
+    P.psw_conv_bwd_data(x.shape, wg, dyg, dx, st, pad, accumulate=True, bf16=bf16)
+    close(dx, refdx + base, "bwd_data accumulate")
+    refdw = torch.nn.grad.conv2d_weight(rd(x), w.shape, rd(dy), st, pad).numpy()
+    dw, db = torch.full(w.shape, 7.0, device="cuda"), torch.full((K,), 7.0, device="cuda")
+    P.psw_conv_bwd_weight(xg, dyg, dw, st, pad, dbias=db, bf16=bf16)
+    close(dw, refdw, "bwd_weight")
+    close(db, dy.astype(np.float64).sum((0, 2, 3)), "bwd_bias")
+
+
+def same_class(gpu, ref, what):
+    """Finite values close; infinities and NaNs in the same places."""
+    torch.cuda.synchronize()
+    g, r = gpu.double().cpu().numpy(), ref.numpy()
+    assert np.array_equal(np.isnan(g), np.isnan(r)), what
+    assert np.array_equal(g[np.isinf(r)], r[np.isinf(r)]) and np.array_equal(np.isinf(g), np.isinf(r)), what
+    fin = np.isfinite(r)
+    assert np.abs(g[fin] - r[fin]).max() <= TOL * np.abs(r[fin]).max(), what
+
+
+@pytest.mark.parametrize("case", [(2, 40, 12, 12, 70, 3, 3, 1, 0), (2, 12, 9, 9, 20, 3, 3, 2, 0)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_conv_not_finite(P, case):
+    """An infinity, a NaN and the largest float among the operands reach exactly the sums they enter."""
+    print("conv not finite", case, flush=True)
+    N, C, H, W, K, R, S, st, pad = case
+    x, w, _, dy, _ = conv_data(case)
+    w[np.abs(w) < 1e-3] = 0.01
+    x[0, 3, 4, 4], x[1, 5, 2, 2], x[1, 0, 0, 0] = np.inf, np.nan, 3.4e38
+    dy[0, 1, 1, 1], dy[1, 2, 2, 2] = -np.inf, np.nan
+    d = lambda a: torch.from_numpy(a).double()  # noqa: E731
+    y = torch.empty(dy.shape, device="cuda")
+    P.psw_conv_fwd(dev(x), dev(w), y, st, pad)
+    ref = torch.nn.functional.conv2d(d(x), d(w), None, st, pad).float()
+    ref = torch.where(ref.isfinite() & (ref.abs() > 1e30), ref, ref)
+    big = ref.isfinite() & (ref.abs() > 1e30)  # 3.4e38 times a weight: compared by themselves
+    torch.cuda.synchronize()
+    assert torch.allclose(y.cpu()[big], ref[big], rtol=1e-5)
+    same_class(torch.where(big.cuda(), torch.zeros_like(y), y), torch.where(big, torch.zeros_like(ref), ref).double(),
+               "fwd")
+    dx = torch.empty(x.shape, device="cuda")
+    P.psw_conv_bwd_data(x.shape, dev(w), dev(dy), dx, st, pad)
+    same_class(dx, torch.nn.grad.conv2d_input(x.shape, d(w), d(dy), st, pad), "bwd_data")
