@@ -461,14 +461,18 @@ hipError_t conv_bwd_weight(const ConvShape& cs, const float* x, const float* dy,
         }
     }
     const int z = wgrad_splits(cs, bf16);
-    const int BK = bf16 ? 32 : 16;
-    IgArgs a = make_args(cs);
-    a.A = dy; a.B = x; a.C = (float*)ws;
-    a.M = cs.k; a.N = cs.c * cs.r * cs.s; a.Kd = cs.n * cs.p * cs.q;
-    const int64_t per = ((int64_t)a.Kd + z - 1) / z;
-    a.kchunk = (int)(((per + BK - 1) / BK) * BK);
-    const int zz = (int)(((int64_t)a.Kd + a.kchunk - 1) / a.kchunk);
-    hipError_t e = bf16 ? launch<BWD_WEIGHT, true>(a, zz, st) : launch<BWD_WEIGHT, false>(a, zz, st);
+    int zz = 0;
+    hipError_t e = conv_general_wgrad(cs, x, dy, (float*)ws, z, &zz, false, bf16, st);
+    if (e == hipErrorNotSupported) {
+        const int BK = bf16 ? 32 : 16;
+        IgArgs a = make_args(cs);
+        a.A = dy; a.B = x; a.C = (float*)ws;
+        a.M = cs.k; a.N = cs.c * cs.r * cs.s; a.Kd = cs.n * cs.p * cs.q;
+        const int64_t per = ((int64_t)a.Kd + z - 1) / z;
+        a.kchunk = (int)(((per + BK - 1) / BK) * BK);
+        zz = (int)(((int64_t)a.Kd + a.kchunk - 1) / a.kchunk);
+        e = bf16 ? launch<BWD_WEIGHT, true>(a, zz, st) : launch<BWD_WEIGHT, false>(a, zz, st);
+    }
     if (e != hipSuccess) return e;
     PSW_LAUNCH(kname("reduce_splits"), (Work{(double)zz * mn, kF * (zz + 1.0) * mn}), reduce_splits,
                dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, (const float*)ws, zz, (int64_t)mn, dw);

@@ -1,0 +1,378 @@
+// Backward-weight of a convolution for the shapes without a kernel of their
+// own, on the bf16 matrix cores: fp32 operands as three bfloat16 parts
+// (split.h), or rounded once in bf16 mode.
+//
+//   dW[k][c][r][s] = sum_{img,p,q} dy[img][k][p][q] x[img][c][p st + r - pad][q st + s - pad]
+//
+// The reduction runs over images and output pixels.  Eight images at one
+// pixel are a 16-byte unit of eight bfloat16, so a tap, which moves the pixel
+// of x, moves whole units: every operand read is an aligned 16 bytes, and a
+// value is loaded and split once for all taps.  (Eight pixels of a row as a
+// unit would need a copy of x per column of the kernel.)
+//
+// A workgroup owns BM output channels and CT blocks of 16 input channels at
+// RG rows of S taps, and walks its share of the chunks: a chunk is 16 units of
+// dy (TO image octets x TH rows x TW columns, powers of two chosen on the
+// host) and the pixels of x they meet.  The next chunk is loaded into
+// registers while the matrix cores work on this one.  A matrix step takes
+// four units (lane group g the g-th); the WK waves that share an output
+// block take the steps in turn and meet in LDS in wave order.  Each workgroup
+// writes one dW-shaped partial sum (its part); reduce_splits adds the parts
+// in a fixed order.
+//
+// Measured with the reduction, batch 128, against the implicit GEMM (fp32):
+// 3x3 64 -> 64 at 32x32 336 -> 81 us, 256 -> 256 at 8x8 299 -> 78 us (123
+// TFLOP/s), 512 -> 512 at 4x4 364 -> 108 us, 5x5 64 -> 192 at 16x16 597 -> 148
+// us; bf16 mode 464 -> 59, 395 -> 48, 425 -> 79, 767 -> 85 us.
+#include "internal.h"
+#include "split.h"
+
+namespace psw {
+namespace {
+
+constexpr int kPx = 16;  // units of dy per chunk
+
+struct GwArgs {
+    const float* x;   // [n][C][H][W]
+    const float* dy;  // [n][K][P][Q]
+    float* part;      // [z][K][C][R][S]
+    int n, C, H, W, K, P, Q, R, S, st, pad;
+    int lw, lh;       // log2 of the chunk's columns and rows
+    int tiles_h, tiles_w, chunks;
+    int z, per;       // parts, chunks per part
+    int kblocks, cblocks, rblocks;
+    int by_xcd;       // parts are dealt to the XCDs in turn
+};
+
+template <int NS, int BM, int WM, int CT, int RG, int S>
+__global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
+{
+    constexpr int NT = 256, WK = 4 / WM, MT = BM / WM / 16;
+    constexpr int TAPS = CT * RG * S;
+    constexpr int DI = BM * kPx, DV = DI / NT;  // units of dy, per thread
+    constexpr int XV = 3;                       // units of x per thread and staging pass
+    static_assert(DI % NT == 0, "units");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+
+    const int combos = a.kblocks * a.cblocks * a.rblocks;
+    int zi, combo;
+    if (a.by_xcd) {  // the blocks of one part read the same tiles: one XCD, one after another
+        const int slot = (int)(blockIdx.x >> 3);
+        combo = slot % combos;
+        zi = slot / combos * 8 + (int)(blockIdx.x & 7);
+    } else {
+        combo = (int)blockIdx.x % combos;
+        zi = (int)blockIdx.x / combos;
+    }
+    if (zi >= a.z) return;
+    const int k0 = combo % a.kblocks * BM;
+    const int c0 = combo / a.kblocks % a.cblocks * (16 * CT);
+    const int r0 = combo / (a.kblocks * a.cblocks) * RG;
+    const int ch_begin = zi * a.per, ch_end = min(ch_begin + a.per, a.chunks);
+
+    const int TW = 1 << a.lw, TH = 1 << a.lh, TO = kPx >> (a.lw + a.lh);
+    const int HC = (TW - 1) * a.st + S, HR = (TH - 1) * a.st + RG;
+    const int XP = TO * HR * HC, XROW = XP | 1;  // units of one channel of x; odd row
+    const int XI = 16 * CT * XP;
+    sp_v8b* const Ds = reinterpret_cast<sp_v8b*>(smem);  // [NS][BM][16], unit u of row m at u ^ (m & 15)
+    sp_v8b* const Xs = Ds + NS * DI;                     // [NS][16 CT][XROW]
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave % WM, wk = wave / WM;
+    const int g = lane >> 4, j = lane & 15;
+    const int PQ = a.P * a.Q, HW = a.H * a.W;
+
+    // chunk -> first octet, first output row and column
+    auto chunk_at = [&](int ch, int* oct, int* p0, int* q0) {
+        *q0 = ch % a.tiles_w * TW;
+        *p0 = ch / a.tiles_w % a.tiles_h * TH;
+        *oct = ch / (a.tiles_w * a.tiles_h) * TO;
+    };
+    const Buffer dyb = make_buffer(a.dy, (int64_t)a.n * a.K * PQ * 4);
+    const Buffer xb = make_buffer(a.x, (int64_t)a.n * a.C * HW * 4);
+
+    float dr[DV][8], xr[XV][8];
+    // eight images of one element: `src` its byte offset in the first of them
+    auto load_unit = [&](const Buffer& b, int src, int img0, int stride, bool whole, float(&r)[8]) {
+        if (whole) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = buffer_load(b, src, e * stride);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = buffer_load(b, src >= 0 && img0 + e < a.n ? src + e * stride : kOutside, 0);
+        }
+    };
+    auto load_x = [&](int idx, int oct, int p0, int q0, bool whole, float(&r)[8]) {
+        const int c = idx / XP, u = idx - c * XP;
+        const int o = u / (HR * HC), rem = u - o * (HR * HC);
+        const int hr = rem / HC, hc = rem - hr * HC;
+        const int ih = p0 * a.st + r0 - a.pad + hr, iw = q0 * a.st - a.pad + hc, img = (oct + o) * 8;
+        const bool in = idx < XI && c0 + c < a.C && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W && img < a.n;
+        load_unit(xb, in ? (((img * a.C + c0 + c) * a.H + ih) * a.W + iw) * 4 : kOutside, img, a.C * HW * 4, whole, r);
+    };
+    auto load_chunk = [&](int ch) {
+        int oct, p0, q0;
+        chunk_at(ch, &oct, &p0, &q0);
+        const bool whole = (oct + TO) * 8 <= a.n;
+#pragma unroll
+        for (int v = 0; v < DV; ++v) {
+            const int idx = tid + v * NT, m = idx / kPx, u = idx % kPx;
+            const int q = q0 + (u & (TW - 1)), p = p0 + ((u >> a.lw) & (TH - 1)), img = (oct + (u >> (a.lw + a.lh))) * 8;
+            const bool in = k0 + m < a.K && p < a.P && q < a.Q && img < a.n;
+            load_unit(dyb, in ? ((img * a.K + k0 + m) * PQ + p * a.Q + q) * 4 : kOutside, img, a.K * PQ * 4, whole,
+                      dr[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < XV; ++v)
+            if (v * NT < XI) load_x(tid + v * NT, oct, p0, q0, whole, xr[v]);
+    };
+    auto put = [&](sp_v8b* dst, int stride, const float(&r)[8]) {
+        sp_v8b parts[NS];
+        split8<NS>(r, parts);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) dst[s * stride] = parts[s];
+    };
+    auto store_chunk = [&](int ch) {
+#pragma unroll
+        for (int v = 0; v < DV; ++v) {
+            const int idx = tid + v * NT, m = idx / kPx, u = idx % kPx;
+            put(Ds + m * kPx + (u ^ (m & 15)), DI, dr[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < XV; ++v) {
+            const int idx = tid + v * NT, c = idx / XP;
+            if (idx < XI) put(Xs + c * XROW + idx - c * XP, 16 * CT * XROW, xr[v]);
+        }
+        if (XV * NT < XI) {  // more units than the registers hold
+            int oct, p0, q0;
+            chunk_at(ch, &oct, &p0, &q0);
+            for (int idx = tid + XV * NT; idx < XI; idx += NT) {
+                const int c = idx / XP;
+                float r[8];
+                load_x(idx, oct, p0, q0, (oct + TO) * 8 <= a.n, r);
+                put(Xs + c * XROW + idx - c * XP, 16 * CT * XROW, r);
+            }
+        }
+    };
+
+    sp_v4f acc[MT][TAPS];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) acc[mt][t] = sp_v4f{0.f, 0.f, 0.f, 0.f};
+
+    if (ch_begin < ch_end) load_chunk(ch_begin);
+    for (int ch = ch_begin; ch < ch_end; ++ch) {
+        __syncthreads();
+        store_chunk(ch);
+        __syncthreads();
+        if (ch + 1 < ch_end) load_chunk(ch + 1);
+#pragma unroll
+        for (int q = 0; q < kPx / 4 / WK; ++q) {
+            const int u = (q * WK + wk) * 4 + g;  // this lane group's unit
+            const int tw = u & (TW - 1), th = (u >> a.lw) & (TH - 1), to = u >> (a.lw + a.lh);
+            const sp_v8b* xp = Xs + j * XROW + (to * HR + th * a.st) * HC + tw * a.st;
+            sp_v8b av[MT][NS];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    av[mt][s] = Ds[s * DI + ((wm * MT + mt) * 16 + j) * kPx + (u ^ j)];
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int r = 0; r < RG; ++r)
+#pragma unroll
+                    for (int s = 0; s < S; ++s) {
+                        sp_v8b bv[NS];
+#pragma unroll
+                        for (int k = 0; k < NS; ++k) bv[k] = xp[(k * CT + ct) * 16 * XROW + r * HC + s];
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[mt][(ct * RG + r) * S + s] = mfma_split<NS>(av[mt], bv, acc[mt][(ct * RG + r) * S + s]);
+                    }
+        }
+    }
+
+    if constexpr (WK > 1) {  // the waves' sums, in wave order, MT tiles at a time
+        float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) {
+            __syncthreads();
+            if (wk > 0)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    *reinterpret_cast<sp_v4f*>(red + (((wk - 1) * WM + wm) * MT + mt) * 256 + lane * 4) = acc[mt][t];
+            __syncthreads();
+            if (wk == 0)
+#pragma unroll
+                for (int q = 0; q < WK - 1; ++q)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[mt][t] +=
+                            *reinterpret_cast<const sp_v4f*>(red + ((q * WM + wm) * MT + mt) * 256 + lane * 4);
+        }
+        if (wk > 0) return;
+    }
+
+    float* out = a.part + (size_t)zi * a.K * a.C * a.R * a.S;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = k0 + (wm * MT + mt) * 16 + 4 * g + i;
+            if (k >= a.K) continue;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const int c = c0 + ct * 16 + j;
+                if (c >= a.C) continue;
+                float* o = out + ((size_t)k * a.C + c) * a.R * S + r0 * S;
+#pragma unroll
+                for (int r = 0; r < RG; ++r)
+#pragma unroll
+                    for (int s = 0; s < S; ++s)
+                        if (RG == 1 || r0 + r < a.R) o[r * S + s] = acc[mt][(ct * RG + r) * S + s][i];
+            }
+        }
+    if constexpr (NS == 3) {
+        // sums that came out as NaN (an infinity or NaN among their operands)
+        // are formed again in plain fp32; one that has become NaN stays so
+        float t = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int q = 0; q < TAPS; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t = fmaf(acc[mt][q][i], 0.f, t);
+        if (t != t) {
+#pragma unroll 1
+            for (int q = 0; q < MT * TAPS * 4; ++q) {
+                const int i = q & 3, tt = (q >> 2) % TAPS, mt = (q >> 2) / TAPS;
+                const int k = k0 + (wm * MT + mt) * 16 + 4 * g + i, c = c0 + tt / (RG * S) * 16 + j;
+                const int r = r0 + tt / S % RG, s = tt % S;
+                if (k >= a.K || c >= a.C || r >= a.R) continue;
+                float* o = out + (((size_t)k * a.C + c) * a.R + r) * S + s;
+                if (*o == *o) continue;
+                float v = 0.f;
+                for (int ch = ch_begin; ch < ch_end && v == v; ++ch) {
+                    int oct, p0, q0;
+                    chunk_at(ch, &oct, &p0, &q0);
+                    for (int u = 0; u < kPx; ++u) {
+                        const int qq = q0 + (u & (TW - 1)), pp = p0 + ((u >> a.lw) & (TH - 1));
+                        const int ih = pp * a.st + r - a.pad, iw = qq * a.st + s - a.pad;
+                        const bool in = ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
+                        if (pp >= a.P || qq >= a.Q) continue;
+                        for (int e = 0; e < 8; ++e) {
+                            const int img = (oct + (u >> (a.lw + a.lh))) * 8 + e;
+                            if (img >= a.n) break;
+                            const float xv = in ? a.x[((img * a.C + c) * a.H + ih) * a.W + iw] : 0.f;
+                            v = fmaf(a.dy[(img * a.K + k) * PQ + pp * a.Q + qq], xv, v);
+                        }
+                    }
+                }
+                *o = v;
+            }
+        }
+    }
+}
+
+constexpr size_t kLdsMax = 160 * 1024;
+
+template <int NS, int BM, int WM, int CT, int RG, int S>
+size_t gw_lds(const GwArgs& a)
+{
+    const int TW = 1 << a.lw, TH = 1 << a.lh, TO = kPx >> (a.lw + a.lh);
+    const size_t xp = (size_t)TO * ((TH - 1) * a.st + RG) * ((TW - 1) * a.st + S);
+    const size_t main = (size_t)NS * 16 * (BM * kPx + 16 * CT * (xp | 1));
+    const size_t red = (size_t)(4 / WM - 1) * BM * 64;  // (WK-1) waves x MT tiles x 256 floats, per row of waves
+    return main > red ? main : red;
+}
+
+template <int NS, int BM, int WM, int CT, int RG, int S>
+hipError_t gw_launch(GwArgs a, int max_splits, int* splits, bool dry, const Work& wk, hipStream_t st)
+{
+    // chunk of 16 units: fewest chunks; then the least of x, rows of a
+    // 32-byte sector where the plane has them
+    int64_t best = 0;
+    int best_x = 0;
+    for (int lw = 0; lw <= 4; ++lw)
+        for (int lh = 0; lw + lh <= 4; ++lh) {
+            const int tw = 1 << lw, th = 1 << lh, to = kPx >> (lw + lh);
+            if (((tw >> 1) >= a.Q && lw) || ((th >> 1) >= a.P && lh)) continue;
+            const int64_t ch = (int64_t)((a.Q + tw - 1) / tw) * ((a.P + th - 1) / th) * (((a.n + 7) / 8 + to - 1) / to);
+            const int xp = to * ((th - 1) * a.st + RG) * ((tw - 1) * a.st + S) + (tw < 8 && a.Q >= 8 ? 8 : 0);
+            if (!best || ch < best || (ch == best && xp < best_x)) {
+                best = ch;
+                best_x = xp;
+                a.lw = lw;
+                a.lh = lh;
+                a.tiles_w = (a.Q + tw - 1) / tw;
+                a.tiles_h = (a.P + th - 1) / th;
+            }
+        }
+    if (best > INT32_MAX) return hipErrorNotSupported;
+    const size_t lds = gw_lds<NS, BM, WM, CT, RG, S>(a);
+    if (lds > kLdsMax) return hipErrorNotSupported;
+    a.chunks = (int)best;
+    a.kblocks = (a.K + BM - 1) / BM;
+    a.cblocks = (a.C + 16 * CT - 1) / (16 * CT);
+    a.rblocks = (a.R + RG - 1) / RG;
+    const int64_t combos = (int64_t)a.kblocks * a.cblocks * a.rblocks;
+    // two workgroups per CU as far as there are chunks (a chunk is a round
+    // trip to memory whatever its size, so small layers spread out fully)
+    int64_t z = (512 + combos - 1) / combos;
+    if (z > a.chunks) z = a.chunks;
+    if (z > max_splits) z = max_splits;
+    if (z >= 8) z = z / 8 * 8;
+    a.per = (int)((a.chunks + z - 1) / z);
+    a.z = (a.chunks + a.per - 1) / a.per;
+    a.by_xcd = a.z >= 8;
+    *splits = a.z;
+    const int64_t blocks = (a.by_xcd ? (a.z + 7) / 8 * 8 : a.z) * combos;
+    if (blocks > INT32_MAX) return hipErrorNotSupported;
+    if (dry) return hipSuccess;
+    PSW_LAUNCH(kname("conv_split_wgrad", NS, BM, WM, CT, RG, S), wk, (conv_split_wgrad<NS, BM, WM, CT, RG, S>),
+               dim3((unsigned)blocks), dim3(256), lds, st, a);
+    return hipGetLastError();
+}
+
+template <int NS, int BM, int WM>
+hipError_t gw_taps(const GwArgs& a, int ms, int* sp, bool dry, const Work& wk, hipStream_t st)
+{
+    if (a.R == 3 && a.S == 3) return gw_launch<NS, BM, WM, 1, 3, 3>(a, ms, sp, dry, wk, st);
+    if (a.S == 5) return gw_launch<NS, BM, WM, 1, 1, 5>(a, ms, sp, dry, wk, st);
+    if (a.S == 3) return gw_launch<NS, BM, WM, 1, 1, 3>(a, ms, sp, dry, wk, st);
+    if (a.S == 1) return gw_launch<NS, BM, WM, 4, 1, 1>(a, ms, sp, dry, wk, st);
+    return hipErrorNotSupported;
+}
+
+template <int NS>
+hipError_t gw_rows(const GwArgs& a, int ms, int* sp, bool dry, const Work& wk, hipStream_t st)
+{
+    if (a.K <= 16) return gw_taps<NS, 16, 1>(a, ms, sp, dry, wk, st);
+    if (a.K <= 32) return gw_taps<NS, 32, 1>(a, ms, sp, dry, wk, st);
+    return gw_taps<NS, 64, 2>(a, ms, sp, dry, wk, st);
+}
+
+}  // namespace
+
+// Partial sums of dW (each K x C x R x S) for `*splits` <= max_splits parts of
+// the reduction; hipErrorNotSupported (nothing launched) for kernels without
+// a configuration.  dry: set *splits only.
+hipError_t conv_general_wgrad(const ConvShape& cs, const float* x, const float* dy, float* part, int max_splits,
+                              int* splits, bool dry, int bf16, hipStream_t st)
+{
+    // byte offsets are 31 bits
+    if ((int64_t)cs.n * cs.c * cs.h * cs.w * 4 > INT32_MAX || (int64_t)cs.n * cs.k * cs.p * cs.q * 4 > INT32_MAX)
+        return hipErrorNotSupported;
+    if (max_splits < 1) return hipErrorNotSupported;
+    GwArgs a{};
+    a.x = x; a.dy = dy; a.part = part;
+    a.n = cs.n; a.C = cs.c; a.H = cs.h; a.W = cs.w;
+    a.K = cs.k; a.P = cs.p; a.Q = cs.q; a.R = cs.r; a.S = cs.s;
+    a.st = cs.stride; a.pad = cs.pad;
+    const Work wk = conv_work(cs);
+    return bf16 ? gw_rows<1>(a, max_splits, splits, dry, wk, st) : gw_rows<3>(a, max_splits, splits, dry, wk, st);
+}
+
+}  // namespace psw

@@ -263,6 +263,11 @@ hipError_t conv3x3_wgrad_group(int n, int C, int H, int W, int K, int stride, co
 // hipErrorNotSupported (nothing launched) for kernels too large for its tiles.
 hipError_t conv_general(const ConvShape& cs, int bwd, const float* x, const float* w, const float* bias, int relu,
                         float* y, int accumulate, int bf16, hipStream_t st);
+// Weight gradient of any convolution as `*splits` <= max_splits partial sums
+// part[z][k*c*r*s] (dry: only sets *splits); hipErrorNotSupported (nothing
+// launched) for kernels without a configuration.
+hipError_t conv_general_wgrad(const ConvShape& cs, const float* x, const float* dy, float* part, int max_splits,
+                              int* splits, bool dry, int bf16, hipStream_t st);
 // in_bn (may be null): x is the raw input of a BN + ReLU whose output is not
 // stored, in_bn its per-channel scale [c] and shift [c] (DirArgs::in_bn);
 // only the direct kernel takes it (conv_fwd_in_bn_ok), otherwise
