@@ -1,0 +1,539 @@
+// Fully connected products on the bf16 matrix cores: C[m][n] (+)= sum_k
+// A(m, k) B(k, n), fp32 operands as three bfloat16 parts (split.h), or rounded
+// once in bf16 mode.  Forward y = x w^T, backward dx = dy w and dw = dy^T x
+// differ in which index of an operand is contiguous in memory.
+//
+// A workgroup owns BM x BN of C and walks k in stages of 32 KG: both tiles are
+// loaded into registers a stage ahead (16 bytes a lane along k, or lanes along
+// the row index), split, and kept in LDS as 16-byte units of eight k.  The
+// matrix instruction's rows are C's columns, so that a lane ends with four
+// consecutive elements of a row of C.  WK waves share one tile and take the
+// matrix steps of a stage in turn: with few outputs and a deep reduction the
+// chip is filled and memory kept busy by the stages' depth, not by more
+// outputs; their sums meet in LDS in wave order, so results do not depend on
+// timing.
+//
+// Measured at 128 x 16384 x 4096 against the gemm that staged scalars (us,
+// fp32 / bf16): forward 2,238 -> 285 / 186, dx 655 -> 166, dw 258 -> 134 (268
+// MB of weights read, read and written: 40-50 us each at memory's rate, 110 at
+// the fp32 matrix rate).  Forward is bound by the L2's delivery of x to every
+// block of columns, dx and dw by their stages' phases following one another.
+#include <algorithm>
+
+#include "internal.h"
+#include "split.h"
+
+namespace psw {
+namespace {
+
+struct GsArgs {
+    const float* A;     // AK: [m][k], row stride lda; else [k][m]
+    const float* B;     // BK: [n][k], row stride ldb; else [k][n]
+    float* C;           // [M][N]
+    const float* bias;  // per column n, or null
+    int M, N, K;
+    int lda, ldb;
+    int nblocks, mblocks;
+    int relu, accumulate;
+    int vec;            // C rows are 16-byte aligned
+};
+
+template <bool AK, bool BK>
+__device__ __forceinline__ float plain_dot(const GsArgs& a, int m, int n)
+{
+    float v = 0.f;
+    for (int k = 0; k < a.K && v == v; ++k)
+        v = fmaf(AK ? a.A[(int64_t)m * a.lda + k] : a.A[(int64_t)k * a.lda + m],
+                 BK ? a.B[(int64_t)n * a.ldb + k] : a.B[(int64_t)k * a.ldb + n], v);
+    return v;
+}
+
+// eight k of one row: `off` its lane offset (kOutside: none), `left` how many
+// of the eight exist (a stage past the end of k)
+template <bool KC>
+__device__ __forceinline__ void load_k8(Buffer b, int off, int ld, bool whole, int left, float (&r)[8])
+{
+    if (KC && whole) {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        const f4 u = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
+        const f4 v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 16, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            r[e] = u[e];
+            r[4 + e] = v[e];
+        }
+    } else if (whole) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = buffer_load(b, off, e * ld * 4);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            r[e] = buffer_load(b, off >= 0 && e < left ? off + e * (KC ? 4 : ld * 4) : kOutside, 0);
+    }
+}
+
+template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK>
+__global__ __launch_bounds__(64 * WM * WN * WK) void gemm_split(GsArgs a)
+{
+    constexpr int NT = 64 * WM * WN * WK, KU = 4 * KG, ROW = KU + 1;  // units per row; odd row of units
+    constexpr int MT = BM / WM / 16, NTL = BN / WN / 16;
+    constexpr int AI = BM * KU, BI = BN * KU, AV = (AI + NT - 1) / NT, BV = (BI + NT - 1) / NT;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    sp_v8b* const As = reinterpret_cast<sp_v8b*>(smem);  // [NS][BM][ROW]
+    sp_v8b* const Bs = As + NS * BM * ROW;               // [NS][BN][ROW]
+
+    // consecutive workgroups go to the 8 XCDs in turn: the row blocks of one
+    // column block run on one XCD, one after another (with fewer than eight
+    // column blocks, in plain order over all XCDs)
+    const int slot = (int)(blockIdx.x >> 3);
+    int nb = slot / a.mblocks * 8 + (int)(blockIdx.x & 7), mb = slot % a.mblocks;
+    if (a.nblocks < 8) {
+        nb = (int)blockIdx.x % a.nblocks;
+        mb = (int)blockIdx.x / a.nblocks;
+    }
+    if (nb >= a.nblocks) return;
+    const int m0 = mb * BM, n0 = nb * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
+    const int g = lane >> 4, j = lane & 15;
+
+    float ar[AV][8], br[BV][8];
+    auto load = [&](int k0) {
+        const bool whole = k0 + 8 * KU <= a.K;
+        const Buffer ab = AK ? make_buffer(a.A + (int64_t)m0 * a.lda + k0, ((int64_t)(a.M - m0) * a.lda - k0) * 4)
+                             : make_buffer(a.A + (int64_t)k0 * a.lda + m0, ((int64_t)(a.K - k0) * a.lda - m0) * 4);
+        const Buffer bb = BK ? make_buffer(a.B + (int64_t)n0 * a.ldb + k0, ((int64_t)(a.N - n0) * a.ldb - k0) * 4)
+                             : make_buffer(a.B + (int64_t)k0 * a.ldb + n0, ((int64_t)(a.K - k0) * a.ldb - n0) * 4);
+#pragma unroll
+        for (int v = 0; v < AV; ++v) {
+            const int idx = tid + v * NT, row = AK ? idx / KU : idx % BM, o = AK ? idx % KU : idx / BM;
+            const bool in = m0 + row < a.M && (AI % NT == 0 || idx < AI);
+            load_k8<AK>(ab, in ? (AK ? row * a.lda + o * 8 : row + o * 8 * a.lda) * 4 : kOutside, a.lda, whole,
+                        a.K - k0 - o * 8, ar[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < BV; ++v) {
+            const int idx = tid + v * NT, row = BK ? idx / KU : idx % BN, o = BK ? idx % KU : idx / BN;
+            const bool in = n0 + row < a.N && (BI % NT == 0 || idx < BI);
+            load_k8<BK>(bb, in ? (BK ? row * a.ldb + o * 8 : row + o * 8 * a.ldb) * 4 : kOutside, a.ldb, whole,
+                        a.K - k0 - o * 8, br[v]);
+        }
+    };
+    auto put = [&](sp_v8b* dst, int stride, const float(&r)[8]) {
+        sp_v8b parts[NS];
+        split8<NS>(r, parts);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) dst[s * stride] = parts[s];
+    };
+    auto store = [&]() {
+#pragma unroll
+        for (int v = 0; v < AV; ++v) {
+            const int idx = tid + v * NT, row = AK ? idx / KU : idx % BM, o = AK ? idx % KU : idx / BM;
+            if (AI % NT == 0 || idx < AI) put(As + row * ROW + o, BM * ROW, ar[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < BV; ++v) {
+            const int idx = tid + v * NT, row = BK ? idx / KU : idx % BN, o = BK ? idx % KU : idx / BN;
+            if (BI % NT == 0 || idx < BI) put(Bs + row * ROW + o, BN * ROW, br[v]);
+        }
+    };
+
+    sp_v4f acc[NTL][MT];
+#pragma unroll
+    for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
+
+    load(0);
+    for (int k0 = 0; k0 < a.K; k0 += 8 * KU) {
+        __syncthreads();
+        store();
+        __syncthreads();
+        if (k0 + 8 * KU < a.K) load(k0 + 8 * KU);
+#pragma unroll
+        for (int q = 0; q < KG / WK; ++q) {
+            const int u = (q * WK + wk) * 4 + g;
+            if (k0 + (q * WK + wk) * 32 >= a.K) break;
+            const sp_v8b* ap = As + (wm * MT * 16 + j) * ROW + u;
+            const sp_v8b* bp = Bs + (wn * NTL * 16 + j) * ROW + u;
+            sp_v8b bv[NTL][NS];
+#pragma unroll
+            for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+                for (int s = 0; s < NS; ++s) bv[nt][s] = bp[(s * BN + nt * 16) * ROW];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                sp_v8b av[NS];
+#pragma unroll
+                for (int s = 0; s < NS; ++s) av[s] = ap[(s * BM + mt * 16) * ROW];
+#pragma unroll
+                for (int nt = 0; nt < NTL; ++nt) acc[nt][mt] = mfma_split<NS>(bv[nt], av, acc[nt][mt]);
+            }
+        }
+    }
+
+    if constexpr (WK > 1) {  // the waves' sums, in wave order
+        float* red = reinterpret_cast<float*>(smem);
+        __syncthreads();
+        if (wk > 0)
+#pragma unroll
+            for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    *reinterpret_cast<sp_v4f*>(red + ((((wk - 1) * WN + wn) * WM + wm) * NTL * MT + nt * MT + mt) * 256 +
+                                               lane * 4) = acc[nt][mt];
+        __syncthreads();
+        if (wk > 0) return;
+        for (int q = 0; q < WK - 1; ++q)
+#pragma unroll
+            for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[nt][mt] += *reinterpret_cast<const sp_v4f*>(
+                        red + (((q * WN + wn) * WM + wm) * NTL * MT + nt * MT + mt) * 256 + lane * 4);
+    }
+
+    const int mrow = m0 + wm * MT * 16 + j, ncol = n0 + wn * NTL * 16 + 4 * g;
+    if constexpr (NS == 3) {
+        // sums that came out as NaN (an infinity or NaN among their operands):
+        // again in plain fp32; left alone below
+        float t = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t = fmaf(acc[nt][mt][i], 0.f, t);
+        if (t != t) {
+            uint64_t bad = 0;
+            static_assert(MT * NTL * 4 <= 64, "one bit per sum");
+#pragma unroll
+            for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        bad |= (uint64_t)(acc[nt][mt][i] != acc[nt][mt][i]) << ((nt * MT + mt) * 4 + i);
+#pragma unroll 1
+            for (; bad; bad &= bad - 1) {
+                const int q = __ffsll((unsigned long long)bad) - 1;
+                const int m = mrow + (q >> 2) % MT * 16, n = ncol + (q >> 2) / MT * 16 + (q & 3);
+                if (m >= a.M || n >= a.N) continue;
+                float v = plain_dot<AK, BK>(a, m, n);
+                if (a.bias) v += a.bias[n];
+                if (a.relu) v = fmaxf(v, 0.f);
+                float* dst = a.C + (int64_t)m * a.N + n;
+                *dst = a.accumulate ? *dst + v : v;
+            }
+        }
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int m = mrow + mt * 16;
+        if (m >= a.M) continue;
+#pragma unroll
+        for (int nt = 0; nt < NTL; ++nt) {
+            const int n = ncol + nt * 16;
+            float* dst = a.C + (int64_t)m * a.N + n;
+            sp_v4f v = acc[nt][mt];
+            const bool fine = NS != 3 || (v[0] == v[0] && v[1] == v[1] && v[2] == v[2] && v[3] == v[3]);
+            if (a.vec && n + 4 <= a.N && fine) {
+                if (a.bias) v += sp_v4f{a.bias[n], a.bias[n + 1], a.bias[n + 2], a.bias[n + 3]};
+                if (a.relu)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+                if (a.accumulate) v += *reinterpret_cast<const sp_v4f*>(dst);
+                __builtin_nontemporal_store(v, reinterpret_cast<sp_v4f*>(dst));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float s = v[i];
+                    if (n + i >= a.N || (NS == 3 && s != s)) continue;
+                    if (a.bias) s += a.bias[n + i];
+                    if (a.relu) s = fmaxf(s, 0.f);
+                    dst[i] = a.accumulate ? dst[i] + s : s;
+                }
+            }
+        }
+    }
+}
+
+// Forward of a batch of few rows (both operands contiguous along k).  A
+// workgroup owns 16 MT rows by 16 columns, and its WK waves take the steps of
+// 32 k in turn, each for the whole tile: no operand is used by two waves, so
+// none goes through LDS.  A lane loads two pieces of 16 bytes along k of its
+// row, 64 bytes apart, so that the four lane groups read 64 bytes in a row; the
+// order of k within a step is free as long as A and B agree, so these are a
+// bf16 operand as they stand, and eight operands of the fp32 instruction (step
+// e takes element e of every lane group).  The weights are read once and the next step's operands are in
+// flight while the matrix cores work.  fp32 uses the fp32 instructions: a
+// split costs the vector units 208 cycles an operand, eight of nine operands
+// are the batch's, and each would serve one block of columns (the tiled kernel
+// takes 370 us at 128 x 16384 x 4096, this one 285).
+template <bool BF, int MT, int WK>
+__global__ __launch_bounds__(64 * WK) void gemm_rows(GsArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wk = tid >> 6;
+    const int g = lane >> 4, j = lane & 15;
+    const int n0 = (int)blockIdx.x * 16, m0 = (int)blockIdx.y * 16 * MT;
+    const Buffer ab = make_buffer(a.A + (int64_t)m0 * a.lda, (int64_t)(a.M - m0) * a.lda * 4);
+    const Buffer bb = make_buffer(a.B + (int64_t)n0 * a.ldb, (int64_t)(a.N - n0) * a.ldb * 4);
+    int aoff[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+        aoff[mt] = m0 + mt * 16 + j < a.M ? ((mt * 16 + j) * a.lda + g * 4) * 4 : kOutside;
+    const int boff = n0 + j < a.N ? (j * a.ldb + g * 4) * 4 : kOutside;
+    const int steps = (a.K + 31) / 32;
+
+    sp_v4f acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    struct Ops {
+        f4 a[MT][2], b[2];
+    };
+    auto load8 = [&](Buffer b, int off, int ks, f4(&r)[2]) {
+        if ((ks + 1) * 32 <= a.K) {
+            r[0] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, off, ks * 128, 0));
+            r[1] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, off + 64, ks * 128, 0));
+        } else {  // the last step's missing k are zero
+            const int left = off >= 0 ? a.K - ks * 32 - g * 4 : 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = e / 4 * 16 + e % 4;
+                r[e / 4][e % 4] = buffer_load(b, k < left ? off + ks * 128 + k * 4 : kOutside, 0);
+            }
+        }
+    };
+    auto load = [&](int ks, Ops& o) {
+        if (ks >= steps) return;
+        load8(bb, boff, ks, o.b);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) load8(ab, aoff[mt], ks, o.a[mt]);
+    };
+    auto bf8 = [](const f4(&r)[2]) {
+        float t[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t[e] = r[e / 4][e % 4];
+        sp_v8b p[1];
+        split8<1>(t, p);
+        return p[0];
+    };
+    auto mul = [&](int ks, const Ops& o) {
+        if (ks >= steps) return;
+        if constexpr (BF) {
+            const sp_v8b bv = bf8(o.b);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, bf8(o.a[mt]), acc[mt], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.b[e / 4][e % 4], o.a[mt][e / 4][e % 4], acc[mt], 0, 0, 0);
+        }
+    };
+    Ops o0, o1;
+    load(wk, o0);
+    for (int ks = wk; ks < steps; ks += 2 * WK) {
+        load(ks + WK, o1);
+        mul(ks, o0);
+        load(ks + 2 * WK, o0);
+        mul(ks + WK, o1);
+    }
+
+    // the waves' sums, in wave order; wave w finishes row blocks w, w + WK, ...
+    float* red = reinterpret_cast<float*>(smem);
+    if (WK > 1) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            *reinterpret_cast<sp_v4f*>(red + (wk * MT + mt) * 256 + lane * 4) = acc[mt];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        if (mt % WK != wk) continue;
+        sp_v4f v = *reinterpret_cast<const sp_v4f*>(red + mt * 256 + lane * 4);
+        for (int q = 1; q < WK; ++q) v += *reinterpret_cast<const sp_v4f*>(red + (q * MT + mt) * 256 + lane * 4);
+        const int m = m0 + mt * 16 + j, n = n0 + 4 * g;
+        if (m >= a.M) continue;
+        float* dst = a.C + (int64_t)m * a.N + n;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (a.bias && n + i < a.N) v[i] += a.bias[n + i];
+            if (a.relu) v[i] = fmaxf(v[i], 0.f);
+        }
+        if (a.vec && n + 4 <= a.N) {
+            *reinterpret_cast<sp_v4f*>(dst) = v;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (n + i < a.N) dst[i] = v[i];
+        }
+    }
+}
+
+// column sums out[c] = sum_r x[r][c] in double, rows in order within each of
+// four lanes of a column, then the lanes in order
+__global__ __launch_bounds__(256) void col_sum_k(int rows, int cols, const float* x, float* out)
+{
+    __shared__ double sh[4][64];
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
+    double s = 0.0;
+    if (c < cols) {
+        int r = q;
+        for (; r + 28 < rows; r += 32) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = x[(int64_t)(r + 4 * e) * cols + c];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s += (double)v[e];
+        }
+        for (; r < rows; r += 4) s += (double)x[(int64_t)r * cols + c];
+    }
+    sh[q][threadIdx.x & 63] = s;
+    __syncthreads();
+    if (q == 0 && c < cols)
+        out[c] = (float)(((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x]);
+}
+
+// one output per thread, for row strides past the descriptors' 31-bit offsets
+template <bool AK, bool BK>
+__global__ void gemm_plain(GsArgs a, int bf16)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (int64_t)a.M * a.N) return;
+    const int m = (int)(i / a.N), n = (int)(i - (int64_t)m * a.N);
+    float v = 0.f;
+    for (int k = 0; k < a.K; ++k) {
+        float p = AK ? a.A[(int64_t)m * a.lda + k] : a.A[(int64_t)k * a.lda + m];
+        float q = BK ? a.B[(int64_t)n * a.ldb + k] : a.B[(int64_t)k * a.ldb + n];
+        if (bf16) {
+            p = (float)(__bf16)p;
+            q = (float)(__bf16)q;
+        }
+        v = fmaf(p, q, v);
+    }
+    if (a.bias) v += a.bias[n];
+    if (a.relu) v = fmaxf(v, 0.f);
+    a.C[i] = a.accumulate ? a.C[i] + v : v;
+}
+
+template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK>
+hipError_t gs_launch(GsArgs a, const Work& wk, hipStream_t st)
+{
+    a.mblocks = (a.M + BM - 1) / BM;
+    a.nblocks = (a.N + BN - 1) / BN;
+    const int64_t blocks = (int64_t)(a.nblocks < 8 ? a.nblocks : (a.nblocks + 7) / 8 * 8) * a.mblocks;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    constexpr size_t main = (size_t)NS * 16 * (BM + BN) * (4 * KG + 1), red = (size_t)(WK - 1) * BM * BN * 4;
+    PSW_LAUNCH(kname("gemm_split", NS, BM, BN, WM, WN, WK, KG, AK, BK), wk,
+               (gemm_split<NS, BM, BN, WM, WN, WK, KG, AK, BK>), dim3((unsigned)blocks), dim3(64 * WM * WN * WK),
+               main > red ? main : red, st, a);
+    return hipGetLastError();
+}
+
+// Tiles, each with the reason it is there (fp32, us; 128 rows unless said):
+// the largest that leaves work for the whole chip, except that
+//  - 128 x 128 pays only over many tiles: dw 4096 x 16384, k 128: 134 (64 x 64
+//    190); dx 128 x 16384, k 4096, is 128 tiles of it: 281 (64 x 64 166);
+//  - few outputs over a deep k take 16 waves on k: 16 x 227, k 4096: 20.
+template <int NS, bool AK, bool BK>
+hipError_t gs_pick(const GsArgs& a, const Work& wk, hipStream_t st)
+{
+    auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    // bf16 forward of more than 64 rows to many columns: x is rounded, not split, again per
+    // column block, so the LDS tile is ahead of gemm_rows (16384 -> 4096: 186
+    // against 258)
+    if constexpr (AK && BK)
+        if (a.M > 64 && a.M <= 256) return gs_launch<NS, 128, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
+    if (blocks(128, 128) >= 512) return gs_launch<NS, 128, 128, 2, 2, 1, 1, AK, BK>(a, wk, st);
+    if (blocks(64, 64) >= 128) return gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(a, wk, st);
+    if (a.K > 512 && blocks(16, 16) <= 256) return gs_launch<NS, 16, 16, 1, 1, 16, 16, AK, BK>(a, wk, st);
+    if (blocks(32, 32) >= 64) return gs_launch<NS, 32, 32, 1, 1, 4, 4, AK, BK>(a, wk, st);
+    return gs_launch<NS, 16, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
+}
+
+template <bool BF, int MT, int WK>
+hipError_t rows_launch(const GsArgs& a, const Work& wk, hipStream_t st)
+{
+    PSW_LAUNCH(kname("gemm_rows", BF, MT, WK), wk, (gemm_rows<BF, MT, WK>),
+               dim3((unsigned)((a.N + 15) / 16), (unsigned)((a.M + 16 * MT - 1) / (16 * MT))), dim3(64 * WK),
+               (size_t)WK * MT * 1024, st, a);
+    return hipGetLastError();
+}
+
+template <bool BF>
+hipError_t rows_pick(const GsArgs& a, const Work& wk, hipStream_t st)
+{
+    // the most rows per workgroup that still leave a workgroup for every
+    // other CU (the columns' operands are then read once or twice); else 16
+    // rows and 16 waves on the depth of k
+    const int64_t cols = (a.N + 15) / 16;
+    if (a.M > 64 && cols * ((a.M + 127) / 128) >= 128) return rows_launch<BF, 8, 8>(a, wk, st);
+    if (a.M > 32 && cols * ((a.M + 63) / 64) >= 128) return rows_launch<BF, 4, 8>(a, wk, st);
+    if (a.M > 16 && cols * ((a.M + 31) / 32) >= 128) return rows_launch<BF, 2, 8>(a, wk, st);
+    return a.K > 512 ? rows_launch<BF, 1, 16>(a, wk, st) : rows_launch<BF, 1, 4>(a, wk, st);
+}
+
+template <bool AK, bool BK>
+hipError_t gemm(GsArgs a, int bf16, hipStream_t st)
+{
+    const Work wk{2.0 * a.M * a.N * (double)a.K,
+                  kF * ((double)a.M * a.K + (double)a.K * a.N + (1.0 + a.accumulate) * a.M * (double)a.N)};
+    a.vec = a.N % 4 == 0 && (uintptr_t)a.C % 16 == 0;
+    // lane offsets within a tile (128 rows, or 512 k of a row-contiguous
+    // operand) are 31 bits
+    if ((int64_t)std::max(a.lda, a.ldb) * 512 * 4 > INT32_MAX) {
+        PSW_LAUNCH(kname("gemm_plain", AK, BK), wk, (gemm_plain<AK, BK>),
+                   dim3((unsigned)(((int64_t)a.M * a.N + 255) / 256)), dim3(256), 0, st, a, bf16);
+        return hipGetLastError();
+    }
+    // up to 256 rows the weights' traffic and the depth of k decide, not the
+    // matrix rate: the kernel without LDS
+    if constexpr (AK && BK)
+        if (a.M <= (bf16 && a.N >= 1024 ? 64 : 256) && !a.accumulate) return bf16 ? rows_pick<true>(a, wk, st) : rows_pick<false>(a, wk, st);
+    return bf16 ? gs_pick<1, AK, BK>(a, wk, st) : gs_pick<3, AK, BK>(a, wk, st);
+}
+
+}  // namespace
+
+hipError_t fc_gemm_fwd(int n, int in, int out, const float* x, const float* w, const float* b, int relu, float* y,
+                       int bf16, hipStream_t st)
+{
+    GsArgs a{};
+    a.A = x; a.B = w; a.C = y; a.bias = b; a.relu = relu;
+    a.M = n; a.N = out; a.K = in;
+    a.lda = in;  // x[n][i]
+    a.ldb = in;  // w[o][i]
+    return gemm<true, true>(a, bf16, st);
+}
+
+hipError_t fc_gemm_bwd(int n, int in, int out, const float* x, const float* w, const float* dy, float* dx,
+                       int dx_accumulate, float* dw, float* db, int bf16, hipStream_t st)
+{
+    if (dx) {
+        GsArgs a{};
+        a.A = dy; a.B = w; a.C = dx; a.accumulate = dx_accumulate;
+        a.M = n; a.N = in; a.K = out;
+        a.lda = out;  // dy[n][o]
+        a.ldb = in;   // w[o][i], k = o
+        const hipError_t e = gemm<true, false>(a, bf16, st);
+        if (e != hipSuccess) return e;
+    }
+    GsArgs a{};
+    a.A = dy; a.B = x; a.C = dw;
+    a.M = out; a.N = in; a.K = n;
+    a.lda = out;  // dy[n][o], k = n
+    a.ldb = in;   // x[n][i], k = n
+    const hipError_t e = gemm<false, false>(a, bf16, st);
+    if (e != hipSuccess || !db) return e;
+    // the column sums of dy (not a product, so never rounded to bf16)
+    PSW_LAUNCH(kname("col_sum_k"), (Work{(double)n * out, kF * ((double)n * out + out)}), col_sum_k,
+               dim3((unsigned)((out + 63) / 64)), dim3(256), 0, st, n, out, dy, db);
+    return hipGetLastError();
+}
+
+}  // namespace psw

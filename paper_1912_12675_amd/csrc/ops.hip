@@ -1,4 +1,4 @@
-// Batch norm (+residual, +ReLU), pooling, fully-connected GEMMs, softmax
+// Batch norm (+residual, +ReLU), pooling, small fully-connected layers, softmax
 // cross-entropy and the SGD-momentum update for gfx950.
 //
 // Reductions (BN statistics, BN backward sums, bias gradients, the loss) are
@@ -11,10 +11,6 @@
 
 namespace psw {
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned short v8us __attribute__((ext_vector_type(8)));
 
 constexpr int kBlock = 256;
 
@@ -547,187 +543,11 @@ __global__ __launch_bounds__(kSgdBlock) void sgd_stage_k(SgdSegs segs, const flo
     }
 }
 
-// ------------------------------------------------------ FC GEMM (MFMA) -----
-// C[m][n] = sum_k A(m,k) B(k,n); A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn]
-struct GemmArgs {
-    const float* A;
-    const float* B;
-    float* C;
-    const float* bias;  // per column n (direct mode only)
-    int M, N, K;
-    int64_t sam, sak, sbk, sbn;
-    int kchunk;
-    int relu, accumulate;
-    int partial;  // 1: write raw sums to C + z*M*N
-};
-
 __device__ __forceinline__ float round_bf16(float f)
 {
     uint32_t u = __float_as_uint(f);
     if ((u & 0x7f800000u) != 0x7f800000u) u += 0x7fffu + ((u >> 16) & 1u);
     return __uint_as_float(u & 0xffff0000u);
-}
-
-template <int BM, int BN, int WM, int WN, bool BF16, bool AK, bool BKC>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a)
-{
-    constexpr int BK = BF16 ? 32 : 16;
-    constexpr int KSTEP = BF16 ? 32 : 4;
-    constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
-    __shared__ float As[BK][BM + 4];
-    __shared__ float Bs[BK][BN + 4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int kbeg = blockIdx.z * a.kchunk;
-    const int kend = min(a.K, kbeg + a.kchunk);
-    v4f acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = kbeg; k0 < kend; k0 += BK) {
-#pragma unroll
-        for (int e = 0; e < (BM * BK + 255) / 256; ++e) {
-            const int idx = e * 256 + tid;
-            if (idx < BM * BK) {
-                int kk, mm;
-                if (AK) { kk = idx % BK; mm = idx / BK; } else { mm = idx % BM; kk = idx / BM; }
-                const int m = m0 + mm, k = k0 + kk;
-                const float v = (m < a.M && k < kend) ? a.A[(int64_t)m * a.sam + (int64_t)k * a.sak] : 0.f;
-                As[kk][mm] = BF16 ? round_bf16(v) : v;
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < (BN * BK + 255) / 256; ++e) {
-            const int idx = e * 256 + tid;
-            if (idx < BN * BK) {
-                int kk, nn;
-                if (BKC) { kk = idx % BK; nn = idx / BK; } else { nn = idx % BN; kk = idx / BN; }
-                const int n = n0 + nn, k = k0 + kk;
-                const float v = (n < a.N && k < kend) ? a.B[(int64_t)k * a.sbk + (int64_t)n * a.sbn] : 0.f;
-                Bs[kk][nn] = BF16 ? round_bf16(v) : v;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < BK; ks += KSTEP) {
-            if constexpr (!BF16) {
-                float af[TM], bfr[TN];
-#pragma unroll
-                for (int i = 0; i < TM; ++i) af[i] = As[ks + (lane >> 4)][wm * (BM / WM) + i * 16 + (lane & 15)];
-#pragma unroll
-                for (int j = 0; j < TN; ++j) bfr[j] = Bs[ks + (lane >> 4)][wn * (BN / WN) + j * 16 + (lane & 15)];
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], bfr[j], acc[i][j], 0, 0, 0);
-            } else {
-                v8bf af[TM], bfr[TN];
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    v8us u;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        u[e] = (unsigned short)(__float_as_uint(
-                                   As[ks + 8 * (lane >> 4) + e][wm * (BM / WM) + i * 16 + (lane & 15)]) >> 16);
-                    af[i] = __builtin_bit_cast(v8bf, u);
-                }
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    v8us u;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        u[e] = (unsigned short)(__float_as_uint(
-                                   Bs[ks + 8 * (lane >> 4) + e][wn * (BN / WN) + j * 16 + (lane & 15)]) >> 16);
-                    bfr[j] = __builtin_bit_cast(v8bf, u);
-                }
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + wn * (BN / WN) + j * 16 + (lane & 15);
-            if (n >= a.N) continue;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int m = m0 + wm * (BM / WM) + i * 16 + 4 * (lane >> 4) + v;
-                if (m >= a.M) continue;
-                float val = acc[i][j][v];
-                if (a.partial) {
-                    a.C[((int64_t)blockIdx.z * a.M + m) * a.N + n] = val;
-                } else {
-                    if (a.bias) val += a.bias[n];
-                    if (a.relu) val = fmaxf(val, 0.f);
-                    float* dst = a.C + (int64_t)m * a.N + n;
-                    *dst = a.accumulate ? *dst + val : val;
-                }
-            }
-        }
-}
-
-__global__ void gemm_reduce(const float* part, int splits, int M, int N, const float* bias, int relu, int accumulate,
-                            float* C)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t count = (int64_t)M * N;
-    if (i >= count) return;
-    float v = 0.f;
-    for (int z = 0; z < splits; ++z) v += part[(int64_t)z * count + i];
-    if (bias) v += bias[i % N];
-    if (relu) v = fmaxf(v, 0.f);
-    C[i] = accumulate ? C[i] + v : v;
-}
-
-template <bool AK, bool BKC>
-hipError_t gemm(GemmArgs a, int bf16, void* ws, size_t ws_bytes, hipStream_t st)
-{
-    constexpr int BM = 64, BN = 64;
-    const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-    const int BK = bf16 ? 32 : 16;
-    int splits = 1;
-    if (tiles < 512 && ws) {
-        splits = (1024 + tiles - 1) / tiles;
-        const int maxs = (a.K + 4 * BK - 1) / (4 * BK);  // at least four BK slices per split
-        if (splits > maxs) splits = maxs;
-        while (splits > 1 && (size_t)splits * a.M * a.N * sizeof(float) > ws_bytes) --splits;
-        if (splits < 1) splits = 1;
-    }
-    const int per = (a.K + splits - 1) / splits;
-    a.kchunk = ((per + BK - 1) / BK) * BK;
-    splits = (a.K + a.kchunk - 1) / a.kchunk;
-    if (splits < 1) splits = 1;
-    float* out = a.C;
-    const float* bias = a.bias;
-    const int relu = a.relu, accum = a.accumulate;
-    if (splits > 1) {
-        a.partial = 1;
-        a.C = (float*)ws;
-    }
-    dim3 grid((a.N + BN - 1) / BN, (a.M + BM - 1) / BM, splits);
-    const Work gw{2.0 * a.M * a.N * (double)a.K, kF * ((double)a.M * a.K + (double)a.K * a.N + (double)a.M * a.N)};
-    if (bf16)
-        PSW_LAUNCH(kname("gemm_kernel", BM, BN, 2, 2, true, AK, BKC), gw, (gemm_kernel<BM, BN, 2, 2, true, AK, BKC>),
-                   grid, dim3(256), 0, st, a);
-    else
-        PSW_LAUNCH(kname("gemm_kernel", BM, BN, 2, 2, false, AK, BKC), gw, (gemm_kernel<BM, BN, 2, 2, false, AK, BKC>),
-                   grid, dim3(256), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
-    const int64_t count = (int64_t)a.M * a.N;
-    PSW_LAUNCH(kname("gemm_reduce"), (Work{(double)splits * count, kF * (splits + 1.0 + accum) * count}), gemm_reduce,
-               dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, (const float*)ws, splits,
-                       a.M, a.N, bias, relu, accum, out);
-    return hipGetLastError();
 }
 
 inline unsigned blocks_for(int64_t n, int b = kBlock) { return (unsigned)((n + b - 1) / b); }
@@ -745,6 +565,11 @@ bool small_fc(int n, int in, int out)
 {
     return n <= kFcMaxN && out <= kFcMaxOut && (int64_t)n * out <= kSmallFcLogits && in <= 4096;
 }
+
+// The forward kernel is one workgroup: its time grows with in (128 rows, 10
+// outputs: 64 features 9 us, 512 41 us, 4096 275 us), while gemm_rows spreads
+// rows and k (8 us) and the loss takes a launch of its own (6 us).
+constexpr int kSmallFwdIn = 96;
 
 // y[i][o] = sum_k x[i][k] w[o][k] (+ b[o]) (relu), k ascending, from LDS
 // chunks of kFcKC columns; with labels: also the mean softmax cross-entropy
@@ -1623,25 +1448,20 @@ hipError_t dropout_apply(int64_t n, const float* in, float* out, int accumulate,
 hipError_t fc_fwd(int n, int in, int out, const float* x, const float* w, const float* b, int relu, float* y, int bf16,
                   hipStream_t st)
 {
-    if (small_fc(n, in, out)) {
+    if (small_fc(n, in, out) && in <= kSmallFwdIn) {
         const double fl = 2.0 * n * out * (double)in;
         PSW_LAUNCH(kname("fc_small_fwd_k"), (Work{fl, kF * ((double)n * in + (double)out * in + (double)n * out)}),
                    fc_small_fwd_k, dim3(1), dim3(kHeadBlock), 0, st, n, in, out, x, w, b, relu, bf16, y,
                    (const int32_t*)nullptr, (float*)nullptr, (float*)nullptr);
         return hipGetLastError();
     }
-    GemmArgs a{};
-    a.A = x; a.B = w; a.C = y; a.bias = b; a.relu = relu;
-    a.M = n; a.N = out; a.K = in;
-    a.sam = in; a.sak = 1;    // x[n][i]
-    a.sbk = 1; a.sbn = in;    // w[o][i]
-    return gemm<true, true>(a, bf16, nullptr, 0, st);
+    return fc_gemm_fwd(n, in, out, x, w, b, relu, y, bf16, st);
 }
 
 hipError_t fc_softmax_xent(int n, int in, int out, const float* x, const float* w, const float* b, float* logits,
                            int bf16, const int32_t* labels, float* loss, float* dlogits, hipStream_t st)
 {
-    if (!small_fc(n, in, out)) return hipErrorNotSupported;
+    if (!small_fc(n, in, out) || in > kSmallFwdIn) return hipErrorNotSupported;
     const double fl = 2.0 * n * out * (double)in + 5.0 * n * out;
     PSW_LAUNCH(kname("fc_small_fwd_k"),
                (Work{fl, kF * ((double)n * in + (double)out * in + 3.0 * n * out + n + 1.0)}), fc_small_fwd_k, dim3(1),
@@ -1674,37 +1494,7 @@ hipError_t fc_bwd(int n, int in, int out, const float* x, const float* w, const 
                    st, n, in, out, x, w, dy, dx, dx_accumulate, dw, db, bf16, nbx);
         return hipGetLastError();
     }
-    const size_t head = (((size_t)out * 2 * sizeof(double)) + 255) / 256 * 256;
-    hipError_t e = hipSuccess;
-    if (dx) {
-        GemmArgs a{};
-        a.A = dy; a.B = w; a.C = dx; a.accumulate = dx_accumulate;
-        a.M = n; a.N = in; a.K = out;
-        a.sam = out; a.sak = 1;   // dy[n][o]
-        a.sbk = in; a.sbn = 1;    // w[o][i]
-        e = gemm<true, false>(a, bf16, (char*)ws + head, ws_bytes - head, st);
-        if (e != hipSuccess) return e;
-    }
-    {
-        GemmArgs a{};
-        a.A = dy; a.B = x; a.C = dw;
-        a.M = out; a.N = in; a.K = n;
-        a.sam = 1; a.sak = out;   // dy[n][o] read as A(m=o, k=n)
-        a.sbk = in; a.sbn = 1;    // x[n][i]
-        e = gemm<false, false>(a, bf16, nullptr, 0, st);
-        if (e != hipSuccess) return e;
-    }
-    if (db) {
-        // db[o] = sum_n dy[n][o]: the column sums of dy viewed as [n][out][1]
-        // (not a product, so never rounded to bf16)
-        PSW_LAUNCH(kname("chan_partials"), (Work{(double)n * out, kF * n * out}), chan_partials, dim3(out, 1),
-                   dim3(kBlock), 0, st, 2, n, out, 1, 1, dy, (const float*)nullptr, (const float*)nullptr,
-                   (const float*)nullptr, (const float*)nullptr, 0, (double*)ws);
-        PSW_LAUNCH(kname("chan_sum_finalize"), (Work{(double)out, 16.0 * out + kF * out}), chan_sum_finalize,
-                   dim3(blocks_for(out)), dim3(kBlock), 0, st, out, 1, (const double*)ws, db);
-        e = hipGetLastError();
-    }
-    return e;
+    return fc_gemm_bwd(n, in, out, x, w, dy, dx, dx_accumulate, dw, db, bf16, st);
 }
 
 }  // namespace psw

@@ -129,3 +129,68 @@ def test_conv_not_finite(P, case):
     dw = torch.empty(w.shape, device="cuda")
     P.psw_conv_bwd_weight(dev(x), dev(dy), dw, st, pad)
     same_class(dw, torch.nn.grad.conv2d_weight(d(x), w.shape, d(dy), st, pad), "bwd_weight")
+
+
+FC = [
+    # N, in, out
+    (1, 1, 65),
+    (3, 5, 65),
+    (16, 400, 120),      # LeNet-5
+    (16, 120, 84),
+    (17, 33, 129),
+    (33, 31, 4096),      # outputs by the row, a reduction shorter than a step
+    (1, 4097, 70),       # deep reductions, one k past a stage
+    (20, 2047, 66),
+    (130, 130, 66),
+    (257, 16, 10),       # more rows than the small classifier takes
+    (128, 5000, 300),
+    (300, 200, 1100),    # tiles of 128 x 128 in the weight gradient
+    (128, 96, 16400),
+]
+
+
+def fc_data(case):
+    n, fin, out = case
+    rng = np.random.default_rng(n * 31 + fin * 7 + out)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)  # noqa: E731
+    return f(n, fin), f(out, fin) * 0.3, f(out), f(n, out), f(n, fin)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("case", FC, ids=lambda c: "x".join(map(str, c)))
+def test_fc_edges(P, case, bf16):
+    print("fc", case, bf16, flush=True)
+    x, w, b, dy, base = fc_data(case)
+    rd = lambda a: (torch.from_numpy(a).bfloat16() if bf16 else torch.from_numpy(a)).double()  # noqa: E731
+    y = torch.empty(dy.shape, device="cuda")
+    ref = (rd(x) @ rd(w).t()).numpy()
+    P.psw_fc_fwd(dev(x), dev(w), y, bf16=bf16)
+    close(y, ref, "fwd")
+    P.psw_fc_fwd(dev(x), dev(w), y, b=dev(b), relu=True, bf16=bf16)
+    close(y, np.maximum(ref + b, 0), "fwd + bias + relu")
+    refdx, refdw = (rd(dy) @ rd(w)).numpy(), (rd(dy).t() @ rd(x)).numpy()
+    dx, dw, db = (torch.full(s, 7.0, device="cuda") for s in (x.shape, w.shape, b.shape))
+    P.psw_fc_bwd(dev(x), dev(w), dev(dy), dw, dx=dx, db=db, bf16=bf16)
+    close(dx, refdx, "dx")
+    close(dw, refdw, "dw")
+    close(db, dy.astype(np.float64).sum(0), "db")
+    dx = dev(base)
+    P.psw_fc_bwd(dev(x), dev(w), dev(dy), dw, dx=dx, dx_accumulate=True, bf16=bf16)
+    close(dx, refdx + base, "dx accumulate")
+
+
+@pytest.mark.parametrize("case", [(20, 300, 130), (5, 1500, 70)], ids=lambda c: "x".join(map(str, c)))
+def test_fc_not_finite(P, case):
+    print("fc not finite", case, flush=True)
+    x, w, _, dy, _ = fc_data(case)
+    w[np.abs(w) < 1e-3] = 0.01
+    x[0, 3], x[1, 5], x[2, 7] = np.inf, np.nan, 3.4e38
+    dy[2] *= 0.1  # a product of the largest float that float32 holds
+    dy[3, 4], dy[4, 1] = -np.inf, np.nan
+    d = lambda a: torch.from_numpy(a).double()  # noqa: E731
+    y, dx, dw = (torch.empty(s, device="cuda") for s in (dy.shape, x.shape, w.shape))
+    P.psw_fc_fwd(dev(x), dev(w), y)
+    same_class(y, d(x) @ d(w).t(), "fwd")
+    P.psw_fc_bwd(dev(x), dev(w), dev(dy), dw, dx=dx)
+    same_class(dx, d(dy) @ d(w), "dx")
+    same_class(dw, d(dy).t() @ d(x), "dw")
