@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(os.path.dirname(HERE), "_build")
 LIB = os.path.join(HERE, "libpsw.so")
-SOURCES = ["conv.hip", "gconv.hip", "gwgrad.hip", "direct.hip", "wgrad.hip", "fc.hip", "ops.hip", "api.hip"]
+SOURCES = ["conv.hip", "gconv.hip", "gwgrad.hip", "direct.hip", "wgrad.hip", "fc.hip", "bn.hip", "ops.hip", "api.hip"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

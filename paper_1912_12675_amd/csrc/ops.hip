@@ -1,4 +1,4 @@
-// Batch norm (+residual, +ReLU), pooling, small fully-connected layers, softmax
+// Batch norm from fused statistics, pooling, small fully-connected layers, softmax
 // cross-entropy and the SGD-momentum update for gfx950.
 //
 // Reductions (BN statistics, BN backward sums, bias gradients, the loss) are
@@ -63,168 +63,6 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double* sh)
         b = tb;
     }
     __syncthreads();
-}
-
-int channel_splits(int n, int c)
-{
-    int sp = (1024 + c - 1) / c;
-    if (sp > n) sp = n;
-    if (sp < 1) sp = 1;
-    return sp;
-}
-
-// ---------------------------------------------------------------- BN -------
-// mode 0: sum y, sum y^2              (forward statistics)
-// mode 1: sum g, sum g*xhat with g = dz*[z>0 if relu]   (backward sums)
-// mode 2: sum x                       (bias gradient; second slot unused)
-__global__ __launch_bounds__(kBlock) void chan_partials(int mode, int n, int c, int hw, int split, const float* x,
-                                                         const float* z, const float* y, const float* mean,
-                                                         const float* invstd, int relu, double* part)
-{
-    __shared__ double sh[kBlock / 64];
-    const int ch = blockIdx.x, sp = blockIdx.y;
-    const int i0 = (int)((int64_t)n * sp / split), i1 = (int)((int64_t)n * (sp + 1) / split);
-    const int64_t total = (int64_t)(i1 - i0) * hw;
-    double s1 = 0.0, s2 = 0.0;
-    const double mu = mode == 1 ? (double)mean[ch] : 0.0;
-    const double is = mode == 1 ? (double)invstd[ch] : 0.0;
-    for (int64_t idx = threadIdx.x; idx < total; idx += kBlock) {
-        const int img = i0 + (int)(idx / hw);
-        const int off = (int)(idx - (int64_t)(img - i0) * hw);
-        const size_t g = ((size_t)img * c + ch) * hw + off;
-        const double v = x[g];
-        if (mode == 0) {
-            s1 += v;
-            s2 += v * v;
-        } else if (mode == 1) {
-            const double gg = (relu && !(z[g] > 0.f)) ? 0.0 : v;
-            s1 += gg;
-            s2 += gg * ((double)y[g] - mu) * is;
-        } else {
-            s1 += v;
-        }
-    }
-    s1 = block_sum(s1, sh);
-    s2 = block_sum(s2, sh);
-    if (threadIdx.x == 0) {
-        part[((size_t)ch * split + sp) * 2 + 0] = s1;
-        part[((size_t)ch * split + sp) * 2 + 1] = s2;
-    }
-}
-
-__global__ void bn_fwd_finalize(int c, int split, double count, const double* part, const float* gamma,
-                                const float* beta, float eps, float momentum, float* save_mean, float* save_invstd,
-                                float* run_mean, float* run_var, float* coef, float* save_scale)
-{
-    const int ch = blockIdx.x * blockDim.x + threadIdx.x;
-    if (ch >= c) return;
-    double s1 = 0.0, s2 = 0.0;
-    for (int sp = 0; sp < split; ++sp) {
-        s1 += part[((size_t)ch * split + sp) * 2 + 0];
-        s2 += part[((size_t)ch * split + sp) * 2 + 1];
-    }
-    const double mean = s1 / count;
-    double var = s2 / count - mean * mean;
-    if (var < 0.0) var = 0.0;
-    const double invstd = 1.0 / sqrt(var + (double)eps);
-    save_mean[ch] = (float)mean;
-    save_invstd[ch] = (float)invstd;
-    if (run_mean) run_mean[ch] = (float)((1.0 - momentum) * run_mean[ch] + momentum * mean);
-    if (run_var)
-        run_var[ch] = (float)((1.0 - momentum) * run_var[ch] +
-                              momentum * (count > 1.0 ? var * count / (count - 1.0) : var));
-    const double scale = (double)gamma[ch] * invstd;
-    coef[2 * ch + 0] = (float)scale;
-    coef[2 * ch + 1] = (float)((double)beta[ch] - mean * scale);
-    if (save_scale) {
-        save_scale[ch] = coef[2 * ch + 0];
-        save_scale[c + ch] = coef[2 * ch + 1];
-    }
-}
-
-__global__ void bn_fwd_apply(int64_t total, int c, int hw, const float* y, const float* coef, const float* res,
-                             int rc, int rh, int rw, int h, int w, int relu, float* z)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int64_t nc = i / hw;
-    const int ch = (int)(nc % c);
-    float v = __fmaf_rn(y[i], coef[2 * ch], coef[2 * ch + 1]);
-    if (res) {
-        if (rc == c && rh == h && rw == w) {
-            v += res[i];
-        } else {
-            const int lo = (c - rc) / 2, cc = ch - lo;
-            if (cc >= 0 && cc < rc) {
-                const int img = (int)(nc / c), off = (int)(i - nc * hw);
-                const int hh = off / w, ww = off - hh * w;
-                v += res[(((size_t)img * rc + cc) * rh + hh * (rh / h)) * rw + ww * (rw / w)];
-            }
-        }
-    }
-    if (relu) v = fmaxf(v, 0.f);
-    z[i] = v;
-}
-
-__global__ void bn_bwd_finalize(int c, int split, double count, const double* part, const float* gamma,
-                                const float* invstd, float* dgamma, float* dbeta, float* coef)
-{
-    const int ch = blockIdx.x * blockDim.x + threadIdx.x;
-    if (ch >= c) return;
-    double s1 = 0.0, s2 = 0.0;
-    for (int sp = 0; sp < split; ++sp) {
-        s1 += part[((size_t)ch * split + sp) * 2 + 0];
-        s2 += part[((size_t)ch * split + sp) * 2 + 1];
-    }
-    dbeta[ch] = (float)s1;
-    dgamma[ch] = (float)s2;
-    coef[3 * ch + 0] = (float)((double)gamma[ch] * (double)invstd[ch]);
-    coef[3 * ch + 1] = (float)(s1 / count);
-    coef[3 * ch + 2] = (float)(s2 / count);
-}
-
-__global__ void bn_bwd_apply(int64_t total, int c, int hw, const float* dz, const float* z, const float* y,
-                             const float* mean, const float* invstd, const float* coef, int relu, float* dy,
-                             float* dres_identity, int res_accumulate)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int ch = (int)((i / hw) % c);
-    const float g = (relu && !(z[i] > 0.f)) ? 0.f : dz[i];
-    const float xh = (y[i] - mean[ch]) * invstd[ch];
-    dy[i] = coef[3 * ch] * (g - coef[3 * ch + 1] - xh * coef[3 * ch + 2]);
-    if (dres_identity) dres_identity[i] = res_accumulate ? dres_identity[i] + g : g;
-}
-
-// option-A shortcut backward: dres[n][cr][hr][wr] gets g[n][cr+lo][hr/sh][wr/sw]
-// at subsampled positions and zero elsewhere
-__global__ void shortcut_a_bwd(int64_t total, int c, int h, int w, int rc, int rh, int rw, const float* dz,
-                               const float* z, int relu, float* dres, int accumulate)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int rhw = rh * rw;
-    const int64_t ncr = i / rhw;
-    const int off = (int)(i - ncr * rhw);
-    const int cr = (int)(ncr % rc), img = (int)(ncr / rc);
-    const int hr = off / rw, wr = off - hr * rw;
-    const int sh = rh / h, sw = rw / w;
-    float g = 0.f;
-    if (hr % sh == 0 && wr % sw == 0) {
-        const int ch = cr + (c - rc) / 2;
-        const size_t j = (((size_t)img * c + ch) * h + hr / sh) * w + wr / sw;
-        g = (relu && !(z[j] > 0.f)) ? 0.f : dz[j];
-    }
-    dres[i] = accumulate ? dres[i] + g : g;
-}
-
-__global__ void chan_sum_finalize(int c, int split, const double* part, float* out)
-{
-    const int ch = blockIdx.x * blockDim.x + threadIdx.x;
-    if (ch >= c) return;
-    double s = 0.0;
-    for (int sp = 0; sp < split; ++sp) s += part[((size_t)ch * split + sp) * 2];
-    out[ch] = (float)s;
 }
 
 // -------------------------------------------------------------- pooling ----
@@ -736,85 +574,6 @@ __global__ __launch_bounds__(kBlock) void fc_small_bwd_k(int n, int in, int out,
 }  // namespace
 
 // ------------------------------------------------------------ launchers -----
-size_t channel_sum_ws_bytes(int n, int c, int hw)
-{
-    (void)hw;
-    return (size_t)c * channel_splits(n, c) * 2 * sizeof(double);
-}
-
-hipError_t channel_sum(int n, int c, int hw, const float* x, float* out, void* ws, size_t ws_bytes, hipStream_t st)
-{
-    const int sp = channel_splits(n, c);
-    if (ws_bytes < channel_sum_ws_bytes(n, c, hw)) return hipErrorInvalidValue;
-    const double elems = (double)n * c * hw;
-    PSW_LAUNCH(kname("chan_partials"), (Work{elems, kF * elems}), chan_partials, dim3(c, sp), dim3(kBlock), 0, st, 2,
-               n, c, hw, sp, x, (const float*)nullptr, (const float*)nullptr, (const float*)nullptr,
-               (const float*)nullptr, 0, (double*)ws);
-    PSW_LAUNCH(kname("chan_sum_finalize"), (Work{(double)c * sp, 16.0 * c * sp + kF * c}), chan_sum_finalize,
-               dim3(blocks_for(c)), dim3(kBlock), 0, st, c, sp, (const double*)ws, out);
-    return hipGetLastError();
-}
-
-size_t bn_ws_bytes(int n, int c, int h, int w)
-{
-    (void)h; (void)w;
-    return (size_t)c * channel_splits(n, c) * 2 * sizeof(double) + (size_t)c * 3 * sizeof(float) + 256;
-}
-
-hipError_t bn_fwd(int n, int c, int h, int w, const float* y, const float* gamma, const float* beta, const float* res,
-                  int rc, int rh, int rw, int relu, float eps, float momentum, float* z, float* save_mean,
-                  float* save_invstd, float* run_mean, float* run_var, void* ws, size_t ws_bytes, hipStream_t st,
-                  float* save_scale)
-{
-    if (ws_bytes < bn_ws_bytes(n, c, h, w)) return hipErrorInvalidValue;
-    const int sp = channel_splits(n, c);
-    const int hw = h * w;
-    double* part = (double*)ws;
-    float* coef = (float*)((char*)ws + (size_t)c * sp * 2 * sizeof(double));
-    const int64_t total = (int64_t)n * c * hw;
-    PSW_LAUNCH(kname("chan_partials"), (Work{3.0 * total, kF * total}), chan_partials, dim3(c, sp), dim3(kBlock), 0, st,
-               0, n, c, hw, sp, y, (const float*)nullptr, (const float*)nullptr, (const float*)nullptr,
-               (const float*)nullptr, 0, part);
-    PSW_LAUNCH(kname("bn_fwd_finalize"), (Work{2.0 * c * sp, 16.0 * c * sp + 6 * kF * c}), bn_fwd_finalize,
-               dim3(blocks_for(c)), dim3(kBlock), 0, st, c, sp, (double)n * hw, (const double*)part, gamma, beta, eps,
-               momentum, save_mean, save_invstd, run_mean, run_var, coef, save_scale);
-    const double rbytes = res ? kF * (double)n * std::min(c, rc) * hw : 0.0;
-    PSW_LAUNCH(kname("bn_fwd_apply"), (Work{3.0 * total, kF * 2.0 * total + rbytes}), bn_fwd_apply,
-               dim3(blocks_for(total)), dim3(kBlock), 0, st, total, c, hw, y, (const float*)coef, res, rc, rh, rw, h, w,
-               relu, z);
-    return hipGetLastError();
-}
-
-hipError_t bn_bwd(int n, int c, int h, int w, const float* dz, const float* z, const float* y, const float* gamma,
-                  const float* save_mean, const float* save_invstd, int relu, float* dy, float* dgamma,
-                  float* dbeta, float* dres, int rc, int rh, int rw, int res_accumulate, void* ws, size_t ws_bytes,
-                  hipStream_t st)
-{
-    if (ws_bytes < bn_ws_bytes(n, c, h, w)) return hipErrorInvalidValue;
-    const int sp = channel_splits(n, c);
-    const int hw = h * w;
-    double* part = (double*)ws;
-    float* coef = (float*)((char*)ws + (size_t)c * sp * 2 * sizeof(double));
-    const int64_t total = (int64_t)n * c * hw;
-    PSW_LAUNCH(kname("chan_partials"), (Work{5.0 * total, 3 * kF * total}), chan_partials, dim3(c, sp), dim3(kBlock), 0,
-               st, 1, n, c, hw, sp, dz, z, y, save_mean, save_invstd, relu, part);
-    PSW_LAUNCH(kname("bn_bwd_finalize"), (Work{2.0 * c * sp, 16.0 * c * sp + 7 * kF * c}), bn_bwd_finalize,
-               dim3(blocks_for(c)), dim3(kBlock), 0, st, c, sp, (double)n * hw, (const double*)part, gamma, save_invstd,
-               dgamma, dbeta, coef);
-    const bool identity = dres && rc == c && rh == h && rw == w;
-    PSW_LAUNCH(kname("bn_bwd_apply"),
-               (Work{6.0 * total, kF * (4.0 + (identity ? 1.0 + res_accumulate : 0.0)) * total}), bn_bwd_apply,
-               dim3(blocks_for(total)), dim3(kBlock), 0, st, total, c, hw, dz, z, y, save_mean, save_invstd,
-               (const float*)coef, relu, dy, identity ? dres : (float*)nullptr, res_accumulate);
-    if (dres && !identity) {
-        const int64_t rtotal = (int64_t)n * rc * rh * rw;
-        PSW_LAUNCH(kname("shortcut_a_bwd"), (Work{0.0, kF * ((1.0 + res_accumulate) * rtotal + 2.0 * n * rc * hw)}),
-                   shortcut_a_bwd, dim3(blocks_for(rtotal)), dim3(kBlock), 0, st, rtotal, c, h, w, rc, rh, rw, dz, z,
-                   relu, dres, res_accumulate);
-    }
-    return hipGetLastError();
-}
-
 namespace {
 // Both kernels run on grid (c, blocks per channel): every block first merges
 // its channel's T per-tile partials in a fixed order (so all blocks of a

@@ -194,3 +194,69 @@ def test_fc_not_finite(P, case):
     P.psw_fc_bwd(dev(x), dev(w), dev(dy), dw, dx=dx)
     same_class(dx, d(dy) @ d(w), "dx")
     same_class(dw, d(dy).t() @ d(x), "dw")
+
+
+BN = [
+    # N, C, H, W, residual, relu: wide and flat planes, by fours and one by one, odd images and channels
+    (3, 3, 1, 2, None, False),  # six values a channel (of two, dy is nothing but cancellation)
+    (5, 7, 3, 5, "identity", True),
+    (33, 300, 2, 2, "identity", True),
+    (17, 64, 4, 4, None, True),
+    (9, 40, 8, 8, "half", True),
+    (6, 20, 15, 17, "identity", True),     # 255 elements: one by one, a plane just below a block
+    (6, 20, 16, 16, "half", False),
+    (3, 12, 14, 18, "third", True),        # 252 = 63 units: the largest flat plane
+    (130, 5, 16, 16, None, True),
+    (2, 4, 66, 66, "half", True),
+]
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("case", BN, ids=lambda c: "x".join(map(str, c)))
+def test_bn_edges(P, case, accumulate):
+    """Sums are taken in double; what is left is the rounding of a few float operations per element."""
+    print("bn", case, accumulate, flush=True)
+    N, C, H, W, kind, relu = case
+    rng = np.random.default_rng(N * 100 + C)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)  # noqa: E731
+    y, gamma, beta, dz = f(N, C, H, W) * 2 + 0.5, f(C), f(C), f(N, C, H, W)
+    z0 = np.maximum(f(N, C, H, W), 0)  # the output the backward pass masks by
+    fac, rc = {"half": (2, C // 2), "third": (3, C // 3)}.get(kind, (1, C))
+    res = None if kind is None else f(N, rc, H * fac, W * fac)
+    lo = (C - rc) // 2
+    t = lambda a: torch.from_numpy(a).double()  # noqa: E731
+    mean, var = t(y).mean((0, 2, 3)), t(y).var((0, 2, 3), unbiased=False)
+    inv = 1 / torch.sqrt(var + 1e-5)
+    v = lambda a: a.view(1, -1, 1, 1)  # noqa: E731
+    xh = (t(y) - v(mean)) * v(inv)
+    ref = xh * v(t(gamma)) + v(t(beta))
+    if res is not None:
+        ref = ref + torch.nn.functional.pad(t(res)[:, :, ::fac, ::fac], (0, 0, 0, 0, lo, lo))
+    ref = ref.clamp(min=0) if relu else ref
+    out = torch.empty(y.shape, device="cuda")
+    sm, si, dg, db = (torch.empty(C, device="cuda") for _ in range(4))
+    rm, rv = torch.zeros(C, device="cuda"), torch.ones(C, device="cuda")
+    P.psw_bn_relu_fwd(dev(y), dev(gamma), dev(beta), out, sm, si, res=None if res is None else dev(res), relu=relu,
+                      run_mean=rm, run_var=rv)
+    m = N * H * W
+    for got, want, what in ((out, ref, "z"), (sm, mean, "mean"), (si, inv, "invstd"), (rm, 0.1 * mean, "run_mean"),
+                            (rv, 0.9 + 0.1 * var * (m / (m - 1)), "run_var")):
+        close(got, want.numpy(), what)
+    g = t(dz) * (t(z0) > 0) if relu else t(dz)
+    sb, sg = g.sum((0, 2, 3)), (g * xh).sum((0, 2, 3))
+    refdy = v(t(gamma) * inv) * (g - v(sb) / m - xh * v(sg) / m)
+    dy = torch.empty(y.shape, device="cuda")
+    dres = base = None
+    if res is not None:
+        base = f(*res.shape)
+        dres = dev(base)
+        refres = torch.zeros(res.shape, dtype=torch.float64)
+        refres[:, :, ::fac, ::fac] = g[:, lo:lo + rc]
+        refres = refres + t(base) if accumulate else refres
+    P.psw_bn_relu_bwd(dev(dz), dev(z0), dev(y), dev(gamma), sm, si, dy, dg, db, dres=dres, relu=relu,
+                      res_accumulate=accumulate)
+    close(dg, sg.numpy(), "dgamma")
+    close(db, sb.numpy(), "dbeta")
+    close(dy, refdy.numpy(), "dy")
+    if res is not None:
+        close(dres, refres.numpy(), "dres")
