@@ -260,3 +260,32 @@ def test_bn_edges(P, case, accumulate):
     close(dy, refdy.numpy(), "dy")
     if res is not None:
         close(dres, refres.numpy(), "dres")
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("case", [(3, 5, 8, 8, 2), (2, 3, 9, 12, 2), (2, 3, 7, 10, 2), (2, 3, 8, 7, 2), (1, 1, 2, 2, 2),
+                                  (2, 4, 11, 13, 3), (5, 67, 32, 32, 2)], ids=lambda c: "x".join(map(str, c)))
+def test_maxpool_edges(P, case, accumulate):
+    """Rows by fours, by twos and one by one, planes with a row or column no window covers; ties and NaNs: exact."""
+    print("pool", case, accumulate, flush=True)
+    N, C, H, W, k = case
+    rng = np.random.default_rng(N + H * W)
+    x = np.maximum(rng.integers(-3, 4, (N, C, H, W)), 0).astype(np.float32)
+    x[0, 0, 0, 0], x[0, 0, 1, 1], x[-1, -1, 0, 1] = np.nan, np.inf, np.nan
+    p, q = H // k, W // k
+    win = x[:, :, :p * k, :q * k].reshape(N, C, p, k, q, k).transpose(0, 1, 2, 4, 3, 5).reshape(N, C, p, q, k * k)
+    best, at = win[..., 0].copy(), np.zeros((N, C, p, q), dtype=np.int64)
+    for e in range(1, k * k):
+        better = win[..., e] > best
+        best[better], at[better] = win[..., e][better], e
+    flat = (np.arange(p)[:, None] * k + at // k) * W + np.arange(q) * k + at % k
+    y, arg = torch.empty((N, C, p, q), device="cuda"), torch.empty((N, C, p, q), dtype=torch.int32, device="cuda")
+    P.psw_pool_fwd(P.PSW_POOL_MAX, dev(x), y, k, k, argmax=arg)
+    assert np.array_equal(y.cpu().numpy(), best, equal_nan=True) and np.array_equal(arg.cpu().numpy(), flat)
+    dy, base = (rng.standard_normal(s).astype(np.float32) for s in (best.shape, x.shape))
+    ref = np.zeros((N, C, H * W), dtype=np.float32)
+    np.put_along_axis(ref, flat.reshape(N, C, -1), dy.reshape(N, C, -1), 2)
+    dx = dev(base)
+    P.psw_pool_bwd(P.PSW_POOL_MAX, x.shape, dev(dy), dx, k, k, argmax=arg, accumulate=accumulate)
+    ref = ref.reshape(x.shape) + base if accumulate else ref.reshape(x.shape)
+    assert np.array_equal(dx.cpu().numpy(), ref)
