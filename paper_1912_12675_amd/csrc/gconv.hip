@@ -25,10 +25,10 @@
 // (deep reductions over few positions); their sums meet in LDS in wave order.
 //
 // Measured against the implicit GEMM that gathered (and, for each tap, divided
-// indices) element by element, fp32 unless stated: backward data 512 -> 512
-// 3x3 at 4x4, batch 128, 1,382 us on average over VGG-16's layers there ->
-// 160 us; forward 185 us; 5x5 64 -> 192 at 16x16 b128 bf16 forward 751 -> 80,
-// backward data 1,330 -> 164 us; VGG-16 b128 step 18.9 -> 6.0 ms.
+// indices) element by element, batch 128, us, fp32 unless stated: 512 -> 512
+// 3x3 at 4x4 forward 126, backward data 116 (1,382 on average over VGG-16's
+// layers there); 5x5 64 -> 192 at 16x16 forward 104, bf16 forward 751 -> 61 and
+// backward data 1,330 -> 79.
 #include "internal.h"
 #include "split.h"
 
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
     constexpr int SLOTS = 4 * KG, TG = SLOTS / OC;   // slots and taps of a weight group
     constexpr int AROW = SLOTS + 1;                  // units per weight row: odd, so the 16 rows spread over the banks
     constexpr int AI = BM * SLOTS, AV = (AI + NT - 1) / NT;
-    constexpr int BV = 3;                            // input units per thread and staging pass
+    constexpr int BV = OC * BP / NT > 2 ? OC * BP / NT : OC * BP / NT + 1;  // input units per thread in registers
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     // this workgroup's class, channel block and tile.  Consecutive workgroups
@@ -172,21 +172,21 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
     int bsrc[BV], bch[BV];
 #pragma unroll
     for (int v = 0; v < BV; ++v) bsrc[v] = unit_at(tid + v * NT, &bch[v]);
+    // Loads ahead of their use carry no branch: what a branch merges is copied
+    // to its place at once, and the copy waits for memory (the matrix work
+    // that should hide the latency came after it: 1.5 times as slow).  A chunk
+    // that does not exist reads zeros (`ok` false), and the last chunk of a
+    // channel count that is no multiple of 8 is loaded when it is stored.
     float br[BV][8];
-    auto load_unit = [&](int src, int ch, int c0, float(&r)[8]) {
-        if (c0 + 8 * OC <= a.C) {  // every channel of the chunk exists
+    auto load_b = [&](int c0, bool ok) {
+        const int lim = ok ? a.C : 0, cb = ok ? c0 : 0, step = ok ? plane * 4 : 0;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) r[e] = buffer_load(xb, src, (c0 + e) * plane * 4);
-        } else {
-            const int left = src >= 0 ? a.C - c0 - ch : 0;
+        for (int v = 0; v < BV; ++v) {
+            if (v * NT >= BI) break;
+            const int off = cb + bch[v] < lim ? bsrc[v] : kOutside;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) r[e] = buffer_load(xb, e < left ? src + (c0 + e) * plane * 4 : kOutside, 0);
+            for (int e = 0; e < 8; ++e) br[v][e] = buffer_load(xb, off, (cb + e) * step);
         }
-    };
-    auto load_b = [&](int c0) {
-#pragma unroll
-        for (int v = 0; v < BV; ++v)
-            if (v * NT < BI) load_unit(bsrc[v], bch[v], c0, br[v]);
     };
     auto put_unit = [&](sp_v8b* dst, int plane_units, const float(&r)[8]) {
         sp_v8b parts[NS];
@@ -194,65 +194,78 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
 #pragma unroll
         for (int s = 0; s < NS; ++s) dst[s * plane_units] = parts[s];
     };
-    auto store_b = [&](int c0) {
+    auto store_b = [&](int c0, bool now) {
+        if (!now)
 #pragma unroll
-        for (int v = 0; v < BV; ++v)
-            if (tid + v * NT < BI) put_unit(Bs + tid + v * NT, BI, br[v]);
-        for (int idx = tid + BV * NT; idx < BI; idx += NT) {  // a tile of more units than the registers hold
-            float r[8];
+            for (int v = 0; v < BV; ++v)
+                if (tid + v * NT < BI) put_unit(Bs + tid + v * NT, BI, br[v]);
+        // a ragged chunk, and a tile of more units than the registers hold
+        for (int idx = tid + (now ? 0 : BV * NT); idx < BI; idx += NT) {
             int ch;
-            const int src = unit_at(idx, &ch);
-            load_unit(src, ch, c0, r);
+            const int src = unit_at(idx, &ch), left = src >= 0 ? a.C - c0 - ch : 0;
+            float r[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[e] = buffer_load(xb, e < left ? src + (c0 + e) * plane * 4 : kOutside, 0);
             put_unit(Bs + idx, BI, r);
         }
     };
     // weight units: idx = channel * SLOTS + slot
     float ar[AV][8];
-    auto load_a = [&](int c0, int grp) {
+    auto weight_at = [&](int u, int grp, int* c) -> int {  // c: its first channel within the chunk
+        const int idx = tid + u * NT;
+        const int m = idx / SLOTS, sl = idx % SLOTS, t = grp * TG + sl / OC;
+        *c = sl % OC * 8;
+        const bool in = t < ntaps && m0 + m < a.M && (AI % NT == 0 || idx < AI);
+        return in ? ((m0 + m) * a.wm + *c * a.wc + wtab[t]) * 4 : kOutside;
+    };
+    auto load_a = [&](int c0, int grp, bool ok) {
+        const int lim = ok ? a.C : 0, cb = ok ? c0 : 0, step = ok ? a.wc * 4 : 0;
+#pragma unroll
+        for (int u = 0; u < AV; ++u) {
+            int c;
+            const int src = weight_at(u, grp, &c), off = cb + c < lim ? src : kOutside;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ar[u][e] = buffer_load(wb, off, (cb + e) * step);
+        }
+    };
+    auto store_a = [&](int c0, int grp, bool now) {
 #pragma unroll
         for (int u = 0; u < AV; ++u) {
             const int idx = tid + u * NT;
-            const int m = idx / SLOTS, sl = idx % SLOTS;
-            const int t = grp * TG + sl / OC, c = sl % OC * 8;
-            const bool in = t < ntaps && m0 + m < a.M && (AI % NT == 0 || idx < AI);
-            const int src = in ? ((m0 + m) * a.wm + c * a.wc + wtab[t]) * 4 : kOutside;
-            if (c0 + 8 * OC <= a.C) {
+            if (AI % NT && idx >= AI) continue;
+            sp_v8b* const dst = As + idx / SLOTS * AROW + idx % SLOTS;
+            if (now) {
+                int c;
+                const int src = weight_at(u, grp, &c), left = src >= 0 ? a.C - c0 - c : 0;
+                float r[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) ar[u][e] = buffer_load(wb, src, (c0 + e) * a.wc * 4);
+                for (int e = 0; e < 8; ++e) r[e] = buffer_load(wb, e < left ? src + (c0 + e) * a.wc * 4 : kOutside, 0);
+                put_unit(dst, BM * AROW, r);
             } else {
-                const int left = in ? a.C - c0 - c : 0;
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    ar[u][e] = buffer_load(wb, e < left ? src + (c0 + e) * a.wc * 4 : kOutside, 0);
+                put_unit(dst, BM * AROW, ar[u]);
             }
         }
     };
-    auto store_a = [&]() {
-#pragma unroll
-        for (int u = 0; u < AV; ++u) {
-            const int idx = tid + u * NT;
-            if (AI % NT == 0 || idx < AI) put_unit(As + idx / SLOTS * AROW + idx % SLOTS, BM * AROW, ar[u]);
-        }
-    };
+    auto ragged = [&](int c0) { return a.C % 8 != 0 && a.C - c0 < 8 * OC; };
 
     __syncthreads();  // the tables
     if (ntaps > 0) {
-        load_a(0, 0);
-        load_b(0);
-        for (int c0 = 0; c0 < a.C; c0 += 8 * OC)
+        load_a(0, 0, !ragged(0));
+        load_b(0, !ragged(0));
+        for (int c0 = 0; c0 < a.C; c0 += 8 * OC) {
+            const bool now = ragged(c0), next = c0 + 8 * OC < a.C && !ragged(c0 + 8 * OC);
+            __syncthreads();  // the previous chunk's operands are read
+            store_b(c0, now);
+            store_a(c0, 0, now);
+            __syncthreads();
+            load_b(c0 + 8 * OC, next);
             for (int grp = 0; grp < ngroups; ++grp) {
-                __syncthreads();  // the previous group's operands are read
-                store_a();
-                if (grp == 0) store_b(c0);
-                __syncthreads();
-                if (grp + 1 < ngroups) {
-                    load_a(c0, grp + 1);
-                } else if (c0 + 8 * OC < a.C) {
-                    load_a(c0 + 8 * OC, 0);
-                    load_b(c0 + 8 * OC);
-                }
-                for (int ks = wk; ks < KG; ks += WK) {
-                    if ((grp * TG) * OC + ks * 4 >= ntaps * OC) break;
+                const bool last = grp + 1 == ngroups;
+                load_a(last ? c0 + 8 * OC : c0, last ? 0 : grp + 1, last ? next : !now);
+#pragma unroll
+                for (int q = 0; q < (KG + WK - 1) / WK; ++q) {
+                    const int ks = q * WK + wk;
+                    if (ks >= KG || grp * SLOTS + ks * 4 >= ntaps * OC) break;
                     const char* bp = reinterpret_cast<const char*>(Bs) + tapo[grp * SLOTS + ks * 4 + g];
                     const sp_v8b* ap = As + j * AROW + ks * 4 + g;
                     sp_v8b av[MT][NS];
@@ -260,17 +273,30 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
                     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                         for (int s = 0; s < NS; ++s) av[mt][s] = ap[(s * BM + mt * 16) * AROW];
-#pragma unroll
-                    for (int nt = 0; nt < NTL; ++nt) {
-                        sp_v8b bv[NS];
+                    // a block's operands are read while the one before it is
+                    // multiplied (left to itself the compiler reads them last)
+                    sp_v8b bv[2][NS];
+                    auto read_b = [&](int nt) {
 #pragma unroll
                         for (int s = 0; s < NS; ++s)
-                            bv[s] = *reinterpret_cast<const sp_v8b*>(bp + boff[nt] + s * BI * 16);
+                            bv[nt & 1][s] = *reinterpret_cast<const sp_v8b*>(bp + boff[nt] + s * BI * 16);
+                    };
+                    read_b(0);
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma_split<NS>(av[mt], bv, acc[mt][nt]);
+                    for (int nt = 0; nt < NTL; ++nt) {
+                        if (nt + 1 < NTL) read_b(nt + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma_split<NS>(av[mt], bv[nt & 1], acc[mt][nt]);
                     }
                 }
+                if (!last) {
+                    __syncthreads();  // the group's weights are read
+                    store_a(c0, grp + 1, now);
+                    __syncthreads();
+                }
             }
+        }
     }
 
     if constexpr (WK > 1) {  // the waves' sums, in wave order
@@ -374,10 +400,12 @@ struct Tiling {
 };
 
 // tile of bp positions over n planes of gh x gw: fewest tiles, then the
-// smallest halo
+// smallest halo, where rows shorter than 16 positions (64 bytes a load and
+// store instruction row) count as more
 Tiling pick_tile(int n, int gh, int gw, int bp, int is, int rs, int ss)
 {
     Tiling best{};
+    double best_cost = 0.0;
     for (int lw = 0; (1 << lw) <= bp; ++lw)
         for (int lh = 0; (1 << (lw + lh)) <= bp; ++lh) {
             const int tw = 1 << lw, th = 1 << lh, ti = bp >> (lw + lh);
@@ -386,7 +414,11 @@ Tiling pick_tile(int n, int gh, int gw, int bp, int is, int rs, int ss)
             Tiling t{lw, lh, (gh + th - 1) / th, (gw + tw - 1) / tw, 0, 0};
             t.tiles = (int64_t)t.tiles_h * t.tiles_w * ((n + ti - 1) / ti);
             t.hp = ti * ((th - 1) * is + rs) * ((tw - 1) * is + ss);
-            if (!best.tiles || t.tiles < best.tiles || (t.tiles == best.tiles && t.hp < best.hp)) best = t;
+            const double cost = t.hp * (tw >= 16 || tw >= gw ? 1.0 : tw >= 8 ? 1.1 : 1.4);
+            if (!best.tiles || t.tiles < best.tiles || (t.tiles == best.tiles && cost < best_cost)) {
+                best = t;
+                best_cost = cost;
+            }
         }
     return best;
 }
@@ -438,29 +470,32 @@ hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
     const int taps = p.rs * p.ss;
     auto tile = [&](int bp) { return pick_tile(a.n, p.gh, p.gw, bp, a.is, p.rs, p.ss); };
     auto blocks = [&](const Tiling& t, int bm) { return t.tiles * ((a.M + bm - 1) / bm) * p.classes; };
-    const Tiling t256 = tile(256), t64 = tile(64), t32 = tile(32);
 #define PSW_GC(T_, ...)                                                                    \
     do {                                                                                   \
-        if (lds_bytes<NS, __VA_ARGS__>(p, T_) <= kLdsMax) return launch_cfg<NS, __VA_ARGS__>(p, T_, wk, st); \
+        const Tiling t_ = T_;                                                              \
+        if (lds_bytes<NS, __VA_ARGS__>(p, t_) <= kLdsMax) return launch_cfg<NS, __VA_ARGS__>(p, t_, wk, st); \
     } while (0)
+    const Tiling t256 = tile(256);
     if (a.C <= 8) {  // an image net's first layer (forward): one octet, four taps per matrix step
         if (a.M <= 16) PSW_GC(t256, 16, 256, 4, 1, 1, 2);
         if (a.M <= 32) PSW_GC(t256, 32, 256, 4, 1, 1, 2);
         PSW_GC(t256, 64, 256, 4, 1, 1, 2);
     }
-    if (taps == 1) {
-        if (a.M <= 16) PSW_GC(t256, 16, 256, 4, 1, 4, 1);
-        PSW_GC(t64, 64, 64, 4, 1, 4, 1);
-    }
+    // Wide tiles while they fill the chip: 32 channels rather than 64, since
+    // three workgroups then share a CU's LDS and registers and one multiplies
+    // while another stages (fp32, us: 128 -> 128 at 16x16 69 against 82, 5x5 64 ->
+    // 192 104 against 145, 1x1 128 -> 192 35 against 44).
     if (a.M <= 16 && blocks(t256, 16) >= 256) PSW_GC(t256, 16, 256, 4, 1, 2, 2);
-    if (a.M <= 32 && blocks(t256, 32) >= 256) PSW_GC(t256, 32, 256, 4, 1, 2, 2);
-    if (a.M > 32 && blocks(t256, 64) >= 384) PSW_GC(t256, 64, 256, 4, 1, 2, 2);
-    if (a.M > 32 && blocks(t64, 64) >= 192) {
-        if (taps % 3 == 0) PSW_GC(t64, 64, 64, 1, 3, 4, 3);
-        PSW_GC(t64, 64, 64, 1, 4, 4, 4);
-    }
-    if (taps % 3 == 0) PSW_GC(t32, 32, 32, 1, 3, 4, 3);
-    PSW_GC(t32, 32, 32, 1, 4, 4, 4);
+    if (a.M > 16 && blocks(t256, 32) >= 256) PSW_GC(t256, 32, 256, 4, 1, 2, 2);
+    // few output channels, a short reduction: small wide tiles (LeNet's second
+    // layer's backward data 14 against 18)
+    if (a.M <= 32 && a.C * taps <= 1024) PSW_GC(tile(128), 16, 128, 4, 1, 2, 2);
+    // deep reductions over few positions: waves share the depth, two of a 32 x
+    // 64 tile (512 -> 512 at 4x4 126 against 174), or with fewer of those, four
+    // of a 32 x 32 tile (at 2x2 89 against 115)
+    const Tiling t64 = tile(64);
+    if (blocks(t64, 32) >= 256) PSW_GC(t64, 32, 64, 2, 2, 4, 2);
+    PSW_GC(tile(32), 32, 32, 1, 4, 4, 4);
 #undef PSW_GC
     return hipErrorNotSupported;
 }
