@@ -221,34 +221,69 @@ __global__ __launch_bounds__(256) void igemm_kernel(IgArgs a)
         }
 }
 
-// dw[i] = sum_z part[z][i] in a fixed order (deterministic): a block owns 16
-// consecutive outputs; its 16 lane groups sum the splits z = zl (mod 16) in
-// increasing z, then the 16 partial sums are added in order zl = 0..15.
+// dw[i] = sum_z part[z][i] in a fixed order (deterministic): the splits z =
+// zl (mod 16) in increasing z for each of 16 classes, then the class sums in
+// order.  G = 16: a block owns 16 V outputs, a thread one class of V of them.
+// G = 1, up to 16 splits (the same sums, a class has one split): a thread all
+// splits of V outputs; with a class per thread, 14 of 16 threads had nothing to
+// do for two splits (512 x 512 x 9: 42 us), and with V = 1 a block read half of
+// each 128-byte line.
+template <int V, int G>
 __global__ __launch_bounds__(256) void reduce_splits(const float* part, int splits, int64_t count, float* out)
 {
-    __shared__ float sh[16][17];
-    const int o = threadIdx.x & 15, zl = threadIdx.x >> 4;
-    const int64_t i = (int64_t)blockIdx.x * 16 + o;
-    float acc = 0.f;
+    typedef float fv __attribute__((ext_vector_type(V)));
+    constexpr int O = 256 / G;  // threads along the outputs
+    __shared__ float sh[G][O * V + 1];
+    const int o = threadIdx.x % O, zl = threadIdx.x / O;
+    const int64_t i = ((int64_t)blockIdx.x * O + o) * V;
+    fv acc = 0.f;
     if (i < count) {
         // eight independent loads in flight per batch, added in increasing z
         int z = zl;
-        for (; z + 7 * 16 < splits; z += 8 * 16) {
-            float v[8];
+        for (; z + 7 * G < splits; z += 8 * G) {
+            fv v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(z + u * 16) * count + i];
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const fv*>(part + (int64_t)(z + u * G) * count + i);
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc += v[u];
         }
-        for (; z < splits; z += 16) acc += part[(int64_t)z * count + i];
+        for (; z < splits; z += G) acc += *reinterpret_cast<const fv*>(part + (int64_t)z * count + i);
     }
-    sh[zl][o] = acc;
+    if constexpr (G == 1) {
+        if (i < count) *reinterpret_cast<fv*>(out + i) = acc;
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) sh[zl][o * V + e] = acc[e];
     __syncthreads();
-    if (zl == 0 && i < count) {
+    const int64_t j = (int64_t)blockIdx.x * (O * V) + threadIdx.x;
+    if (threadIdx.x < O * V && j < count) {
         float t = 0.f;
-        for (int k = 0; k < 16; ++k) t += sh[k][o];
-        out[i] = t;
+        for (int k = 0; k < G; ++k) t += sh[k][threadIdx.x];
+        out[j] = t;
     }
+}
+
+hipError_t launch_reduce(const float* part, int splits, int64_t count, float* out, hipStream_t st)
+{
+    const Work wk{(double)splits * count, kF * (splits + 1.0) * count};
+    const bool vec = count % 4 == 0 && (uintptr_t)part % 16 == 0 && (uintptr_t)out % 16 == 0;
+    auto blocks = [&](int per) { return dim3((unsigned)((count + per - 1) / per)); };
+    if (splits <= 16) {
+        if (vec)
+            PSW_LAUNCH(kname("reduce_splits", 4, 1), wk, (reduce_splits<4, 1>), blocks(1024), dim3(256), 0, st, part, splits,
+                       count, out);
+        else
+            PSW_LAUNCH(kname("reduce_splits", 1, 1), wk, (reduce_splits<1, 1>), blocks(256), dim3(256), 0, st, part, splits,
+                       count, out);
+    } else if (vec) {
+        PSW_LAUNCH(kname("reduce_splits", 4, 16), wk, (reduce_splits<4, 16>), blocks(64), dim3(256), 0, st, part, splits,
+                   count, out);
+    } else {
+        PSW_LAUNCH(kname("reduce_splits", 1, 16), wk, (reduce_splits<1, 16>), blocks(16), dim3(256), 0, st, part, splits,
+                   count, out);
+    }
+    return hipGetLastError();
 }
 
 template <int PASS, bool BF16>
@@ -450,9 +485,7 @@ hipError_t conv_bwd_weight(const ConvShape& cs, const float* x, const float* dy,
         hipError_t e = conv3x3_wgrad(cs.n, cs.c, cs.h, cs.w, cs.k, cs.stride, x, dy, (float*)ws, st, bf16);
         if (e != hipErrorNotSupported) {  // otherwise (misaligned operands) fall through to the implicit GEMM
             if (e != hipSuccess) return e;
-            PSW_LAUNCH(kname("reduce_splits"), (Work{(double)zd * mn, kF * (zd + 1.0) * mn}), reduce_splits,
-                       dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, (const float*)ws, zd, (int64_t)mn, dw);
-            e = hipGetLastError();
+            e = launch_reduce((const float*)ws, zd, (int64_t)mn, dw, st);
             if (e != hipSuccess || !db) return e;
             const size_t zmax = conv_bwd_weight_ws_bytes(cs, bf16) - channel_sum_ws_bytes(cs.n, cs.k, cs.p * cs.q);
             char* rest = (char*)ws + zmax;
@@ -474,9 +507,7 @@ hipError_t conv_bwd_weight(const ConvShape& cs, const float* x, const float* dy,
         e = bf16 ? launch<BWD_WEIGHT, true>(a, zz, st) : launch<BWD_WEIGHT, false>(a, zz, st);
     }
     if (e != hipSuccess) return e;
-    PSW_LAUNCH(kname("reduce_splits"), (Work{(double)zz * mn, kF * (zz + 1.0) * mn}), reduce_splits,
-               dim3((unsigned)((mn + 15) / 16)), dim3(256), 0, st, (const float*)ws, zz, (int64_t)mn, dw);
-    e = hipGetLastError();
+    e = launch_reduce((const float*)ws, zz, (int64_t)mn, dw, st);
     if (e != hipSuccess || !db) return e;
     const size_t zmax = conv_bwd_weight_ws_bytes(cs, bf16) - channel_sum_ws_bytes(cs.n, cs.k, cs.p * cs.q);
     char* rest = (char*)ws + zmax;
