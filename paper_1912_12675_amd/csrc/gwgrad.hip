@@ -11,7 +11,7 @@
 // unit would need a copy of x per column of the kernel.)
 //
 // A workgroup owns BM output channels and CT blocks of 16 input channels at
-// RG rows of S taps, and walks its share of the chunks: a chunk is 16 units of
+// RG rows of S taps, and walks its share of the chunks: a chunk is PX units of
 // dy (TO image octets x TH rows x TW columns, powers of two chosen on the
 // host) and the pixels of x they meet.  The next chunk is loaded into
 // registers while the matrix cores work on this one.  A matrix step takes
@@ -30,8 +30,6 @@
 namespace psw {
 namespace {
 
-constexpr int kPx = 16;  // units of dy per chunk
-
 struct GwArgs {
     const float* x;   // [n][C][H][W]
     const float* dy;  // [n][K][P][Q]
@@ -44,12 +42,12 @@ struct GwArgs {
     int by_xcd;       // parts are dealt to the XCDs in turn
 };
 
-template <int NS, int BM, int WM, int CT, int RG, int S>
+template <int NS, int BM, int WM, int CT, int RG, int S, int PX>
 __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
 {
     constexpr int NT = 256, WK = 4 / WM, MT = BM / WM / 16;
     constexpr int TAPS = CT * RG * S;
-    constexpr int DI = BM * kPx, DV = DI / NT;  // units of dy, per thread
+    constexpr int DI = BM * PX, DV = DI / NT;  // units of dy, per thread
     constexpr int XV = 3;                       // units of x per thread and staging pass
     static_assert(DI % NT == 0, "units");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -70,11 +68,11 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
     const int r0 = combo / (a.kblocks * a.cblocks) * RG;
     const int ch_begin = zi * a.per, ch_end = min(ch_begin + a.per, a.chunks);
 
-    const int TW = 1 << a.lw, TH = 1 << a.lh, TO = kPx >> (a.lw + a.lh);
+    const int TW = 1 << a.lw, TH = 1 << a.lh, TO = PX >> (a.lw + a.lh);
     const int HC = (TW - 1) * a.st + S, HR = (TH - 1) * a.st + RG;
     const int XP = TO * HR * HC, XROW = XP | 1;  // units of one channel of x; odd row
     const int XI = 16 * CT * XP;
-    sp_v8b* const Ds = reinterpret_cast<sp_v8b*>(smem);  // [NS][BM][16], unit u of row m at u ^ (m & 15)
+    sp_v8b* const Ds = reinterpret_cast<sp_v8b*>(smem);  // [NS][BM][PX], unit u of row m at u ^ (m % PX)
     sp_v8b* const Xs = Ds + NS * DI;                     // [NS][16 CT][XROW]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -116,7 +114,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
         const bool whole = (oct + TO) * 8 <= a.n;
 #pragma unroll
         for (int v = 0; v < DV; ++v) {
-            const int idx = tid + v * NT, m = idx / kPx, u = idx % kPx;
+            const int idx = tid + v * NT, m = idx / PX, u = idx % PX;
             const int q = q0 + (u & (TW - 1)), p = p0 + ((u >> a.lw) & (TH - 1)), img = (oct + (u >> (a.lw + a.lh))) * 8;
             const bool in = k0 + m < a.K && p < a.P && q < a.Q && img < a.n;
             load_unit(dyb, in ? ((img * a.K + k0 + m) * PQ + p * a.Q + q) * 4 : kOutside, img, a.K * PQ * 4, whole,
@@ -135,8 +133,8 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
     auto store_chunk = [&](int ch) {
 #pragma unroll
         for (int v = 0; v < DV; ++v) {
-            const int idx = tid + v * NT, m = idx / kPx, u = idx % kPx;
-            put(Ds + m * kPx + (u ^ (m & 15)), DI, dr[v]);
+            const int idx = tid + v * NT, m = idx / PX, u = idx % PX;
+            put(Ds + m * PX + (u ^ (m & (PX - 1))), DI, dr[v]);
         }
 #pragma unroll
         for (int v = 0; v < XV; ++v) {
@@ -168,7 +166,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
         __syncthreads();
         if (ch + 1 < ch_end) load_chunk(ch + 1);
 #pragma unroll
-        for (int q = 0; q < kPx / 4 / WK; ++q) {
+        for (int q = 0; q < PX / 4 / WK; ++q) {
             const int u = (q * WK + wk) * 4 + g;  // this lane group's unit
             const int tw = u & (TW - 1), th = (u >> a.lw) & (TH - 1), to = u >> (a.lw + a.lh);
             const sp_v8b* xp = Xs + j * XROW + (to * HR + th * a.st) * HC + tw * a.st;
@@ -177,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
-                    av[mt][s] = Ds[s * DI + ((wm * MT + mt) * 16 + j) * kPx + (u ^ j)];
+                    av[mt][s] = Ds[s * DI + ((wm * MT + mt) * 16 + j) * PX + (u ^ (j & (PX - 1)))];
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -257,7 +255,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
                 for (int ch = ch_begin; ch < ch_end && v == v; ++ch) {
                     int oct, p0, q0;
                     chunk_at(ch, &oct, &p0, &q0);
-                    for (int u = 0; u < kPx; ++u) {
+                    for (int u = 0; u < PX; ++u) {
                         const int qq = q0 + (u & (TW - 1)), pp = p0 + ((u >> a.lw) & (TH - 1));
                         const int ih = pp * a.st + r - a.pad, iw = qq * a.st + s - a.pad;
                         const bool in = ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
@@ -278,26 +276,27 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
 
 constexpr size_t kLdsMax = 160 * 1024;
 
-template <int NS, int BM, int WM, int CT, int RG, int S>
+template <int NS, int BM, int WM, int CT, int RG, int S, int PX>
 size_t gw_lds(const GwArgs& a)
 {
-    const int TW = 1 << a.lw, TH = 1 << a.lh, TO = kPx >> (a.lw + a.lh);
+    const int TW = 1 << a.lw, TH = 1 << a.lh, TO = PX >> (a.lw + a.lh);
     const size_t xp = (size_t)TO * ((TH - 1) * a.st + RG) * ((TW - 1) * a.st + S);
-    const size_t main = (size_t)NS * 16 * (BM * kPx + 16 * CT * (xp | 1));
+    const size_t main = (size_t)NS * 16 * (BM * PX + 16 * CT * (xp | 1));
     const size_t red = (size_t)(4 / WM - 1) * BM * 64;  // (WK-1) waves x MT tiles x 256 floats, per row of waves
     return main > red ? main : red;
 }
 
-template <int NS, int BM, int WM, int CT, int RG, int S>
+template <int NS, int BM, int WM, int CT, int RG, int S, int PX>
 hipError_t gw_launch(GwArgs a, int max_splits, int* splits, bool dry, const Work& wk, hipStream_t st)
 {
-    // chunk of 16 units: fewest chunks; then the least of x, rows of a
+    constexpr int LP = PX == 16 ? 4 : 3;
+    // chunk of PX units: fewest chunks; then the least of x, rows of a
     // 32-byte sector where the plane has them
     int64_t best = 0;
     int best_x = 0;
-    for (int lw = 0; lw <= 4; ++lw)
-        for (int lh = 0; lw + lh <= 4; ++lh) {
-            const int tw = 1 << lw, th = 1 << lh, to = kPx >> (lw + lh);
+    for (int lw = 0; lw <= LP; ++lw)
+        for (int lh = 0; lw + lh <= LP; ++lh) {
+            const int tw = 1 << lw, th = 1 << lh, to = PX >> (lw + lh);
             if (((tw >> 1) >= a.Q && lw) || ((th >> 1) >= a.P && lh)) continue;
             const int64_t ch = (int64_t)((a.Q + tw - 1) / tw) * ((a.P + th - 1) / th) * (((a.n + 7) / 8 + to - 1) / to);
             const int xp = to * ((th - 1) * a.st + RG) * ((tw - 1) * a.st + S) + (tw < 8 && a.Q >= 8 ? 8 : 0);
@@ -311,7 +310,7 @@ hipError_t gw_launch(GwArgs a, int max_splits, int* splits, bool dry, const Work
             }
         }
     if (best > INT32_MAX) return hipErrorNotSupported;
-    const size_t lds = gw_lds<NS, BM, WM, CT, RG, S>(a);
+    const size_t lds = gw_lds<NS, BM, WM, CT, RG, S, PX>(a);
     if (lds > kLdsMax) return hipErrorNotSupported;
     a.chunks = (int)best;
     a.kblocks = (a.K + BM - 1) / BM;
@@ -331,27 +330,34 @@ hipError_t gw_launch(GwArgs a, int max_splits, int* splits, bool dry, const Work
     const int64_t blocks = (a.by_xcd ? (a.z + 7) / 8 * 8 : a.z) * combos;
     if (blocks > INT32_MAX) return hipErrorNotSupported;
     if (dry) return hipSuccess;
-    PSW_LAUNCH(kname("conv_split_wgrad", NS, BM, WM, CT, RG, S), wk, (conv_split_wgrad<NS, BM, WM, CT, RG, S>),
+    PSW_LAUNCH(kname("conv_split_wgrad", NS, BM, WM, CT, RG, S, PX), wk, (conv_split_wgrad<NS, BM, WM, CT, RG, S, PX>),
                dim3((unsigned)blocks), dim3(256), lds, st, a);
     return hipGetLastError();
 }
 
-template <int NS, int BM, int WM>
+template <int NS, int BM, int WM, int PX>
 hipError_t gw_taps(const GwArgs& a, int ms, int* sp, bool dry, const Work& wk, hipStream_t st)
 {
-    if (a.R == 3 && a.S == 3) return gw_launch<NS, BM, WM, 1, 3, 3>(a, ms, sp, dry, wk, st);
-    if (a.S == 5) return gw_launch<NS, BM, WM, 1, 1, 5>(a, ms, sp, dry, wk, st);
-    if (a.S == 3) return gw_launch<NS, BM, WM, 1, 1, 3>(a, ms, sp, dry, wk, st);
-    if (a.S == 1) return gw_launch<NS, BM, WM, 4, 1, 1>(a, ms, sp, dry, wk, st);
+    if (a.R == 3 && a.S == 3) return gw_launch<NS, BM, WM, 1, 3, 3, PX>(a, ms, sp, dry, wk, st);
+    if (a.S == 5) return gw_launch<NS, BM, WM, 1, 1, 5, PX>(a, ms, sp, dry, wk, st);
+    if (a.S == 3) return gw_launch<NS, BM, WM, 1, 1, 3, PX>(a, ms, sp, dry, wk, st);
+    if (a.S == 1) return gw_launch<NS, BM, WM, 4, 1, 1, PX>(a, ms, sp, dry, wk, st);
     return hipErrorNotSupported;
 }
 
 template <int NS>
 hipError_t gw_rows(const GwArgs& a, int ms, int* sp, bool dry, const Work& wk, hipStream_t st)
 {
-    if (a.K <= 16) return gw_taps<NS, 16, 1>(a, ms, sp, dry, wk, st);
-    if (a.K <= 32) return gw_taps<NS, 32, 1>(a, ms, sp, dry, wk, st);
-    return gw_taps<NS, 64, 2>(a, ms, sp, dry, wk, st);
+    if (a.K <= 16) return gw_taps<NS, 16, 1, 16>(a, ms, sp, dry, wk, st);
+    // half-size tiles and chunks where 64 x 16 ones would be fewer than two per
+    // CU (37 images, 24 -> 56 at 29x23, stride 2: 26 -> 16 us)
+    const int64_t units = (int64_t)((a.n + 7) / 8) * a.P * a.Q / 16 * ((a.K + 63) / 64) * ((a.C + 15) / 16);
+    if (units < 512 && a.S > 1) return gw_taps<NS, 32, 2, 8>(a, ms, sp, dry, wk, st);
+    if (a.K <= 32) return gw_taps<NS, 32, 1, 16>(a, ms, sp, dry, wk, st);
+    // a 1x1 chunk has one tap to multiply per loaded value: smaller chunks, three
+    // workgroups a CU (128 -> 192 at 16x16 b128 52 -> 34 us)
+    if (a.S == 1) return gw_launch<NS, 64, 2, 4, 1, 1, 8>(a, ms, sp, dry, wk, st);
+    return gw_taps<NS, 64, 2, 16>(a, ms, sp, dry, wk, st);
 }
 
 }  // namespace
