@@ -1,0 +1,71 @@
+"""Nets of one device share the library's weight and forward streams: nets
+issued in turn from two threads on streams of their own, and a graph captured
+beside them, give what they give alone."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+T = 6
+
+
+def make(P, batch, seed):
+    from paper_1912_12675_amd import synth
+    wl = synth.resnet20_workload(batch=batch, seed=seed)
+    net = P.Net(wl.ops, batch, wl.in_shape, wl.stage_end, [4, 3, 2, 1])
+    net.load_params(synth.init_params(wl))
+    xs, ys = synth.batches(wl, T, batch)
+    return net, wl, torch.from_numpy(xs).cuda(), torch.from_numpy(ys).cuda()
+
+
+def run(P, made, stream, steps_only=False):
+    net, wl, xs, ys = made
+    st = np.tile(np.array([3, 2, 1, 0], dtype=np.int32), (T, 1))
+    losses = torch.zeros(T, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        if steps_only:
+            for t in range(T):
+                net.step(t, st[t], wl.lr, xs[t], ys[t])
+        else:
+            net.pipeline_run(0, st, wl.lr, xs, ys, losses)
+    stream.synchronize()
+    return net.params(T)
+
+
+def test_two_threads_share_the_streams():
+    from paper_1912_12675_amd import psw as P
+    print("streams: two threads", flush=True)
+    alone = [run(P, make(P, b, s), torch.cuda.Stream()) for b, s in ((8, 1), (12, 2))]
+    made = [make(P, 8, 1), make(P, 12, 2)]
+    got, errors = [None, None], []
+
+    def work(i):
+        try:
+            got[i] = run(P, made[i], torch.cuda.Stream(), steps_only=i == 1)
+        except Exception as e:  # reported below: a thread's exception does not fail a test
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for a, b in zip(alone, got):
+        assert torch.equal(a, b)
+
+
+def test_streams_outlive_one_net():
+    from paper_1912_12675_amd import psw as P
+    print("streams: a net destroyed beside another", flush=True)
+    ref = run(P, make(P, 8, 1), torch.cuda.Stream())
+    first, second = make(P, 12, 2), make(P, 8, 1)
+    run(P, first, torch.cuda.Stream())
+    del first
+    assert torch.equal(run(P, second, torch.cuda.Stream()), ref)
+    del second
+    assert torch.equal(run(P, make(P, 8, 1), torch.cuda.Stream()), ref)  # the streams are made again
