@@ -3,7 +3,8 @@
     python -m paper_1912_12675_amd.build
 
 Compiles every source under csrc/ to an object in _build/ (in parallel) and
-links paper_1912_12675_amd/libpsw.so.  Always rebuilds.
+links paper_1912_12675_amd/libpsw.so; csrc/fastcall.cpp, the CPython module
+that calls it, becomes paper_1912_12675_amd/_fastcall.so.  Always rebuilds.
 """
 from __future__ import annotations
 
@@ -15,6 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(os.path.dirname(HERE), "_build")
 LIB = os.path.join(HERE, "libpsw.so")
+FAST = os.path.join(HERE, "_fastcall.so")
 SOURCES = ["conv.hip", "gconv.hip", "gwgrad.hip", "direct.hip", "wgrad.hip", "fc.hip", "bn.hip", "ops.hip", "api.hip"]
 ARCH = "gfx950"
 
@@ -24,6 +26,21 @@ FLAGS = [
     # keep the compiler from emitting packed-fp32 VALU instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+
+
+def fastcall_command(out: str) -> list:
+    import sysconfig
+
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    inc = [os.path.join(root, "include"), os.path.join(root, "include/torch/csrc/api/include"),
+           sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")]
+    lib = os.path.join(root, "lib")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *[a for i in inc for a in ("-isystem", i)], os.path.join(CSRC, "fastcall.cpp"), "-o", out, f"-L{lib}",
+            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{lib}"]
 
 
 def build(verbose: bool = False) -> str:
@@ -37,6 +54,10 @@ def build(verbose: bool = False) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
+    cmd = fastcall_command(FAST + ".tmp")
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs.append(("fastcall.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
     failed = []
     for src, p in procs:
         out, _ = p.communicate()
@@ -48,10 +69,11 @@ def build(verbose: bool = False) -> str:
         if p.returncode != 0:
             failed.append(src)
     if failed:
-        raise RuntimeError(f"hipcc failed for {failed}")
+        raise RuntimeError(f"the compiler failed for {failed}")
     tmp = LIB + ".tmp"
     subprocess.check_call([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
+    os.replace(FAST + ".tmp", FAST)
     return LIB
 
 

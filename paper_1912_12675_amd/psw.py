@@ -19,6 +19,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpsw.so")
+FAST_PATH = os.path.join(os.path.dirname(LIB_PATH), "_fastcall.so")
 
 PSW_OK = 0
 PSW_ERR = {-1: "NULL", -2: "SHAPE", -3: "UNSUPPORTED", -4: "STALENESS", -5: "STEP_ORDER", -6: "WORKSPACE",
@@ -110,6 +111,7 @@ PROF_KINDS = ["conv_fwd", "conv_bwd_data", "conv_bwd_weight", "bn_fwd", "bn_bwd"
               "other"]
 
 _lib = None
+_fast = None  # the module _fastcall, its functions bound to libpsw's
 
 
 def lib():
@@ -125,6 +127,24 @@ def lib():
             fn.argtypes = args
         _lib = L
     return _lib
+
+
+def _fastcall():
+    """The native module that makes the per-layer calls (raises if it has not been built).
+
+    Its functions return the status, or None for arguments they leave to the
+    calls below: integer addresses, stream objects, anything to be refused.
+    """
+    global _fast
+    if _fast is None:
+        L = lib()
+        if not os.path.exists(FAST_PATH):
+            raise RuntimeError(f"{FAST_PATH} is missing: build it with `python -m paper_1912_12675_amd.build`")
+        from . import _fastcall as m
+        for name in SIGNATURES:
+            m.bind(name, ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
+        _fast = m
+    return _fast
 
 
 def _check(rc: int):
@@ -162,6 +182,9 @@ def _prec(bf16):
 
 # ------------------------------------------------------------ per layer ----
 def psw_conv_fwd(x, w, y, stride=1, pad=0, bias=None, relu=False, bf16=False, stream=None):
+    rc = (_fast or _fastcall()).conv_fwd(x, w, y, stride, pad, bias, relu, bf16, stream)
+    if rc is not None:
+        return _check(rc)
     n, c, h, wd = x.shape
     k, _, r, s = w.shape
     _check(lib().psw_conv_fwd(n, c, h, wd, k, r, s, stride, pad, _ptr(x), _ptr(w), _ptr(bias), int(relu), _ptr(y),
@@ -169,6 +192,9 @@ def psw_conv_fwd(x, w, y, stride=1, pad=0, bias=None, relu=False, bf16=False, st
 
 
 def psw_conv_bwd_data(x_shape, w, dy, dx, stride=1, pad=0, accumulate=False, bf16=False, stream=None):
+    rc = (_fast or _fastcall()).conv_bwd_data(x_shape, w, dy, dx, stride, pad, accumulate, bf16, stream)
+    if rc is not None:
+        return _check(rc)
     n, c, h, wd = x_shape
     k, _, r, s = w.shape
     _check(lib().psw_conv_bwd_data(n, c, h, wd, k, r, s, stride, pad, _ptr(w), _ptr(dy), _ptr(dx), int(accumulate),
@@ -182,6 +208,9 @@ def psw_conv_bwd_weight_ws_bytes(x_shape, w_shape, stride=1, pad=0, bf16=False):
 
 
 def psw_conv_bwd_weight(x, dy, dw, stride=1, pad=0, dbias=None, bf16=False, ws=None, stream=None):
+    rc = (_fast or _fastcall()).conv_bwd_weight(x, dy, dw, stride, pad, dbias, bf16, ws, stream)
+    if rc is not None:
+        return _check(rc)
     n, c, h, wd = x.shape
     k, _, r, s = dw.shape
     if ws is None:
@@ -209,6 +238,10 @@ def _ws(nbytes, device):
 
 def psw_bn_relu_fwd(y, gamma, beta, z, save_mean, save_invstd, res=None, relu=False, eps=1e-5, momentum=0.1,
                     run_mean=None, run_var=None, ws=None, stream=None):
+    rc = (_fast or _fastcall()).bn_relu_fwd(y, gamma, beta, z, save_mean, save_invstd, res, relu, eps, momentum,
+                                          run_mean, run_var, ws, stream)
+    if rc is not None:
+        return _check(rc)
     n, c, h, w = y.shape
     rc, rh, rw = (0, 0, 0) if res is None else tuple(res.shape[1:])
     ws = _ws(psw_bn_ws_bytes(y.shape), y.device) if ws is None else ws
@@ -219,6 +252,10 @@ def psw_bn_relu_fwd(y, gamma, beta, z, save_mean, save_invstd, res=None, relu=Fa
 
 def psw_bn_relu_bwd(dz, z, y, gamma, save_mean, save_invstd, dy, dgamma, dbeta, dres=None, relu=False,
                     res_accumulate=False, ws=None, stream=None):
+    rc = (_fast or _fastcall()).bn_relu_bwd(dz, z, y, gamma, save_mean, save_invstd, dy, dgamma, dbeta, dres, relu,
+                                          res_accumulate, ws, stream)
+    if rc is not None:
+        return _check(rc)
     n, c, h, w = y.shape
     rc, rh, rw = (0, 0, 0) if dres is None else tuple(dres.shape[1:])
     ws = _ws(psw_bn_ws_bytes(y.shape), y.device) if ws is None else ws
@@ -228,17 +265,26 @@ def psw_bn_relu_bwd(dz, z, y, gamma, save_mean, save_invstd, dy, dgamma, dbeta, 
 
 
 def psw_pool_fwd(kind, x, y, k=2, stride=2, argmax=None, stream=None):
+    rc = (_fast or _fastcall()).pool_fwd(kind, x, y, k, stride, argmax, stream)
+    if rc is not None:
+        return _check(rc)
     n, c, h, w = x.shape
     _check(lib().psw_pool_fwd(kind, n, c, h, w, k, stride, _ptr(x), _ptr(y), _ptr(argmax), _stream(stream)))
 
 
 def psw_pool_bwd(kind, x_shape, dy, dx, k=2, stride=2, argmax=None, accumulate=False, stream=None):
+    rc = (_fast or _fastcall()).pool_bwd(kind, x_shape, dy, dx, k, stride, argmax, accumulate, stream)
+    if rc is not None:
+        return _check(rc)
     n, c, h, w = x_shape
     _check(lib().psw_pool_bwd(kind, n, c, h, w, k, stride, _ptr(dy), _ptr(argmax), _ptr(dx), int(accumulate),
                               _stream(stream)))
 
 
 def psw_fc_fwd(x, w, y, b=None, relu=False, bf16=False, stream=None):
+    rc = (_fast or _fastcall()).fc_fwd(x, w, y, b, relu, bf16, stream)
+    if rc is not None:
+        return _check(rc)
     n, fin = x.shape
     out = w.shape[0]
     _check(lib().psw_fc_fwd(n, fin, out, _ptr(x), _ptr(w), _ptr(b), int(relu), _ptr(y), _prec(bf16),
@@ -250,6 +296,9 @@ def psw_fc_bwd_ws_bytes(n, fin, out):
 
 
 def psw_fc_bwd(x, w, dy, dw, dx=None, db=None, dx_accumulate=False, bf16=False, ws=None, stream=None):
+    rc = (_fast or _fastcall()).fc_bwd(x, w, dy, dw, dx, db, dx_accumulate, bf16, ws, stream)
+    if rc is not None:
+        return _check(rc)
     n, fin = x.shape
     out = w.shape[0]
     ws = _ws(psw_fc_bwd_ws_bytes(n, fin, out), x.device) if ws is None else ws
@@ -258,16 +307,25 @@ def psw_fc_bwd(x, w, dy, dw, dx=None, db=None, dx_accumulate=False, bf16=False, 
 
 
 def psw_relu_mask(z, g, stream=None):
+    rc = (_fast or _fastcall()).relu_mask(z, g, stream)
+    if rc is not None:
+        return _check(rc)
     _check(lib().psw_relu_mask(z.numel(), _ptr(z), _ptr(g), _stream(stream)))
 
 
 def psw_softmax_xent(logits, labels, loss, dlogits, stream=None):
+    rc = (_fast or _fastcall()).softmax_xent(logits, labels, loss, dlogits, stream)
+    if rc is not None:
+        return _check(rc)
     n, classes = logits.shape
     _check(lib().psw_softmax_xent(n, classes, _ptr(logits), _ptr(labels), _ptr(loss), _ptr(dlogits),
                                   _stream(stream)))
 
 
 def psw_sgd_momentum_step(w_in, w_out, v, g, lr, mom=0.9, wd=0.0, nesterov=False, stream=None):
+    rc = (_fast or _fastcall()).sgd(w_in, w_out, v, g, lr, mom, wd, nesterov, stream)
+    if rc is not None:
+        return _check(rc)
     _check(lib().psw_sgd_momentum_step(w_in.numel(), _ptr(w_in), _ptr(w_out), _ptr(v), _ptr(g), lr, mom, wd,
                                        int(nesterov), _stream(stream)))
 
