@@ -7,6 +7,8 @@ Bound: both sides form the same fp32 (or bf16-rounded) products; the GPU adds
 them in fp32, so the error of a sum of L products is at most L 2^-24 of the
 sum of their magnitudes and typically sqrt(L) 2^-24 of their root mean square:
 2e-5 of the largest result covers every L here (at most 12,800)."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -289,3 +291,31 @@ def test_maxpool_edges(P, case, accumulate):
     P.psw_pool_bwd(P.PSW_POOL_MAX, x.shape, dev(dy), dx, k, k, argmax=arg, accumulate=accumulate)
     ref = ref.reshape(x.shape) + base if accumulate else ref.reshape(x.shape)
     assert np.array_equal(dx.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("n,classes", [(1, 1), (3, 2), (1024, 1), (1025, 3), (16, 64), (17, 65), (250, 100), (5, 1000),
+                                       (2100, 33)])
+def test_softmax_xent_lanes(P, n, classes):
+    """Each number of lanes a row can get, a last pass of rows that is part full, classes that are not a
+    multiple of the lanes; a row of which one logit is -inf, and one that has a NaN."""
+    g = torch.Generator().manual_seed(n * classes)
+    z = torch.randn(n, classes, generator=g) * 3
+    if n > 2 and classes > 1:
+        z[1, 0] = -math.inf
+    lab = torch.randint(classes, (n,), generator=g, dtype=torch.int32)
+    if n > 2 and classes > 1:
+        lab[1] = classes - 1
+    loss, dz = torch.empty(1, device="cuda"), torch.empty(n, classes, device="cuda")
+    P.psw_softmax_xent(z.cuda(), lab.cuda(), loss, dz)
+    p = torch.log_softmax(z.double(), 1)
+    want = (p.exp() - torch.nn.functional.one_hot(lab.long(), classes)) / n
+    # z - max and z - lse round at |z| + |lse| < 2 * 16 + 7, the sum of the classes at most `classes` times,
+    # exp and log at a few ulp
+    eps = 2.0 ** -24
+    tol = (2 * (2 * 16 + 7) + classes + 16) * eps
+    assert ((dz.cpu().double() - want).abs() <= tol / n).all()
+    assert abs(float(loss) - float(-p[torch.arange(n), lab.long()].mean())) <= tol
+    if n > 2 and classes > 1:
+        z[2, classes - 1] = math.nan
+        P.psw_softmax_xent(z.cuda(), lab.cuda(), loss, dz)
+        assert dz[2].isnan().all() and not dz[torch.arange(n) != 2].isnan().any() and loss.isnan().all()
