@@ -14,10 +14,10 @@
 // timing.
 //
 // Measured at 128 x 16384 x 4096 against the gemm that staged scalars (us,
-// fp32 / bf16): forward 2,238 -> 285 / 186, dx 655 -> 166, dw 258 -> 134 (268
+// fp32 / bf16): forward 2,238 -> 228 / 184, dx 655 -> 166, dw 258 -> 134 (268
 // MB of weights read, read and written: 40-50 us each at memory's rate, 110 at
-// the fp32 matrix rate).  Forward is bound by the L2's delivery of x to every
-// block of columns, dx and dw by their stages' phases following one another.
+// the fp32 matrix rate).  Forward is bound by the delivery of x to every block
+// of columns, dx and dw by their stages' phases following one another.
 #include <algorithm>
 
 #include "internal.h"
@@ -261,15 +261,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_split(GsArgs a)
 // Forward of a batch of few rows (both operands contiguous along k).  A
 // workgroup owns 16 MT rows by 16 columns, and its WK waves take the steps of
 // 32 k in turn, each for the whole tile: no operand is used by two waves, so
-// none goes through LDS.  A lane loads two pieces of 16 bytes along k of its
-// row, 64 bytes apart, so that the four lane groups read 64 bytes in a row; the
-// order of k within a step is free as long as A and B agree, so these are a
-// bf16 operand as they stand, and eight operands of the fp32 instruction (step
-// e takes element e of every lane group).  The weights are read once and the next step's operands are in
-// flight while the matrix cores work.  fp32 uses the fp32 instructions: a
-// split costs the vector units 208 cycles an operand, eight of nine operands
-// are the batch's, and each would serve one block of columns (the tiled kernel
-// takes 370 us at 128 x 16384 x 4096, this one 285).
+// there are no barriers.  Four neighbouring lanes load 64 bytes of a row, and
+// the wave's own LDS turns 16 rows of 4 pieces into the operands' order: loads
+// in that order (a row's four pieces 16 lanes apart) took a cycle of address
+// processing a lane, and bound the kernel (us before, now: 128 x 16384 x 4096
+// 285, 228; 128 x 4096 x 4096 72, 53; 16 x 16384 x 4096 62, 50; 128 x 4096 x
+// 10 14.4, 8.6).  The order of k within a step is free as long as A and B
+// agree, so two pieces 64 bytes apart are a bf16 operand as they stand, and
+// eight operands of the fp32 instruction.  The weights are read once and the
+// next step's operands are in flight while the matrix cores work.  fp32 uses
+// the fp32 instructions: a split costs the vector units 208 cycles an operand,
+// eight of nine operands are the batch's, and each would serve one block of
+// columns (the tiled kernel takes 370 us at 128 x 16384 x 4096).
 template <bool BF, int MT, int WK>
 __global__ __launch_bounds__(64 * WK) void gemm_rows(GsArgs a)
 {
@@ -279,69 +282,111 @@ __global__ __launch_bounds__(64 * WK) void gemm_rows(GsArgs a)
     const int n0 = (int)blockIdx.x * 16, m0 = (int)blockIdx.y * 16 * MT;
     const Buffer ab = make_buffer(a.A + (int64_t)m0 * a.lda, (int64_t)(a.M - m0) * a.lda * 4);
     const Buffer bb = make_buffer(a.B + (int64_t)n0 * a.ldb, (int64_t)(a.N - n0) * a.ldb * 4);
+    // lane l loads piece l % 4 of row l / 4 of a block of 16 rows
+    const int lr = lane >> 2, lp = lane & 3;
     int aoff[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-        aoff[mt] = m0 + mt * 16 + j < a.M ? ((mt * 16 + j) * a.lda + g * 4) * 4 : kOutside;
-    const int boff = n0 + j < a.N ? (j * a.ldb + g * 4) * 4 : kOutside;
-    const int steps = (a.K + 31) / 32;
+        aoff[mt] = m0 + mt * 16 + lr < a.M ? ((mt * 16 + lr) * a.lda + lp * 4) * 4 : kOutside;
+    const int boff = n0 + lr < a.N ? (lr * a.ldb + lp * 4) * 4 : kOutside;
+    const int full = a.K / 32;
 
     sp_v4f acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
     typedef float f4 __attribute__((ext_vector_type(4)));
-    struct Ops {
-        f4 a[MT][2], b[2];
+    f4 ar[MT][2], br[2];
+    // Half h (16 k) of whole step ks; past the last step nothing is read.
+    auto load_a = [&](int ks, int h) {
+        const int none = ks < full ? 0 : kOutside, at = ks < full ? ks * 128 + h * 64 : 0;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            ar[mt][h] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(ab, aoff[mt] | none, at, 0));
     };
-    auto load8 = [&](Buffer b, int off, int ks, f4(&r)[2]) {
-        if ((ks + 1) * 32 <= a.K) {
-            r[0] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, off, ks * 128, 0));
-            r[1] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, off + 64, ks * 128, 0));
-        } else {  // the last step's missing k are zero
-            const int left = off >= 0 ? a.K - ks * 32 - g * 4 : 0;
+    auto load_b = [&](int ks) {
+        const int none = ks < full ? 0 : kOutside, at = ks < full ? ks * 128 : 0;
+        br[0] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(bb, boff | none, at, 0));
+        br[1] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(bb, (boff + 64) | none, at, 0));
+    };
+    // The wave's own LDS, 1 KB a block of rows: piece p of row r at unit
+    // 4 r + (p ^ (r >> 2)), so that neither the stores by rows nor the reads
+    // by pieces meet in a bank.  A wave's LDS operations are done in order:
+    // no barrier, the compiler only keeps to that order.
+    f4* const own = reinterpret_cast<f4*>(smem) + wk * MT * 64;
+    const int put = lr * 4 + (lp ^ (lr >> 2)), get = j * 4 + (g ^ (j >> 2));
+    auto fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+    f4 av[MT][2], bv[2];
+    auto swap_b = [&]() {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            own[put] = br[h];
+            fence();
+            bv[h] = own[get];
+            fence();
+        }
+    };
+    auto put_a = [&](int h) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) own[mt * 64 + put] = ar[mt][h];
+        fence();
+    };
+    auto mul = [&](int h) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) av[mt][h] = own[mt * 64 + get];
+        fence();
+        if constexpr (BF) {
+            if (h == 0) return;
+            auto bf8 = [](const f4(&r)[2]) {
+                float t[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) t[e] = r[e / 4][e % 4];
+                sp_v8b p[1];
+                split8<1>(t, p);
+                return p[0];
+            };
+            const sp_v8b b8 = bf8(bv);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b8, bf8(av[mt]), acc[mt], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[h][e], av[mt][h][e], acc[mt], 0, 0, 0);
+        }
+    };
+    load_b(wk);
+    load_a(wk, 0);
+    load_a(wk, 1);
+    for (int ks = wk; ks < full; ks += WK) {
+        swap_b();
+        load_b(ks + WK);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            put_a(h);
+            load_a(ks + WK, h);
+            mul(h);
+        }
+    }
+    if (full * 32 < a.K && full % WK == wk) {  // the last step's missing k are zero
+        auto part = [&](Buffer b, int off, f4(&r)[2]) {
+            const int left = off >= 0 ? a.K - full * 32 - lp * 4 : 0;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = e / 4 * 16 + e % 4;
-                r[e / 4][e % 4] = buffer_load(b, k < left ? off + ks * 128 + k * 4 : kOutside, 0);
+                r[e / 4][e % 4] = buffer_load(b, k < left ? off + full * 128 + k * 4 : kOutside, 0);
             }
+        };
+        part(bb, boff, br);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) part(ab, aoff[mt], ar[mt]);
+        swap_b();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            put_a(h);
+            mul(h);
         }
-    };
-    auto load = [&](int ks, Ops& o) {
-        if (ks >= steps) return;
-        load8(bb, boff, ks, o.b);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) load8(ab, aoff[mt], ks, o.a[mt]);
-    };
-    auto bf8 = [](const f4(&r)[2]) {
-        float t[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) t[e] = r[e / 4][e % 4];
-        sp_v8b p[1];
-        split8<1>(t, p);
-        return p[0];
-    };
-    auto mul = [&](int ks, const Ops& o) {
-        if (ks >= steps) return;
-        if constexpr (BF) {
-            const sp_v8b bv = bf8(o.b);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, bf8(o.a[mt]), acc[mt], 0, 0, 0);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.b[e / 4][e % 4], o.a[mt][e / 4][e % 4], acc[mt], 0, 0, 0);
-        }
-    };
-    Ops o0, o1;
-    load(wk, o0);
-    for (int ks = wk; ks < steps; ks += 2 * WK) {
-        load(ks + WK, o1);
-        mul(ks, o0);
-        load(ks + 2 * WK, o0);
-        mul(ks + WK, o1);
     }
 
     // the waves' sums, in wave order; wave w finishes row blocks w, w + WK, ...
@@ -444,9 +489,7 @@ template <int NS, bool AK, bool BK>
 hipError_t gs_pick(const GsArgs& a, const Work& wk, hipStream_t st)
 {
     auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    // bf16 forward of more than 64 rows to many columns: x is rounded, not split, again per
-    // column block, so the LDS tile is ahead of gemm_rows (16384 -> 4096: 186
-    // against 258)
+    // bf16 forward of more than 64 rows whose x is larger than the L2 (see gemm())
     if constexpr (AK && BK)
         if (a.M > 64 && a.M <= 256) return gs_launch<NS, 128, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
     if (blocks(128, 128) >= 512) return gs_launch<NS, 128, 128, 2, 2, 1, 1, AK, BK>(a, wk, st);
@@ -478,6 +521,8 @@ hipError_t rows_pick(const GsArgs& a, const Work& wk, hipStream_t st)
     return a.K > 512 ? rows_launch<BF, 1, 16>(a, wk, st) : rows_launch<BF, 1, 4>(a, wk, st);
 }
 
+constexpr int64_t kRowsL2 = 4 << 20;  // bytes
+
 template <bool AK, bool BK>
 hipError_t gemm(GsArgs a, int bf16, hipStream_t st)
 {
@@ -492,9 +537,12 @@ hipError_t gemm(GsArgs a, int bf16, hipStream_t st)
         return hipGetLastError();
     }
     // up to 256 rows the weights' traffic and the depth of k decide, not the
-    // matrix rate: the kernel without LDS
+    // matrix rate: gemm_rows.  bf16 with an x past an XCD's 4 MB of L2 (fp32,
+    // re-read by every block of columns) takes the LDS tile of 128 rows
+    // (16384 -> 4096, 128 rows: 184 against 192; 9216, 100 rows: 104 and 78)
     if constexpr (AK && BK)
-        if (a.M <= (bf16 && a.N >= 1024 ? 64 : 256) && !a.accumulate) return bf16 ? rows_pick<true>(a, wk, st) : rows_pick<false>(a, wk, st);
+        if (a.M <= (bf16 && a.N >= 1024 && (int64_t)a.M * a.K * 4 > kRowsL2 ? 64 : 256) && !a.accumulate)
+            return bf16 ? rows_pick<true>(a, wk, st) : rows_pick<false>(a, wk, st);
     return bf16 ? gs_pick<1, AK, BK>(a, wk, st) : gs_pick<3, AK, BK>(a, wk, st);
 }
 

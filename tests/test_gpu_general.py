@@ -141,6 +141,10 @@ FC = [
     (16, 120, 84),
     (17, 33, 129),
     (33, 31, 4096),      # outputs by the row, a reduction shorter than a step
+    (129, 70, 2049),     # 128, 64 and 32 rows a block, each with a part block, column and step
+    (65, 99, 4100),
+    (40, 97, 4098),
+    (101, 10500, 1030),  # an x past 4 MB
     (1, 4097, 70),       # deep reductions, one k past a stage
     (20, 2047, 66),
     (130, 130, 66),
