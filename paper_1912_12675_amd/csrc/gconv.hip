@@ -12,7 +12,7 @@
 // product with an inserted zero is formed (blockIdx.z is the class).
 //
 // A workgroup owns BM output channels of BP grid positions (TI images x TH
-// rows x TW columns, powers of two chosen on the host for the least padding).
+// rows x TW columns, powers of two chosen on the host, see pick_tile).
 // Reduction channels come in chunks of 8 OC.  A chunk's input tile with its
 // halo is loaded once, split once and kept in LDS as 16-byte units [octet of
 // channels][pixel], so that a tap is only another pixel offset: nothing is
@@ -399,9 +399,14 @@ struct Tiling {
     int hp;  // staged pixels
 };
 
-// tile of bp positions over n planes of gh x gw: fewest tiles, then the
-// smallest halo, where rows shorter than 16 positions (64 bytes a load and
-// store instruction row) count as more
+// Tile of bp positions over n planes of gh x gw, for the least of all tiles'
+// products (bp positions each, padding included) and staging (the halo's
+// elements; rows shorter than 16 positions, 64 bytes a load and store
+// instruction row, count as more).  The fewest tiles alone gave 14x14 planes
+// tiles of 2x2 positions in 64 images, a halo four times the positions (fp32,
+// 128 images, us before and now: 256 -> 256 at 14x14 693, 216; at 7x7 395, 100;
+// 64 -> 64 at 28x28 114, 67; 5x5 64 -> 96 at 27x27 962, 194; 1x1 96 -> 200 at 14x14
+// 184, 46; a staged element weighing a quarter to twice a position: within 5%).
 Tiling pick_tile(int n, int gh, int gw, int bp, int is, int rs, int ss)
 {
     Tiling best{};
@@ -414,8 +419,9 @@ Tiling pick_tile(int n, int gh, int gw, int bp, int is, int rs, int ss)
             Tiling t{lw, lh, (gh + th - 1) / th, (gw + tw - 1) / tw, 0, 0};
             t.tiles = (int64_t)t.tiles_h * t.tiles_w * ((n + ti - 1) / ti);
             t.hp = ti * ((th - 1) * is + rs) * ((tw - 1) * is + ss);
-            const double cost = t.hp * (tw >= 16 || tw >= gw ? 1.0 : tw >= 8 ? 1.1 : 1.4);
-            if (!best.tiles || t.tiles < best.tiles || (t.tiles == best.tiles && cost < best_cost)) {
+            const double stage = t.hp * (tw >= 16 || tw >= gw ? 1.0 : tw >= 8 ? 1.1 : 1.4);
+            const double cost = (double)t.tiles * (bp + stage);
+            if (!best.tiles || cost < best_cost) {
                 best = t;
                 best_cost = cost;
             }

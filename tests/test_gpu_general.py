@@ -47,6 +47,8 @@ CONV = [
     (2, 31, 16, 17, 63, 3, 3, 1, 1),
     (130, 33, 4, 4, 70, 3, 3, 1, 1),     # several images per tile, one past a 32-channel chunk
     (129, 64, 2, 2, 40, 3, 3, 1, 1),
+    (130, 24, 14, 14, 33, 3, 3, 1, 1),   # planes a little smaller than a tile, and than a part of one
+    (130, 40, 7, 7, 70, 3, 3, 1, 1),
     (40, 40, 1, 1, 48, 3, 3, 1, 1),
     (2, 24, 29, 23, 56, 3, 3, 2, 1),     # stride 2: four classes backward, odd plane
     (2, 20, 13, 14, 24, 5, 5, 3, 2),     # stride 3: nine classes
