@@ -94,7 +94,7 @@ void* g_scratch_ptr[kMaxDevices];  // device address of `scratch` per device, nu
 // ms instead of 7.4.  So all nets of a device share one pair.  A stream is in
 // issue order and every wait refers to an event recorded before it, so nets
 // issued from several threads only ever wait for work issued earlier.  Graph
-// captures use streams of their own.
+// captures, the library's and a caller's, use streams of their own.
 struct SharedStream {
     hipStream_t stream = nullptr;
     int users = 0;
@@ -443,6 +443,8 @@ struct psw_net {
     // when a conv's output gradient is final and joined before the update
     hipStream_t side = nullptr;
     int side_dev = 0, fwd_dev = 0;
+    // in their place while the caller's stream is being captured (made on first use)
+    hipStream_t cap_side = nullptr, cap_fwd = nullptr;
     std::vector<hipEvent_t> stage_ev;       // per stage: the chain is done with the stage
     hipEvent_t join_ev = nullptr;
     // pipelined runs (psw_pipeline_run): forward stream, further step sets,
@@ -524,6 +526,8 @@ struct psw_net {
             if (e) (void)hipEventDestroy(e);
         if (side) give_stream(kWeightStream, side_dev);
         if (fwd) give_stream(kForwardStream, fwd_dev);
+        for (hipStream_t c : {cap_side, cap_fwd})
+            if (c) (void)hipStreamDestroy(c);
     }
     hipEvent_t next_event()
     {
@@ -1552,6 +1556,39 @@ struct RecorderScope {
     ~RecorderScope() { psw::kernel_recorder() = nullptr; }
 };
 
+// While the caller captures `st` into a graph of its own, the net's weight and
+// forward streams are streams of this net: a fork would draw the shared ones
+// into the capture, and what other nets issue on them with it.
+struct CaptureScope {
+    psw_net* net;
+    hipStream_t side, fwd;
+    hipError_t err = hipSuccess;
+    CaptureScope(psw_net* n, hipStream_t st) : net(n), side(n->side), fwd(n->fwd)
+    {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (st) err = hipStreamIsCapturing(st, &status);  // the default stream is never captured
+        if (err != hipSuccess || status != hipStreamCaptureStatusActive) return;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // making a stream is no part of the graph
+        err = hipThreadExchangeStreamCaptureMode(&mode);
+        if (err != hipSuccess) return;
+        for (hipStream_t* c : {&net->cap_side, &net->cap_fwd})
+            if (err == hipSuccess && !*c) {
+                err = hipStreamCreateWithFlags(c, hipStreamNonBlocking);
+                if (err != hipSuccess) *c = nullptr;
+            }
+        const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+        if (err == hipSuccess) err = back;
+        if (err != hipSuccess) return;
+        net->side = net->cap_side;
+        if (fwd) net->fwd = net->cap_fwd;
+    }
+    ~CaptureScope()
+    {
+        net->side = side;
+        net->fwd = fwd;
+    }
+};
+
 }  // namespace
 
 extern "C" {
@@ -1568,6 +1605,8 @@ int psw_stage_step(psw_net* net, int64_t t, const int32_t* staleness, const floa
     if (t != net->next_t)
         return fail(PSW_ERR_STEP_ORDER, "stage_step: expected t = %lld, got %lld", (long long)net->next_t, (long long)t);
     hipStream_t st = S(stream);
+    CaptureScope capture(net, st);
+    if (capture.err != hipSuccess) return hip_check(capture.err, "stage_step: capture");
     StepIO io{t, std::vector<int64_t>(net->S), net->arena, x, labels, loss_out, lr, mom, wd, nesterov, net->grad};
     for (int s = 0; s < net->S; ++s) io.rv[s] = fwd_version(t, staleness[s]);
     Issue is{net, io};
@@ -1781,6 +1820,8 @@ int psw_pipeline_run(psw_net* net, int64_t t0, int n_steps, const int32_t* stale
         return fail(PSW_ERR_STEP_ORDER, "pipeline_run: expected t0 = %lld, got %lld", (long long)net->next_t,
                     (long long)t0);
     if (n_steps == 0) return PSW_OK;
+    CaptureScope capture(net, S(stream));
+    if (capture.err != hipSuccess) return hip_check(capture.err, "pipeline_run: capture");
     net->rec.kind = PSW_PROF_OTHER;
     RecorderScope rec_scope(net->profiling ? &net->rec : nullptr);
     int64_t issued = 0;

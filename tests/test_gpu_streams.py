@@ -69,3 +69,63 @@ def test_streams_outlive_one_net():
     assert torch.equal(run(P, second, torch.cuda.Stream()), ref)
     del second
     assert torch.equal(run(P, make(P, 8, 1), torch.cuda.Stream()), ref)  # the streams are made again
+
+
+@pytest.mark.parametrize("pipeline", [False, True])
+def test_caller_captures_beside_another_net(pipeline):
+    """A step captured into the caller's graph, with another net's step issued in
+    another thread before the capture ends: neither takes the other's work in."""
+    from paper_1912_12675_amd import psw as P
+    print("streams: the caller's capture", flush=True)
+    eager, other = make(P, 8, 1), make(P, 12, 2)
+    zero = np.zeros((T, 4), dtype=np.int32)
+    losses = torch.zeros(T, device="cuda")
+
+    def step(m):
+        net, wl, xs, ys = m
+        if pipeline:
+            net.pipeline_run(0, zero[:1], wl.lr, xs[:1], ys[:1], losses)
+        else:
+            net.step(0, zero[0], wl.lr, xs[0], ys[0])
+
+    step(eager)
+    torch.cuda.synchronize()
+    ref = eager[0].params(1)
+    ref_other = run(P, make(P, 12, 2), torch.cuda.Stream(), steps_only=True)
+
+    made = make(P, 8, 1)
+    net = made[0]
+    start = net.ring.clone()
+    net._ensure_pipeline_set()  # bound before the capture
+    errors, theirs = [], torch.cuda.Stream()
+
+    def beside():
+        try:
+            onet, owl, xs, ys = other
+            with torch.cuda.stream(theirs):
+                for t in range(T):
+                    onet.step(t, [3, 2, 1, 0], owl.lr, xs[t], ys[t])
+            theirs.synchronize()
+        except Exception as e:  # reported below
+            errors.append(e)
+
+    thread = threading.Thread(target=beside)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, capture_error_mode="thread_local"):
+        step(made)
+        thread.start()
+        thread.join()
+    assert not errors, errors
+    torch.cuda.synchronize()
+    assert torch.equal(other[0].params(T), ref_other)
+    for _ in range(3):
+        net.ring.copy_(start)
+        net.momentum.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(net.params(1), ref)
+        step_again = make(P, 8, 1)
+        step(step_again)  # eager work between the replays
+        torch.cuda.synchronize()
+        assert torch.equal(step_again[0].params(1), ref)
