@@ -65,8 +65,9 @@ __host__ __device__ inline Taps class_taps(int R, int pad, int os, int bwd, int 
 }
 
 // one output in plain fp32, in the order of the definition (zero outside the
-// input): the value wherever the split products give NaN.  A sum that has
+// input): the value wherever the matrix products give NaN.  A sum that has
 // become NaN stays one, so it ends there.
+template <int NS>
 __device__ __forceinline__ float plain_sum(const GcArgs& a, int img, int m, int oh, int ow)
 {
     float acc = 0.f;
@@ -88,7 +89,7 @@ __device__ __forceinline__ float plain_sum(const GcArgs& a, int img, int m, int 
                 }
                 ok = ok && ih < a.IH && iw < a.IW;
                 const float v = ok ? a.x[((img * a.C + c) * a.IH + ih) * a.IW + iw] : 0.f;
-                acc = fmaf(a.w[m * a.wm + c * a.wc + r * a.S + s], v, acc);
+                acc = fmaf(operand<NS>(a.w[m * a.wm + c * a.wc + r * a.S + s]), operand<NS>(v), acc);
             }
     return acc;
 }
@@ -331,10 +332,10 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
         *q = Pos{img0 + (p >> (a.lw + a.lh)), gi * a.os + ph, gj * a.os + pw};
         return gi < GH && gj < GW && q->img < a.n;
     };
-    if constexpr (NS == 3) {
-        // sums that came out as NaN (an infinity or NaN among their operands)
-        // are formed again in plain fp32 and stored here; the loop below
-        // leaves them alone
+    {
+        // sums that came out as NaN (an infinity or NaN among their operands,
+        // or at the place that a group's unused slots read) are formed again
+        // in plain fp32 and stored here; the loop below leaves them alone
         float t = 0.f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
@@ -358,7 +359,7 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
                 const int m = m0 + (k >> 2) / NTL * 16 + 4 * g + (k & 3);
                 Pos q;
                 if (!pos_at((wp * NTL + (k >> 2) % NTL) * 16 + j, &q) || m >= a.M) continue;
-                float v = plain_sum(a, q.img, m, q.oh, q.ow);
+                float v = plain_sum<NS>(a, q.img, m, q.oh, q.ow);
                 float* dst = a.y + ((q.img * a.M + m) * a.OH + q.oh) * a.OW + q.ow;
                 if (a.bias) v += a.bias[m];
                 if (a.relu) v = fmaxf(v, 0.f);
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
             for (int i = 0; i < 4; ++i) {
                 const int m = m0 + mt * 16 + 4 * g + i;
                 float v = acc[mt][nt][i];
-                if (m >= a.M || (NS == 3 && v != v)) continue;
+                if (m >= a.M || v != v) continue;
                 if (a.bias) v += a.bias[m];
                 if (a.relu) v = fmaxf(v, 0.f);
                 if (a.accumulate) v += old[mt][i];

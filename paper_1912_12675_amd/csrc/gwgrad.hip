@@ -232,9 +232,10 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
                         if (RG == 1 || r0 + r < a.R) o[r * S + s] = acc[mt][(ct * RG + r) * S + s][i];
             }
         }
-    if constexpr (NS == 3) {
-        // sums that came out as NaN (an infinity or NaN among their operands)
-        // are formed again in plain fp32; one that has become NaN stays so
+    {
+        // sums that came out as NaN (an infinity or NaN among their operands,
+        // or where a chunk reaches past dy's plane and its zeros meet x) are
+        // formed again in plain fp32; one that has become NaN stays so
         float t = 0.f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
                             const int img = (oct + (u >> (a.lw + a.lh))) * 8 + e;
                             if (img >= a.n) break;
                             const float xv = in ? a.x[((img * a.C + c) * a.H + ih) * a.W + iw] : 0.f;
-                            v = fmaf(a.dy[(img * a.K + k) * PQ + pp * a.Q + qq], xv, v);
+                            v = fmaf(operand<NS>(a.dy[(img * a.K + k) * PQ + pp * a.Q + qq]), operand<NS>(xv), v);
                         }
                     }
                 }

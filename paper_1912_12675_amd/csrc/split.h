@@ -15,7 +15,9 @@
 // NaN; the kernels form those sums again in plain fp32 (their epilogues).
 //
 // bf16 mode is the same with the first part only: operands rounded to
-// nearest even, one product.
+// nearest even, one product.  The kernels pad a block's products with zeros
+// on one side only, and a zero times an infinity or NaN that the padding met
+// makes a sum NaN that has no such operand: formed again in the same way.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -30,6 +32,13 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b)
     typedef float f2 __attribute__((ext_vector_type(2)));
     typedef __bf16 b2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, b2));
+}
+
+// an operand as the products of NS parts take it
+template <int NS>
+__device__ __forceinline__ float operand(float v)
+{
+    return NS == 1 ? (float)(__bf16)v : v;
 }
 
 // parts[0] = h, parts[1] = m, parts[2] = l of eight floats (NS = 1: h alone)

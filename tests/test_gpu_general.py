@@ -112,26 +112,30 @@ def same_class(gpu, ref, what):
     assert np.abs(g[fin] - r[fin]).max() <= TOL * np.abs(r[fin]).max(), what
 
 
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("case", [(2, 40, 12, 12, 70, 3, 3, 1, 0), (2, 12, 9, 9, 20, 3, 3, 2, 0),
-                                  (3, 20, 8, 8, 12, 1, 1, 1, 0)], ids=lambda c: "x".join(map(str, c)))
-def test_conv_not_finite(P, case):
-    """An infinity, a NaN and the largest float among the operands reach exactly the sums they enter."""
-    print("conv not finite", case, flush=True)
+                                  (3, 20, 8, 8, 12, 1, 1, 1, 0), (3, 24, 13, 11, 40, 3, 3, 1, 1),
+                                  (2, 8, 14, 13, 20, 5, 5, 1, 0)], ids=lambda c: "x".join(map(str, c)))
+def test_conv_not_finite(P, case, bf16):
+    """An infinity, a NaN and the largest float among the operands (an infinity in bf16) reach exactly the
+    sums they enter: also those in the last row and column of a plane, which a chunk of the weight gradient
+    that reaches past the output plane meets with zeros, and those that a forward group's unused slots read."""
+    print("conv not finite", case, bf16, flush=True)
     N, C, H, W, K, R, S, st, pad = case
     x, w, _, dy, _ = conv_data(case)
     w[np.abs(w) < 1e-3] = 0.01
-    x[0, 3, 4, 4], x[1, 5, 2, 2], x[1, 0, 0, 0] = np.inf, np.nan, 3.4e38
+    x[0, 3, 4, 4], x[1, 5, 2, 2], x[1, 0, 0, 0], x[N - 1, 2, H - 1, W - 1] = np.inf, np.nan, 3.4e38, np.inf
     dy[1, :, 0, 0] *= 0.1  # a product of the largest float that float32 holds
     dy[0, 1, 1, 1], dy[1, 2, 2, 2] = -np.inf, np.nan
-    d = lambda a: torch.from_numpy(a).double()  # noqa: E731
+    d = lambda a: (torch.from_numpy(a).bfloat16() if bf16 else torch.from_numpy(a)).double()  # noqa: E731
     y = torch.empty(dy.shape, device="cuda")
-    P.psw_conv_fwd(dev(x), dev(w), y, st, pad)
+    P.psw_conv_fwd(dev(x), dev(w), y, st, pad, bf16=bf16)
     same_class(y, torch.nn.functional.conv2d(d(x), d(w), None, st, pad), "fwd")
     dx = torch.empty(x.shape, device="cuda")
-    P.psw_conv_bwd_data(x.shape, dev(w), dev(dy), dx, st, pad)
+    P.psw_conv_bwd_data(x.shape, dev(w), dev(dy), dx, st, pad, bf16=bf16)
     same_class(dx, torch.nn.grad.conv2d_input(x.shape, d(w), d(dy), st, pad), "bwd_data")
     dw = torch.empty(w.shape, device="cuda")
-    P.psw_conv_bwd_weight(dev(x), dev(dy), dw, st, pad)
+    P.psw_conv_bwd_weight(dev(x), dev(dy), dw, st, pad, bf16=bf16)
     same_class(dw, torch.nn.grad.conv2d_weight(d(x), w.shape, d(dy), st, pad), "bwd_weight")
 
 
@@ -187,19 +191,20 @@ def test_fc_edges(P, case, bf16):
     close(dx, refdx + base, "dx accumulate")
 
 
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("case", [(20, 300, 130), (5, 1500, 70)], ids=lambda c: "x".join(map(str, c)))
-def test_fc_not_finite(P, case):
-    print("fc not finite", case, flush=True)
+def test_fc_not_finite(P, case, bf16):
+    print("fc not finite", case, bf16, flush=True)
     x, w, _, dy, _ = fc_data(case)
     w[np.abs(w) < 1e-3] = 0.01
     x[0, 3], x[1, 5], x[2, 7] = np.inf, np.nan, 3.4e38
     dy[2] *= 0.1  # a product of the largest float that float32 holds
     dy[3, 4], dy[4, 1] = -np.inf, np.nan
-    d = lambda a: torch.from_numpy(a).double()  # noqa: E731
+    d = lambda a: (torch.from_numpy(a).bfloat16() if bf16 else torch.from_numpy(a)).double()  # noqa: E731
     y, dx, dw = (torch.empty(s, device="cuda") for s in (dy.shape, x.shape, w.shape))
-    P.psw_fc_fwd(dev(x), dev(w), y)
+    P.psw_fc_fwd(dev(x), dev(w), y, bf16=bf16)
     same_class(y, d(x) @ d(w).t(), "fwd")
-    P.psw_fc_bwd(dev(x), dev(w), dev(dy), dw, dx=dx)
+    P.psw_fc_bwd(dev(x), dev(w), dev(dy), dw, dx=dx, bf16=bf16)
     same_class(dx, d(dy) @ d(w), "dx")
     same_class(dw, d(dy).t() @ d(x), "dw")
 
