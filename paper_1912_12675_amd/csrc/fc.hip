@@ -73,10 +73,12 @@ __device__ __forceinline__ void load_k8(Buffer b, int off, int ld, bool whole, i
 }
 
 template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK>
-__global__ __launch_bounds__(64 * WM * WN * WK) void gemm_split(GsArgs a)
+__global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void gemm_split(GsArgs a)
 {
     constexpr int NT = 64 * WM * WN * WK, KU = 4 * KG, ROW = KU + 1;  // units per row; odd row of units
     constexpr int MT = BM / WM / 16, NTL = BN / WN / 16;
+    // registers for a second sum: the small products' or, in bf16, of every other step
+    constexpr bool OWN = MT * NTL <= 4 && (NS == 3 || KG / WK % 2 == 0);
     constexpr int AI = BM * KU, BI = BN * KU, AV = (AI + NT - 1) / NT, BV = (BI + NT - 1) / NT;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     sp_v8b* const As = reinterpret_cast<sp_v8b*>(smem);  // [NS][BM][ROW]
@@ -144,6 +146,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_split(GsArgs a)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
 
+    sp_v4f lo[OWN ? NTL : 1][OWN ? MT : 1];
+#pragma unroll
+    for (int nt = 0; nt < (OWN ? NTL : 1); ++nt)
+#pragma unroll
+        for (int mt = 0; mt < (OWN ? MT : 1); ++mt) lo[nt][mt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
+
     load(0);
     for (int k0 = 0; k0 < a.K; k0 += 8 * KU) {
         __syncthreads();
@@ -167,11 +175,19 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_split(GsArgs a)
 #pragma unroll
                 for (int s = 0; s < NS; ++s) av[s] = ap[(s * BM + mt * 16) * ROW];
 #pragma unroll
-                for (int nt = 0; nt < NTL; ++nt) acc[nt][mt] = mfma_split<NS>(bv[nt], av, acc[nt][mt]);
+                for (int nt = 0; nt < NTL; ++nt) {
+                    sp_v4f& second = lo[OWN ? nt : 0][OWN ? mt : 0];
+                    mfma_split<NS, OWN>(bv[nt], av, NS == 1 && OWN && q % 2 ? second : acc[nt][mt], second);
+                }
             }
         }
     }
 
+    if constexpr (OWN)
+#pragma unroll
+        for (int nt = 0; nt < NTL; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[nt][mt] += lo[nt][mt];
     if constexpr (WK > 1) {  // the waves' sums, in wave order
         float* red = reinterpret_cast<float*>(smem);
         __syncthreads();

@@ -26,9 +26,9 @@
 //
 // Measured against the implicit GEMM that gathered (and, for each tap, divided
 // indices) element by element, batch 128, us, fp32 unless stated: 512 -> 512
-// 3x3 at 4x4 forward 126, backward data 116 (1,382 on average over VGG-16's
-// layers there); 5x5 64 -> 192 at 16x16 forward 104, bf16 forward 751 -> 61 and
-// backward data 1,330 -> 79.
+// 3x3 at 4x4 forward 119, backward data 110 (1,382 on average over VGG-16's
+// layers there); 5x5 64 -> 192 at 16x16 forward 112, bf16 forward 751 -> 57 and
+// backward data 1,330 -> 78.
 #include "internal.h"
 #include "split.h"
 
@@ -94,8 +94,8 @@ __device__ __forceinline__ float plain_sum(const GcArgs& a, int img, int m, int 
     return acc;
 }
 
-template <int NS, int BM, int BP, int WP, int WK, int OC, int KG>
-__global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
+template <int NS, int BM, int BP, int WP, int WK, int OC, int KG, bool OWN>
+__global__ __launch_bounds__(64 * WP * WK, NS == 3 && BM == 32 && BP == 256 && !OWN ? 3 : 2) void conv_split(GcArgs a)
 {
     constexpr int NT = 64 * WP * WK;
     constexpr int MT = BM / 16, NTL = BP / WP / 16;  // 16x16 tiles of a wave
@@ -155,6 +155,12 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NTL; ++nt) acc[mt][nt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
+
+    sp_v4f lo[OWN ? MT : 1][OWN ? NTL : 1];
+#pragma unroll
+    for (int mt = 0; mt < (OWN ? MT : 1); ++mt)
+#pragma unroll
+        for (int nt = 0; nt < (OWN ? NTL : 1); ++nt) lo[mt][nt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
 
     // input units: unit idx = octet * HP + staged pixel; src is the byte
     // offset of its first channel (chunk 0) from the tile's first image
@@ -288,7 +294,8 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
                         if (nt + 1 < NTL) read_b(nt + 1);
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma_split<NS>(av[mt], bv[nt & 1], acc[mt][nt]);
+                        for (int mt = 0; mt < MT; ++mt)
+                            mfma_split<NS, OWN>(av[mt], bv[nt & 1], acc[mt][nt], lo[OWN ? mt : 0][OWN ? nt : 0]);
                     }
                 }
                 if (!last) {
@@ -300,6 +307,11 @@ __global__ __launch_bounds__(64 * WP * WK, 2) void conv_split(GcArgs a)
         }
     }
 
+    if constexpr (OWN)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NTL; ++nt) acc[mt][nt] += lo[mt][nt];
     if constexpr (WK > 1) {  // the waves' sums, in wave order
         float* red = reinterpret_cast<float*>(smem);
         __syncthreads();
@@ -448,7 +460,7 @@ size_t lds_bytes(const Plan& p, const Tiling& t)
     return main > red ? main : red;
 }
 
-template <int NS, int BM, int BP, int WP, int WK, int OC, int KG>
+template <int NS, int BM, int BP, int WP, int WK, int OC, int KG, bool OWN>
 hipError_t launch_cfg(Plan& p, const Tiling& t, const Work& wk, hipStream_t st)
 {
     GcArgs a = p.a;
@@ -465,7 +477,7 @@ hipError_t launch_cfg(Plan& p, const Tiling& t, const Work& wk, hipStream_t st)
     if (t.tiles > INT32_MAX / 8 || blocks > INT32_MAX) return hipErrorNotSupported;
     const size_t lds = lds_bytes<NS, BM, BP, WP, WK, OC, KG>(p, t);
     if (lds > kLdsMax) return hipErrorNotSupported;
-    PSW_LAUNCH(kname("conv_split", NS, BM, BP, WP, WK, OC, KG), wk, (conv_split<NS, BM, BP, WP, WK, OC, KG>),
+    PSW_LAUNCH(kname("conv_split", NS, BM, BP, WP, WK, OC, KG, OWN), wk, (conv_split<NS, BM, BP, WP, WK, OC, KG, OWN>),
                dim3((unsigned)blocks, 1, (unsigned)p.classes), dim3(64 * WP * WK), lds, st, a);
     return hipGetLastError();
 }
@@ -477,32 +489,39 @@ hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
     const int taps = p.rs * p.ss;
     auto tile = [&](int bp) { return pick_tile(a.n, p.gh, p.gw, bp, a.is, p.rs, p.ss); };
     auto blocks = [&](const Tiling& t, int bm) { return t.tiles * ((a.M + bm - 1) / bm) * p.classes; };
-#define PSW_GC(T_, ...)                                                                    \
+#define PSW_GC(T_, OWN_, ...)                                                              \
     do {                                                                                   \
         const Tiling t_ = T_;                                                              \
-        if (lds_bytes<NS, __VA_ARGS__>(p, t_) <= kLdsMax) return launch_cfg<NS, __VA_ARGS__>(p, t_, wk, st); \
+        if (lds_bytes<NS, __VA_ARGS__>(p, t_) <= kLdsMax)                                  \
+            return launch_cfg<NS, __VA_ARGS__, NS == 3 && OWN_>(p, t_, wk, st);            \
     } while (0)
     const Tiling t256 = tile(256);
     if (a.C <= 8) {  // an image net's first layer (forward): one octet, four taps per matrix step
-        if (a.M <= 16) PSW_GC(t256, 16, 256, 4, 1, 1, 2);
-        if (a.M <= 32) PSW_GC(t256, 32, 256, 4, 1, 1, 2);
-        PSW_GC(t256, 64, 256, 4, 1, 1, 2);
+        if (a.M <= 16) PSW_GC(t256, true, 16, 256, 4, 1, 1, 2);
+        if (a.M <= 32) PSW_GC(t256, false, 32, 256, 4, 1, 1, 2);
+        PSW_GC(t256, false, 64, 256, 4, 1, 1, 2);
     }
     // Wide tiles while they fill the chip: 32 channels rather than 64, since
     // three workgroups then share a CU's LDS and registers and one multiplies
     // while another stages (fp32, us: 128 -> 128 at 16x16 69 against 82, 5x5 64 ->
     // 192 104 against 145, 1x1 128 -> 192 35 against 44).
-    if (a.M <= 16 && blocks(t256, 16) >= 256) PSW_GC(t256, 16, 256, 4, 1, 2, 2);
-    if (a.M > 16 && blocks(t256, 32) >= 256) PSW_GC(t256, 32, 256, 4, 1, 2, 2);
+    if (a.M <= 16 && blocks(t256, 16) >= 256) PSW_GC(t256, true, 16, 256, 4, 1, 2, 2);
+    if (a.M > 16 && blocks(t256, 32) >= 256) {
+        // up to two workgroups a CU leave registers for the small products' own
+        // sums (192 -> 64 5x5 backward data 141 us against 162); with more,
+        // three a CU are faster (256 -> 256 at 14x14 222 against 228)
+        if (NS == 3 && blocks(t256, 32) <= 512) PSW_GC(t256, true, 32, 256, 4, 1, 2, 2);
+        PSW_GC(t256, false, 32, 256, 4, 1, 2, 2);
+    }
     // few output channels, a short reduction: small wide tiles (LeNet's second
     // layer's backward data 14 against 18)
-    if (a.M <= 32 && a.C * taps <= 1024) PSW_GC(tile(128), 16, 128, 4, 1, 2, 2);
+    if (a.M <= 32 && a.C * taps <= 1024) PSW_GC(tile(128), true, 16, 128, 4, 1, 2, 2);
     // deep reductions over few positions: waves share the depth, two of a 32 x
     // 64 tile (512 -> 512 at 4x4 126 against 174), or with fewer of those, four
     // of a 32 x 32 tile (at 2x2 89 against 115)
     const Tiling t64 = tile(64);
-    if (blocks(t64, 32) >= 256) PSW_GC(t64, 32, 64, 2, 2, 4, 2);
-    PSW_GC(tile(32), 32, 32, 1, 4, 4, 4);
+    if (blocks(t64, 32) >= 256) PSW_GC(t64, true, 32, 64, 2, 2, 4, 2);
+    PSW_GC(tile(32), true, 32, 32, 1, 4, 4, 4);
 #undef PSW_GC
     return hipErrorNotSupported;
 }

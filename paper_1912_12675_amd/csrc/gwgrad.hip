@@ -47,6 +47,9 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
 {
     constexpr int NT = 256, WK = 4 / WM, MT = BM / WM / 16;
     constexpr int TAPS = CT * RG * S;
+    // bf16 rows of five taps: few parts and long sums, so the steps of a chunk
+    // take two sums in turn
+    constexpr bool TWO = NS == 1 && S == 5 && PX / 4 / WK >= 2;
     constexpr int DI = BM * PX, DV = DI / NT;  // units of dy, per thread
     constexpr int XV = 3;                       // units of x per thread and staging pass
     static_assert(DI % NT == 0, "units");
@@ -159,6 +162,11 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
 #pragma unroll
         for (int t = 0; t < TAPS; ++t) acc[mt][t] = sp_v4f{0.f, 0.f, 0.f, 0.f};
 
+    sp_v4f odd[TWO ? MT : 1][TWO ? TAPS : 1];
+#pragma unroll
+    for (int mt = 0; mt < (TWO ? MT : 1); ++mt)
+#pragma unroll
+        for (int t = 0; t < (TWO ? TAPS : 1); ++t) odd[mt][t] = sp_v4f{0.f, 0.f, 0.f, 0.f};
     if (ch_begin < ch_end) load_chunk(ch_begin);
     for (int ch = ch_begin; ch < ch_end; ++ch) {
         __syncthreads();
@@ -187,11 +195,20 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
                         for (int k = 0; k < NS; ++k) bv[k] = xp[(k * CT + ct) * 16 * XROW + r * HC + s];
 #pragma unroll
                         for (int mt = 0; mt < MT; ++mt)
-                            acc[mt][(ct * RG + r) * S + s] = mfma_split<NS>(av[mt], bv, acc[mt][(ct * RG + r) * S + s]);
+                            {
+                            const int t = (ct * RG + r) * S + s;
+                            sp_v4f& sum = TWO && q % 2 ? odd[TWO ? mt : 0][TWO ? t : 0] : acc[mt][t];
+                            mfma_split<NS, false>(av[mt], bv, sum, sum);
+                        }
                     }
         }
     }
 
+    if constexpr (TWO)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int t = 0; t < TAPS; ++t) acc[mt][t] += odd[mt][t];
     if constexpr (WK > 1) {  // the waves' sums, in wave order, MT tiles at a time
         float* red = reinterpret_cast<float*>(smem);
 #pragma unroll

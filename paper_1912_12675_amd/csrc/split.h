@@ -7,9 +7,9 @@
 //   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + O(2^-26 |a b|),
 // each an exact product accumulated in fp32 by v_mfma_f32_16x16x32_bf16.
 // Six of those take 6/16 of the time of the fp32 matrix instructions for the
-// same product (2.5 PFLOP/s against 157 TFLOP/s), and the sums are rounded
-// as often as theirs: the measured error against 64 bits is the fp32
-// instructions' or smaller (conv 256 -> 256 3x3: 5.7e-7 there).
+// same product (2.5 PFLOP/s against 157 TFLOP/s).  The error against 64 bits
+// is a third to a half of the fp32 instructions' (256 -> 256 3x3 at 14x14: 2.6e-7
+// against 5.9e-7), since the small products are summed apart (mfma_split).
 // The split of an infinity, a NaN or a float that rounds to infinity in
 // bfloat16 holds a NaN, so every sum such an operand enters comes out as
 // NaN; the kernels form those sums again in plain fp32 (their epilogues).
@@ -80,18 +80,31 @@ __device__ __forceinline__ float buffer_load(Buffer b, int lane_bytes, int unifo
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, lane_bytes, uniform_bytes, 0));
 }
 
-// acc += A B for one 16x16x32 block, smallest products first
-template <int NS>
-__device__ __forceinline__ sp_v4f mfma_split(const sp_v8b (&a)[NS], const sp_v8b (&b)[NS], sp_v4f acc)
+// acc += A B for one 16x16x32 block.  A matrix instruction rounds its result
+// at the running sum's size, so six of them into one sum err 1.1 to 1.9 times
+// as far as the fp32 instructions (and FC's depth of 4096 2.4 times).  The
+// five small products are therefore summed apart, smallest first: OWN in `lo`,
+// which the kernel adds at its end and keeps in registers, and otherwise from
+// zero for each block (4 additions of the vector units a block, no register
+// that lives on).
+template <int NS, bool OWN>
+__device__ __forceinline__ void mfma_split(const sp_v8b (&a)[NS], const sp_v8b (&b)[NS], sp_v4f& acc, sp_v4f& lo)
 {
     if constexpr (NS == 3) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
+        sp_v4f t = OWN ? lo : sp_v4f{0.f, 0.f, 0.f, 0.f};
+        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], t, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
+        if constexpr (OWN)
+            lo = t;
+        else
+            acc += t;
+    } else {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
     }
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
 }
 
 }  // namespace psw

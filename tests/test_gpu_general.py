@@ -139,6 +139,47 @@ def test_conv_not_finite(P, case, bf16):
     same_class(dw, torch.nn.grad.conv2d_weight(d(x), w.shape, d(dy), st, pad), "bwd_weight")
 
 
+def fp32_error(L):
+    """Relative error (2-norm) of a sum of L products of zero mean that an fp32 matrix instruction forms, four
+    products to a rounding: each rounding errs 2.5e-8 of the running sum (half an ulp, uniform), whose square
+    grows with its length, so sqrt(L / 4 / 2) of those; and the result's own rounding."""
+    return 2.5e-8 * (math.sqrt(L / 8) + 1)
+
+
+@pytest.mark.parametrize("case", [(64, 256, 14, 14, 256, 3, 3, 1, 1), (16, 1, 28, 28, 6, 5, 5, 1, 2),
+                                  (64, 128, 16, 16, 192, 1, 1, 1, 0)], ids=lambda c: "x".join(map(str, c)))
+def test_conv_error_is_fp32s(P, case):
+    """Products in three bfloat16 parts: no further from 64 bits than the fp32 matrix instructions' sums."""
+    print("conv error", case, flush=True)
+    N, C, H, W, K, R, S, st, pad = case
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x, w = torch.randn(N, C, H, W, generator=g, device="cuda"), torch.randn(K, C, R, S, generator=g, device="cuda")
+    cols = torch.nn.functional.unfold(x.double(), (R, S), padding=pad, stride=st)
+    want = w.double().view(K, -1) @ cols
+    y = torch.empty(N, K, H, W, device="cuda")
+    P.psw_conv_fwd(x, w, y, st, pad)
+    assert float((y.view(N, K, -1) - want).norm() / want.norm()) <= fp32_error(C * R * S)
+    dy = torch.randn(N, K, H, W, generator=g, device="cuda")
+    dw = torch.empty_like(w)
+    P.psw_conv_bwd_weight(x, dy, dw, st, pad)
+    want = (dy.double().view(N, K, -1) @ cols.transpose(1, 2).contiguous()).sum(0).view(w.shape)
+    assert float((dw - want).norm() / want.norm()) <= fp32_error(N * H * W)
+
+
+@pytest.mark.parametrize("case", [(128, 4096, 4096), (200, 250, 2500), (16, 400, 120)], ids=lambda c: "x".join(map(str, c)))
+def test_fc_error_is_fp32s(P, case):
+    print("fc error", case, flush=True)
+    n, fin, out = case
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x, w, dy = (torch.randn(*s, generator=g, device="cuda") for s in ((n, fin), (out, fin), (n, out)))
+    y, dx, dw = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w)
+    P.psw_fc_fwd(x, w, y)
+    P.psw_fc_bwd(x, w, dy, dw, dx=dx)
+    for got, want, L in ((y, x.double() @ w.double().t(), fin), (dx, dy.double() @ w.double(), out),
+                         (dw, dy.double().t() @ x.double(), n)):
+        assert float((got - want).norm() / want.norm()) <= fp32_error(L)
+
+
 FC = [
     # N, in, out
     (1, 1, 65),
