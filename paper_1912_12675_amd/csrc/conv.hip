@@ -221,7 +221,7 @@ __global__ __launch_bounds__(256) void igemm_kernel(IgArgs a)
         }
 }
 
-// dw[i] = sum_z part[z][i] in a fixed order (deterministic): the splits z =
+// out[i] (+)= sum_z part[z][i] in a fixed order (deterministic): the splits z =
 // zl (mod 16) in increasing z for each of 16 classes, then the class sums in
 // order.  G = 16: a block owns 16 V outputs, a thread one class of V of them.
 // G = 1, up to 16 splits (the same sums, a class has one split): a thread all
@@ -229,7 +229,8 @@ __global__ __launch_bounds__(256) void igemm_kernel(IgArgs a)
 // do for two splits (512 x 512 x 9: 42 us), and with V = 1 a block read half of
 // each 128-byte line.
 template <int V, int G>
-__global__ __launch_bounds__(256) void reduce_splits(const float* part, int splits, int64_t count, float* out)
+__global__ __launch_bounds__(256) void reduce_splits(const float* part, int splits, int64_t count, float* out,
+                                                     int accumulate)
 {
     typedef float fv __attribute__((ext_vector_type(V)));
     constexpr int O = 256 / G;  // threads along the outputs
@@ -250,7 +251,10 @@ __global__ __launch_bounds__(256) void reduce_splits(const float* part, int spli
         for (; z < splits; z += G) acc += *reinterpret_cast<const fv*>(part + (int64_t)z * count + i);
     }
     if constexpr (G == 1) {
-        if (i < count) *reinterpret_cast<fv*>(out + i) = acc;
+        if (i < count) {
+            if (accumulate) acc = *reinterpret_cast<const fv*>(out + i) + acc;
+            *reinterpret_cast<fv*>(out + i) = acc;
+        }
         return;
     }
 #pragma unroll
@@ -260,31 +264,35 @@ __global__ __launch_bounds__(256) void reduce_splits(const float* part, int spli
     if (threadIdx.x < O * V && j < count) {
         float t = 0.f;
         for (int k = 0; k < G; ++k) t += sh[k][threadIdx.x];
-        out[j] = t;
+        out[j] = accumulate ? out[j] + t : t;
     }
 }
 
-hipError_t launch_reduce(const float* part, int splits, int64_t count, float* out, hipStream_t st)
+}  // namespace
+
+hipError_t reduce_parts(const float* part, int splits, int64_t count, float* out, int accumulate, hipStream_t st)
 {
-    const Work wk{(double)splits * count, kF * (splits + 1.0) * count};
+    const Work wk{(double)splits * count, kF * (splits + 1.0 + accumulate) * count};
     const bool vec = count % 4 == 0 && (uintptr_t)part % 16 == 0 && (uintptr_t)out % 16 == 0;
     auto blocks = [&](int per) { return dim3((unsigned)((count + per - 1) / per)); };
     if (splits <= 16) {
         if (vec)
             PSW_LAUNCH(kname("reduce_splits", 4, 1), wk, (reduce_splits<4, 1>), blocks(1024), dim3(256), 0, st, part, splits,
-                       count, out);
+                       count, out, accumulate);
         else
             PSW_LAUNCH(kname("reduce_splits", 1, 1), wk, (reduce_splits<1, 1>), blocks(256), dim3(256), 0, st, part, splits,
-                       count, out);
+                       count, out, accumulate);
     } else if (vec) {
         PSW_LAUNCH(kname("reduce_splits", 4, 16), wk, (reduce_splits<4, 16>), blocks(64), dim3(256), 0, st, part, splits,
-                   count, out);
+                   count, out, accumulate);
     } else {
         PSW_LAUNCH(kname("reduce_splits", 1, 16), wk, (reduce_splits<1, 16>), blocks(16), dim3(256), 0, st, part, splits,
-                   count, out);
+                   count, out, accumulate);
     }
     return hipGetLastError();
 }
+
+namespace {
 
 template <int PASS, bool BF16>
 hipError_t launch(const IgArgs& a, int splits, hipStream_t st)
@@ -485,7 +493,7 @@ hipError_t conv_bwd_weight(const ConvShape& cs, const float* x, const float* dy,
         hipError_t e = conv3x3_wgrad(cs.n, cs.c, cs.h, cs.w, cs.k, cs.stride, x, dy, (float*)ws, st, bf16);
         if (e != hipErrorNotSupported) {  // otherwise (misaligned operands) fall through to the implicit GEMM
             if (e != hipSuccess) return e;
-            e = launch_reduce((const float*)ws, zd, (int64_t)mn, dw, st);
+            e = reduce_parts((const float*)ws, zd, (int64_t)mn, dw, 0, st);
             if (e != hipSuccess || !db) return e;
             const size_t zmax = conv_bwd_weight_ws_bytes(cs, bf16) - channel_sum_ws_bytes(cs.n, cs.k, cs.p * cs.q);
             char* rest = (char*)ws + zmax;
@@ -507,7 +515,7 @@ hipError_t conv_bwd_weight(const ConvShape& cs, const float* x, const float* dy,
         e = bf16 ? launch<BWD_WEIGHT, true>(a, zz, st) : launch<BWD_WEIGHT, false>(a, zz, st);
     }
     if (e != hipSuccess) return e;
-    e = launch_reduce((const float*)ws, zz, (int64_t)mn, dw, st);
+    e = reduce_parts((const float*)ws, zz, (int64_t)mn, dw, 0, st);
     if (e != hipSuccess || !db) return e;
     const size_t zmax = conv_bwd_weight_ws_bytes(cs, bf16) - channel_sum_ws_bytes(cs.n, cs.k, cs.p * cs.q);
     char* rest = (char*)ws + zmax;

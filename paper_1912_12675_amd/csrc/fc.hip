@@ -19,6 +19,7 @@
 // the fp32 matrix rate).  Forward is bound by the delivery of x to every block
 // of columns, dx and dw by their stages' phases following one another.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 #include "split.h"
@@ -36,13 +37,15 @@ struct GsArgs {
     int nblocks, mblocks;
     int relu, accumulate;
     int vec;            // C rows are 16-byte aligned
+    int kchunk;         // k of one part (blockIdx.y), a multiple of the stage
+    int64_t part;       // floats from one part's C to the next
 };
 
 template <bool AK, bool BK>
-__device__ __forceinline__ float plain_dot(const GsArgs& a, int m, int n)
+__device__ __forceinline__ float plain_dot(const GsArgs& a, int m, int n, int k0, int k1)
 {
     float v = 0.f;
-    for (int k = 0; k < a.K && v == v; ++k)
+    for (int k = k0; k < k1 && v == v; ++k)
         v = fmaf(AK ? a.A[(int64_t)m * a.lda + k] : a.A[(int64_t)k * a.lda + m],
                  BK ? a.B[(int64_t)n * a.ldb + k] : a.B[(int64_t)k * a.ldb + n], v);
     return v;
@@ -99,26 +102,32 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
     const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
     const int g = lane >> 4, j = lane & 15;
 
+    const int kbeg = (int)blockIdx.y * a.kchunk, kend = (int)min((int64_t)a.K, (int64_t)kbeg + a.kchunk);
+    float* const C = a.C + blockIdx.y * a.part;
+
     float ar[AV][8], br[BV][8];
+    // eight k of row r0 + row of one operand from stage k0's octet o
+    auto load_op = [&](auto kc, const float* p, int ld, int rows, int r0, int row, bool in, int o, int k0, bool whole,
+                       float(&r)[8]) {
+        constexpr bool KC = decltype(kc)::value;
+        const Buffer b = KC ? make_buffer(p + (int64_t)r0 * ld + k0, ((int64_t)(rows - r0) * ld - k0) * 4)
+                            : make_buffer(p + (int64_t)k0 * ld + r0, ((int64_t)(a.K - k0) * ld - r0) * 4);
+        load_k8<KC>(b, in ? (KC ? row * ld + o * 8 : row + o * 8 * ld) * 4 : kOutside, ld, whole, kend - k0 - o * 8,
+                    r);
+    };
     auto load = [&](int k0) {
-        const bool whole = k0 + 8 * KU <= a.K;
-        const Buffer ab = AK ? make_buffer(a.A + (int64_t)m0 * a.lda + k0, ((int64_t)(a.M - m0) * a.lda - k0) * 4)
-                             : make_buffer(a.A + (int64_t)k0 * a.lda + m0, ((int64_t)(a.K - k0) * a.lda - m0) * 4);
-        const Buffer bb = BK ? make_buffer(a.B + (int64_t)n0 * a.ldb + k0, ((int64_t)(a.N - n0) * a.ldb - k0) * 4)
-                             : make_buffer(a.B + (int64_t)k0 * a.ldb + n0, ((int64_t)(a.K - k0) * a.ldb - n0) * 4);
+        const bool whole = k0 + 8 * KU <= kend;
 #pragma unroll
         for (int v = 0; v < AV; ++v) {
             const int idx = tid + v * NT, row = AK ? idx / KU : idx % BM, o = AK ? idx % KU : idx / BM;
-            const bool in = m0 + row < a.M && (AI % NT == 0 || idx < AI);
-            load_k8<AK>(ab, in ? (AK ? row * a.lda + o * 8 : row + o * 8 * a.lda) * 4 : kOutside, a.lda, whole,
-                        a.K - k0 - o * 8, ar[v]);
+            load_op(std::bool_constant<AK>{}, a.A, a.lda, a.M, m0, row, m0 + row < a.M && (AI % NT == 0 || idx < AI), o, k0,
+                    whole, ar[v]);
         }
 #pragma unroll
         for (int v = 0; v < BV; ++v) {
             const int idx = tid + v * NT, row = BK ? idx / KU : idx % BN, o = BK ? idx % KU : idx / BN;
-            const bool in = n0 + row < a.N && (BI % NT == 0 || idx < BI);
-            load_k8<BK>(bb, in ? (BK ? row * a.ldb + o * 8 : row + o * 8 * a.ldb) * 4 : kOutside, a.ldb, whole,
-                        a.K - k0 - o * 8, br[v]);
+            load_op(std::bool_constant<BK>{}, a.B, a.ldb, a.N, n0, row, n0 + row < a.N && (BI % NT == 0 || idx < BI), o, k0,
+                    whole, br[v]);
         }
     };
     auto put = [&](sp_v8b* dst, int stride, const float(&r)[8]) {
@@ -152,16 +161,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
 #pragma unroll
         for (int mt = 0; mt < (OWN ? MT : 1); ++mt) lo[nt][mt] = sp_v4f{0.f, 0.f, 0.f, 0.f};
 
-    load(0);
-    for (int k0 = 0; k0 < a.K; k0 += 8 * KU) {
+    load(kbeg);
+    for (int k0 = kbeg; k0 < kend; k0 += 8 * KU) {
         __syncthreads();
         store();
         __syncthreads();
-        if (k0 + 8 * KU < a.K) load(k0 + 8 * KU);
+        if (k0 + 8 * KU < kend) load(k0 + 8 * KU);
 #pragma unroll
         for (int q = 0; q < KG / WK; ++q) {
             const int u = (q * WK + wk) * 4 + g;
-            if (k0 + (q * WK + wk) * 32 >= a.K) break;
+            if (k0 + (q * WK + wk) * 32 >= kend) break;
             const sp_v8b* ap = As + (wm * MT * 16 + j) * ROW + u;
             const sp_v8b* bp = Bs + (wn * NTL * 16 + j) * ROW + u;
             sp_v8b bv[NTL][NS];
@@ -235,10 +244,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
                 const int q = __ffsll((unsigned long long)bad) - 1;
                 const int m = mrow + (q >> 2) % MT * 16, n = ncol + (q >> 2) / MT * 16 + (q & 3);
                 if (m >= a.M || n >= a.N) continue;
-                float v = plain_dot<AK, BK>(a, m, n);
+                float v = plain_dot<AK, BK>(a, m, n, kbeg, kend);
                 if (a.bias) v += a.bias[n];
                 if (a.relu) v = fmaxf(v, 0.f);
-                float* dst = a.C + (int64_t)m * a.N + n;
+                float* dst = C + (int64_t)m * a.N + n;
                 *dst = a.accumulate ? *dst + v : v;
             }
         }
@@ -250,7 +259,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
 #pragma unroll
         for (int nt = 0; nt < NTL; ++nt) {
             const int n = ncol + nt * 16;
-            float* dst = a.C + (int64_t)m * a.N + n;
+            float* dst = C + (int64_t)m * a.N + n;
             sp_v4f v = acc[nt][mt];
             const bool fine = NS != 3 || (v[0] == v[0] && v[1] == v[1] && v[2] == v[2] && v[3] == v[3]);
             if (a.vec && n + 4 <= a.N && fine) {
@@ -483,17 +492,34 @@ __global__ void gemm_plain(GsArgs a, int bf16)
 }
 
 template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK>
-hipError_t gs_launch(GsArgs a, const Work& wk, hipStream_t st)
+hipError_t gs_launch(GsArgs a, const Work& wk, hipStream_t st, int parts = 1)
 {
     a.mblocks = (a.M + BM - 1) / BM;
     a.nblocks = (a.N + BN - 1) / BN;
     const int64_t blocks = (int64_t)(a.nblocks < 8 ? a.nblocks : (a.nblocks + 7) / 8 * 8) * a.mblocks;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    if (parts == 1) a.kchunk = INT32_MAX / (32 * KG) * (32 * KG);
     constexpr size_t main = (size_t)NS * 16 * (BM + BN) * (4 * KG + 1), red = (size_t)(WK - 1) * BM * BN * 4;
     PSW_LAUNCH(kname("gemm_split", NS, BM, BN, WM, WN, WK, KG, AK, BK), wk,
-               (gemm_split<NS, BM, BN, WM, WN, WK, KG, AK, BK>), dim3((unsigned)blocks), dim3(64 * WM * WN * WK),
-               main > red ? main : red, st, a);
+               (gemm_split<NS, BM, BN, WM, WN, WK, KG, AK, BK>), dim3((unsigned)blocks, (unsigned)parts),
+               dim3(64 * WM * WN * WK), main > red ? main : red, st, a);
     return hipGetLastError();
+}
+
+constexpr int64_t kRowsL2 = 4 << 20;  // bytes
+
+// The depth in parts of a multiple of 64 k, whose sums meet in the workspace:
+// where a wave of the one-launch tile would add up more than 16 steps of 32 k
+// and the tiles leave the chip room.  `splits` parts at most, `tiles` of 64 x 64.
+int gs_parts(const GsArgs& a, int64_t tiles, int waves, int bf16, size_t ws_bytes, int* kchunk)
+{
+    if (a.K <= 512 * waves || tiles >= 512) return 1;
+    const int64_t least = bf16 ? 128 : 64;
+    int64_t z = std::min((1024 + tiles - 1) / tiles, (a.K + least - 1) / least);
+    z = std::min(z, (int64_t)(ws_bytes / ((size_t)a.M * a.N * sizeof(float))));
+    if (z <= 1) return 1;
+    *kchunk = (int)(((a.K + z - 1) / z + 63) / 64 * 64);
+    return (a.K + *kchunk - 1) / *kchunk;
 }
 
 // Tiles, each with the reason it is there (fp32, us; 128 rows unless said):
@@ -502,15 +528,28 @@ hipError_t gs_launch(GsArgs a, const Work& wk, hipStream_t st)
 //    190); dx 128 x 16384, k 4096, is 128 tiles of it: 281 (64 x 64 166);
 //  - few outputs over a deep k take 16 waves on k: 16 x 227, k 4096: 20.
 template <int NS, bool AK, bool BK>
-hipError_t gs_pick(const GsArgs& a, const Work& wk, hipStream_t st)
+hipError_t gs_pick(GsArgs a, const Work& wk, float* ws, size_t ws_bytes, hipStream_t st)
 {
     auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    const int64_t tiles = blocks(64, 64);
+    const bool deep = a.K > 512 && blocks(16, 16) <= 256;
+    const int waves = tiles >= 128 ? 1 : deep ? 16 : 4;
+    const int parts = ws ? gs_parts(a, tiles, waves, NS == 1, ws_bytes, &a.kchunk) : 1;
+    if (parts > 1) {
+        GsArgs p = a;
+        p.C = ws;
+        p.part = (int64_t)a.M * a.N;
+        p.vec = a.N % 4 == 0 && (uintptr_t)ws % 16 == 0;
+        p.accumulate = 0;
+        const hipError_t e = gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(p, wk, st, parts);
+        return e != hipSuccess ? e : reduce_parts(ws, parts, p.part, a.C, a.accumulate, st);
+    }
     // bf16 forward of more than 64 rows whose x is larger than the L2 (see gemm())
-    if constexpr (AK && BK)
+    if constexpr (NS == 1 && AK && BK)
         if (a.M > 64 && a.M <= 256) return gs_launch<NS, 128, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
     if (blocks(128, 128) >= 512) return gs_launch<NS, 128, 128, 2, 2, 1, 1, AK, BK>(a, wk, st);
-    if (blocks(64, 64) >= 128) return gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(a, wk, st);
-    if (a.K > 512 && blocks(16, 16) <= 256) return gs_launch<NS, 16, 16, 1, 1, 16, 16, AK, BK>(a, wk, st);
+    if (tiles >= 128) return gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(a, wk, st);
+    if (deep) return gs_launch<NS, 16, 16, 1, 1, 16, 16, AK, BK>(a, wk, st);
     if (blocks(32, 32) >= 64) return gs_launch<NS, 32, 32, 1, 1, 4, 4, AK, BK>(a, wk, st);
     return gs_launch<NS, 16, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
 }
@@ -537,10 +576,8 @@ hipError_t rows_pick(const GsArgs& a, const Work& wk, hipStream_t st)
     return a.K > 512 ? rows_launch<BF, 1, 16>(a, wk, st) : rows_launch<BF, 1, 4>(a, wk, st);
 }
 
-constexpr int64_t kRowsL2 = 4 << 20;  // bytes
-
 template <bool AK, bool BK>
-hipError_t gemm(GsArgs a, int bf16, hipStream_t st)
+hipError_t gemm(GsArgs a, int bf16, float* ws, size_t ws_bytes, hipStream_t st)
 {
     const Work wk{2.0 * a.M * a.N * (double)a.K,
                   kF * ((double)a.M * a.K + (double)a.K * a.N + (1.0 + a.accumulate) * a.M * (double)a.N)};
@@ -559,7 +596,7 @@ hipError_t gemm(GsArgs a, int bf16, hipStream_t st)
     if constexpr (AK && BK)
         if (a.M <= (bf16 && a.N >= 1024 && (int64_t)a.M * a.K * 4 > kRowsL2 ? 64 : 256) && !a.accumulate)
             return bf16 ? rows_pick<true>(a, wk, st) : rows_pick<false>(a, wk, st);
-    return bf16 ? gs_pick<1, AK, BK>(a, wk, st) : gs_pick<3, AK, BK>(a, wk, st);
+    return bf16 ? gs_pick<1, AK, BK>(a, wk, ws, ws_bytes, st) : gs_pick<3, AK, BK>(a, wk, ws, ws_bytes, st);
 }
 
 }  // namespace
@@ -572,11 +609,11 @@ hipError_t fc_gemm_fwd(int n, int in, int out, const float* x, const float* w, c
     a.M = n; a.N = out; a.K = in;
     a.lda = in;  // x[n][i]
     a.ldb = in;  // w[o][i]
-    return gemm<true, true>(a, bf16, st);
+    return gemm<true, true>(a, bf16, nullptr, 0, st);
 }
 
 hipError_t fc_gemm_bwd(int n, int in, int out, const float* x, const float* w, const float* dy, float* dx,
-                       int dx_accumulate, float* dw, float* db, int bf16, hipStream_t st)
+                       int dx_accumulate, float* dw, float* db, int bf16, void* ws, size_t ws_bytes, hipStream_t st)
 {
     if (dx) {
         GsArgs a{};
@@ -584,7 +621,7 @@ hipError_t fc_gemm_bwd(int n, int in, int out, const float* x, const float* w, c
         a.M = n; a.N = in; a.K = out;
         a.lda = out;  // dy[n][o]
         a.ldb = in;   // w[o][i], k = o
-        const hipError_t e = gemm<true, false>(a, bf16, st);
+        const hipError_t e = gemm<true, false>(a, bf16, (float*)ws, ws_bytes, st);
         if (e != hipSuccess) return e;
     }
     GsArgs a{};
@@ -592,7 +629,7 @@ hipError_t fc_gemm_bwd(int n, int in, int out, const float* x, const float* w, c
     a.M = out; a.N = in; a.K = n;
     a.lda = out;  // dy[n][o], k = n
     a.ldb = in;   // x[n][i], k = n
-    const hipError_t e = gemm<false, false>(a, bf16, st);
+    const hipError_t e = gemm<false, false>(a, bf16, nullptr, 0, st);
     if (e != hipSuccess || !db) return e;
     // the column sums of dy (not a product, so never rounded to bf16)
     PSW_LAUNCH(kname("col_sum_k"), (Work{(double)n * out, kF * ((double)n * out + out)}), col_sum_k,

@@ -268,6 +268,8 @@ hipError_t conv_general(const ConvShape& cs, int bwd, const float* x, const floa
 // launched) for kernels without a configuration.
 hipError_t conv_general_wgrad(const ConvShape& cs, const float* x, const float* dy, float* part, int max_splits,
                               int* splits, bool dry, int bf16, hipStream_t st);
+// out[i] (+)= sum of part[z][i] over z < splits, in a fixed order.
+hipError_t reduce_parts(const float* part, int splits, int64_t count, float* out, int accumulate, hipStream_t st);
 // in_bn (may be null): x is the raw input of a BN + ReLU whose output is not
 // stored, in_bn its per-channel scale [c] and shift [c] (DirArgs::in_bn);
 // only the direct kernel takes it (conv_fwd_in_bn_ok), otherwise
@@ -337,7 +339,7 @@ hipError_t gavgpool_bwd(int n, int c, int h, int w, const float* dy, float* dx, 
 hipError_t fc_gemm_fwd(int n, int in, int out, const float* x, const float* w, const float* b, int relu, float* y,
                        int bf16, hipStream_t st);
 hipError_t fc_gemm_bwd(int n, int in, int out, const float* x, const float* w, const float* dy, float* dx,
-                       int dx_accumulate, float* dw, float* db, int bf16, hipStream_t st);
+                       int dx_accumulate, float* dw, float* db, int bf16, void* ws, size_t ws_bytes, hipStream_t st);
 hipError_t fc_fwd(int n, int in, int out, const float* x, const float* w, const float* b, int relu, float* y,
                   int bf16, hipStream_t st);
 size_t fc_bwd_ws_bytes(int n, int in, int out);

@@ -1282,7 +1282,7 @@ hipError_t fc_bwd(int n, int in, int out, const float* x, const float* w, const 
                        n, in, out, x, w, dy, dx, dx_accumulate, dw, db, nbx, nbw);
         return hipGetLastError();
     }
-    return fc_gemm_bwd(n, in, out, x, w, dy, dx, dx_accumulate, dw, db, bf16, st);
+    return fc_gemm_bwd(n, in, out, x, w, dy, dx, dx_accumulate, dw, db, bf16, ws, ws_bytes, st);
 }
 
 }  // namespace psw
