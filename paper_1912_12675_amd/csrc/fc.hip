@@ -546,7 +546,8 @@ hipError_t gs_pick(GsArgs a, const Work& wk, float* ws, size_t ws_bytes, hipStre
     }
     // bf16 forward of more than 64 rows whose x is larger than the L2 (see gemm())
     if constexpr (NS == 1 && AK && BK)
-        if (a.M > 64 && a.M <= 256) return gs_launch<NS, 128, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
+        if (a.M > 64 && a.M <= 256 && (int64_t)a.M * a.K * 4 > kRowsL2)
+            return gs_launch<NS, 128, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
     if (blocks(128, 128) >= 512) return gs_launch<NS, 128, 128, 2, 2, 1, 1, AK, BK>(a, wk, st);
     if (tiles >= 128) return gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(a, wk, st);
     if (deep) return gs_launch<NS, 16, 16, 1, 1, 16, 16, AK, BK>(a, wk, st);
@@ -589,13 +590,19 @@ hipError_t gemm(GsArgs a, int bf16, float* ws, size_t ws_bytes, hipStream_t st)
                    dim3((unsigned)(((int64_t)a.M * a.N + 255) / 256)), dim3(256), 0, st, a, bf16);
         return hipGetLastError();
     }
-    // up to 256 rows the weights' traffic and the depth of k decide, not the
-    // matrix rate: gemm_rows.  bf16 with an x past an XCD's 4 MB of L2 (fp32,
-    // re-read by every block of columns) takes the LDS tile of 128 rows
+    // Forward of up to 256 rows: the weights' traffic and the depth of k decide,
+    // not the matrix rate: gemm_rows.  Not over many columns and few k, where
+    // its eight waves a workgroup have a step each or none (us at 128 x 64 ->
+    // 30,000: rows 32.8, tiles 9.0; 256 x 300 -> 4096: 17.5, 11.5; 128 x 300 ->
+    // 4096, 128 tiles: 9.4, 11.2).  bf16 with an x past an XCD's 4 MB of L2
+    // (fp32, re-read by every block of columns) takes the LDS tile of 128 rows
     // (16384 -> 4096, 128 rows: 184 against 192; 9216, 100 rows: 104 and 78)
-    if constexpr (AK && BK)
-        if (a.M <= (bf16 && a.N >= 1024 && (int64_t)a.M * a.K * 4 > kRowsL2 ? 64 : 256) && !a.accumulate)
+    if constexpr (AK && BK) {
+        const bool tiles = a.M > 32 && a.K <= 1024 && (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 256;
+        const bool past = bf16 && a.N >= 1024 && a.M > 64 && (int64_t)a.M * a.K * 4 > kRowsL2;
+        if (a.M <= 256 && !tiles && !past)
             return bf16 ? rows_pick<true>(a, wk, st) : rows_pick<false>(a, wk, st);
+    }
     return bf16 ? gs_pick<1, AK, BK>(a, wk, ws, ws_bytes, st) : gs_pick<3, AK, BK>(a, wk, ws, ws_bytes, st);
 }
 

@@ -199,6 +199,7 @@ FC = [
     (128, 5000, 300),
     (300, 200, 1100),    # tiles of 128 x 128 in the weight gradient
     (128, 96, 16400),
+    (33, 70, 16400),     # few k over many columns: 64 x 64 tiles in the forward
     (20, 70, 9000),      # the input's gradient over a deep k, in parts whose sums meet: few tiles
     (130, 1100, 2100),   # ... more of them
     (128, 4100, 530),    # ... 130 of 64 x 64, the last part short
