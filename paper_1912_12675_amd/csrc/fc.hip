@@ -75,7 +75,7 @@ __device__ __forceinline__ void load_k8(Buffer b, int off, int ld, bool whole, i
     }
 }
 
-template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK>
+template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK, bool FAR>
 __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void gemm_split(GsArgs a)
 {
     constexpr int NT = 64 * WM * WN * WK, KU = 4 * KG, ROW = KU + 1;  // units per row; odd row of units
@@ -110,10 +110,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
     auto load_op = [&](auto kc, const float* p, int ld, int rows, int r0, int row, bool in, int o, int k0, bool whole,
                        float(&r)[8]) {
         constexpr bool KC = decltype(kc)::value;
-        const Buffer b = KC ? make_buffer(p + (int64_t)r0 * ld + k0, ((int64_t)(rows - r0) * ld - k0) * 4)
-                            : make_buffer(p + (int64_t)k0 * ld + r0, ((int64_t)(a.K - k0) * ld - r0) * 4);
-        load_k8<KC>(b, in ? (KC ? row * ld + o * 8 : row + o * 8 * ld) * 4 : kOutside, ld, whole, kend - k0 - o * 8,
-                    r);
+        if constexpr (FAR) {
+            const float* q = KC ? p + (int64_t)(r0 + row) * ld : p + r0 + row;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = k0 + o * 8 + e;
+                const bool ok = in && k < kend;
+                const float v = *(ok ? q + (KC ? (int64_t)k : (int64_t)k * ld) : p);
+                r[e] = ok ? v : 0.f;
+            }
+        } else {
+            const Buffer b = KC ? make_buffer(p + (int64_t)r0 * ld + k0, ((int64_t)(rows - r0) * ld - k0) * 4)
+                                : make_buffer(p + (int64_t)k0 * ld + r0, ((int64_t)(a.K - k0) * ld - r0) * 4);
+            load_k8<KC>(b, in ? (KC ? row * ld + o * 8 : row + o * 8 * ld) * 4 : kOutside, ld, whole, kend - k0 - o * 8,
+                        r);
+        }
     };
     auto load = [&](int k0) {
         const bool whole = k0 + 8 * KU <= kend;
@@ -469,29 +480,7 @@ __global__ __launch_bounds__(256) void col_sum_k(int rows, int cols, const float
         out[c] = (float)(((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x]);
 }
 
-// one output per thread, for row strides past the descriptors' 31-bit offsets
-template <bool AK, bool BK>
-__global__ void gemm_plain(GsArgs a, int bf16)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)a.M * a.N) return;
-    const int m = (int)(i / a.N), n = (int)(i - (int64_t)m * a.N);
-    float v = 0.f;
-    for (int k = 0; k < a.K; ++k) {
-        float p = AK ? a.A[(int64_t)m * a.lda + k] : a.A[(int64_t)k * a.lda + m];
-        float q = BK ? a.B[(int64_t)n * a.ldb + k] : a.B[(int64_t)k * a.ldb + n];
-        if (bf16) {
-            p = (float)(__bf16)p;
-            q = (float)(__bf16)q;
-        }
-        v = fmaf(p, q, v);
-    }
-    if (a.bias) v += a.bias[n];
-    if (a.relu) v = fmaxf(v, 0.f);
-    a.C[i] = a.accumulate ? a.C[i] + v : v;
-}
-
-template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK>
+template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK, bool FAR = false>
 hipError_t gs_launch(GsArgs a, const Work& wk, hipStream_t st, int parts = 1)
 {
     a.mblocks = (a.M + BM - 1) / BM;
@@ -500,8 +489,8 @@ hipError_t gs_launch(GsArgs a, const Work& wk, hipStream_t st, int parts = 1)
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     if (parts == 1) a.kchunk = INT32_MAX / (32 * KG) * (32 * KG);
     constexpr size_t main = (size_t)NS * 16 * (BM + BN) * (4 * KG + 1), red = (size_t)(WK - 1) * BM * BN * 4;
-    PSW_LAUNCH(kname("gemm_split", NS, BM, BN, WM, WN, WK, KG, AK, BK), wk,
-               (gemm_split<NS, BM, BN, WM, WN, WK, KG, AK, BK>), dim3((unsigned)blocks, (unsigned)parts),
+    PSW_LAUNCH(kname("gemm_split", NS, BM, BN, WM, WN, WK, KG, AK, BK, FAR), wk,
+               (gemm_split<NS, BM, BN, WM, WN, WK, KG, AK, BK, FAR>), dim3((unsigned)blocks, (unsigned)parts),
                dim3(64 * WM * WN * WK), main > red ? main : red, st, a);
     return hipGetLastError();
 }
@@ -531,18 +520,27 @@ template <int NS, bool AK, bool BK>
 hipError_t gs_pick(GsArgs a, const Work& wk, float* ws, size_t ws_bytes, hipStream_t st)
 {
     auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    const int64_t ld = std::max(a.lda, a.ldb);
+    // a descriptor's lane offsets are 31 bits: 512 k of a row-contiguous operand
+    // or 128 rows of another are the most of any tile here, 64 of either the
+    // most of the 64 x 64 tile; past that, plain loads
+    const bool near = ld * 512 * 4 <= INT32_MAX, far = ld * 64 * 4 > INT32_MAX;
     const int64_t tiles = blocks(64, 64);
     const bool deep = a.K > 512 && blocks(16, 16) <= 256;
-    const int waves = tiles >= 128 ? 1 : deep ? 16 : 4;
+    const int waves = !near || tiles >= 128 ? 1 : deep ? 16 : 4;
     const int parts = ws ? gs_parts(a, tiles, waves, NS == 1, ws_bytes, &a.kchunk) : 1;
-    if (parts > 1) {
+    if (parts > 1 || !near) {
         GsArgs p = a;
-        p.C = ws;
-        p.part = (int64_t)a.M * a.N;
-        p.vec = a.N % 4 == 0 && (uintptr_t)ws % 16 == 0;
-        p.accumulate = 0;
-        const hipError_t e = gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(p, wk, st, parts);
-        return e != hipSuccess ? e : reduce_parts(ws, parts, p.part, a.C, a.accumulate, st);
+        if (parts > 1) {
+            p.C = ws;
+            p.part = (int64_t)a.M * a.N;
+            p.vec = a.N % 4 == 0 && (uintptr_t)ws % 16 == 0;
+            p.accumulate = 0;
+        }
+        const hipError_t e = far ? gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK, true>(p, wk, st, parts)
+                                 : gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(p, wk, st, parts);
+        if (e != hipSuccess || parts == 1) return e;
+        return reduce_parts(ws, parts, p.part, a.C, a.accumulate, st);
     }
     // bf16 forward of more than 64 rows whose x is larger than the L2 (see gemm())
     if constexpr (NS == 1 && AK && BK)
@@ -565,15 +563,15 @@ hipError_t rows_launch(const GsArgs& a, const Work& wk, hipStream_t st)
 }
 
 template <bool BF>
-hipError_t rows_pick(const GsArgs& a, const Work& wk, hipStream_t st)
+hipError_t rows_pick(const GsArgs& a, int64_t most, const Work& wk, hipStream_t st)
 {
     // the most rows per workgroup that still leave a workgroup for every
     // other CU (the columns' operands are then read once or twice); else 16
     // rows and 16 waves on the depth of k
     const int64_t cols = (a.N + 15) / 16;
-    if (a.M > 64 && cols * ((a.M + 127) / 128) >= 128) return rows_launch<BF, 8, 8>(a, wk, st);
-    if (a.M > 32 && cols * ((a.M + 63) / 64) >= 128) return rows_launch<BF, 4, 8>(a, wk, st);
-    if (a.M > 16 && cols * ((a.M + 31) / 32) >= 128) return rows_launch<BF, 2, 8>(a, wk, st);
+    if (most >= 8 && a.M > 64 && cols * ((a.M + 127) / 128) >= 128) return rows_launch<BF, 8, 8>(a, wk, st);
+    if (most >= 4 && a.M > 32 && cols * ((a.M + 63) / 64) >= 128) return rows_launch<BF, 4, 8>(a, wk, st);
+    if (most >= 2 && a.M > 16 && cols * ((a.M + 31) / 32) >= 128) return rows_launch<BF, 2, 8>(a, wk, st);
     return a.K > 512 ? rows_launch<BF, 1, 16>(a, wk, st) : rows_launch<BF, 1, 4>(a, wk, st);
 }
 
@@ -583,13 +581,6 @@ hipError_t gemm(GsArgs a, int bf16, float* ws, size_t ws_bytes, hipStream_t st)
     const Work wk{2.0 * a.M * a.N * (double)a.K,
                   kF * ((double)a.M * a.K + (double)a.K * a.N + (1.0 + a.accumulate) * a.M * (double)a.N)};
     a.vec = a.N % 4 == 0 && (uintptr_t)a.C % 16 == 0;
-    // lane offsets within a tile (128 rows, or 512 k of a row-contiguous
-    // operand) are 31 bits
-    if ((int64_t)std::max(a.lda, a.ldb) * 512 * 4 > INT32_MAX) {
-        PSW_LAUNCH(kname("gemm_plain", AK, BK), wk, (gemm_plain<AK, BK>),
-                   dim3((unsigned)(((int64_t)a.M * a.N + 255) / 256)), dim3(256), 0, st, a, bf16);
-        return hipGetLastError();
-    }
     // Forward of up to 256 rows: the weights' traffic and the depth of k decide,
     // not the matrix rate: gemm_rows.  Not over many columns and few k, where
     // its eight waves a workgroup have a step each or none (us at 128 x 64 ->
@@ -598,10 +589,11 @@ hipError_t gemm(GsArgs a, int bf16, float* ws, size_t ws_bytes, hipStream_t st)
     // (fp32, re-read by every block of columns) takes the LDS tile of 128 rows
     // (16384 -> 4096, 128 rows: 184 against 192; 9216, 100 rows: 104 and 78)
     if constexpr (AK && BK) {
+        const int64_t most = INT32_MAX / 64 / std::max(a.lda, a.ldb);  // blocks of 16 rows in 31 bits
         const bool tiles = a.M > 32 && a.K <= 1024 && (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 256;
         const bool past = bf16 && a.N >= 1024 && a.M > 64 && (int64_t)a.M * a.K * 4 > kRowsL2;
-        if (a.M <= 256 && !tiles && !past)
-            return bf16 ? rows_pick<true>(a, wk, st) : rows_pick<false>(a, wk, st);
+        if (most >= 1 && a.M <= 256 && !tiles && !past)
+            return bf16 ? rows_pick<true>(a, most, wk, st) : rows_pick<false>(a, most, wk, st);
     }
     return bf16 ? gs_pick<1, AK, BK>(a, wk, ws, ws_bytes, st) : gs_pick<3, AK, BK>(a, wk, ws, ws_bytes, st);
 }

@@ -6,7 +6,8 @@ backward pass, planes smaller than a tile, and operands that are not finite.
 Bound: both sides form the same fp32 (or bf16-rounded) products; the GPU adds
 them in fp32, so the error of a sum of L products is at most L 2^-24 of the
 sum of their magnitudes and typically sqrt(L) 2^-24 of their root mean square:
-2e-5 of the largest result covers every L here (at most 12,800)."""
+2e-5 of the largest result covers every L here (at most 12,800; one sum of
+1,048,600 is formed in parts of at most 1,088)."""
 import math
 
 import numpy as np
@@ -203,6 +204,7 @@ FC = [
     (20, 70, 9000),      # the input's gradient over a deep k, in parts whose sums meet: few tiles
     (130, 1100, 2100),   # ... more of them
     (128, 4100, 530),    # ... 130 of 64 x 64, the last part short
+    (3, 5, 1048600),     # rows past the larger tiles' 31-bit offsets
 ]
 
 
@@ -234,6 +236,40 @@ def test_fc_edges(P, case, bf16):
     dx = dev(base)
     P.psw_fc_bwd(dev(x), dev(w), dev(dy), dw, dx=dx, dx_accumulate=True, bf16=bf16)
     close(dx, refdx + base, "dx accumulate")
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("case", [(1, 33554500, 2), (2, 8388700, 3), (2, 3, 8388700)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_fc_rows_past_31_bits(P, case, bf16):
+    """Rows whose byte offsets pass 31 bits within a tile.  x, w and dy hold 200 values each among zeros (the
+    first and last elements among them), so every sum is short and the same bound holds."""
+    print("fc far", case, bf16, flush=True)
+    n, fin, out = case
+    g = torch.Generator().manual_seed(fin + out)
+
+    def sparse(rows, cols):
+        t = torch.zeros(rows * cols, device="cuda")
+        at = torch.randint(t.numel(), (200,), generator=g)
+        at[0], at[1] = 0, t.numel() - 1
+        at[2:100] = torch.randint(max(0, cols - 60), cols, (98,), generator=g) + cols * torch.randint(rows, (98,), generator=g)
+        t[at.cuda()] = torch.randn(200, generator=g).cuda()
+        return t.view(rows, cols)
+
+    x, w, dy = sparse(n, fin), sparse(out, fin), sparse(n, out)
+    rd = lambda a: (a.bfloat16() if bf16 else a).double()  # noqa: E731
+    outer = lambda a, b: sum(a[:, k, None] * b[None, k] for k in range(a.shape[1]))  # noqa: E731
+    y, dx, dw, db = (torch.full(s, 7.0, device="cuda") for s in (dy.shape, x.shape, w.shape, (out,)))
+    P.psw_fc_fwd(x, w, y, bf16=bf16)
+    P.psw_fc_bwd(x, w, dy, dw, dx=dx, db=db, bf16=bf16)
+
+    def same(got, want):  # on the GPU: the tensors are large
+        assert got.shape == want.shape and bool((got.double() - want).abs().max() <= TOL * want.abs().max())
+
+    same(y, torch.stack([(rd(x[i]) * rd(w)).sum(1) for i in range(n)]))
+    same(dx, torch.stack([(rd(dy[i])[:, None] * rd(w)).sum(0) for i in range(n)]))
+    same(dw, outer(rd(dy).t(), rd(x)))
+    same(db, dy.double().sum(0))
 
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
