@@ -480,6 +480,52 @@ __global__ __launch_bounds__(256) void col_sum_k(int rows, int cols, const float
         out[c] = (float)(((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x]);
 }
 
+// Backward products of few rows, few k and many columns (classifiers of a
+// handful of samples over a wide input): V columns a thread, MR rows in
+// registers, A by uniform loads, k in order.  A row of B is read once and
+// memory is the bound; the 64 x 64 tile spends its time on padding (fp32, dx and
+// dw, us: 4 samples 1,200,000 -> 10 229, 8 samples 60,000 -> 10 17.4).
+template <int NS, int MR, int V, bool AK>
+__global__ __launch_bounds__(256) void gemm_thin(GsArgs a)
+{
+    typedef float fv __attribute__((ext_vector_type(V)));
+    const int64_t n = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
+    if (n >= a.N) return;
+    const int m0 = (int)blockIdx.y * MR;
+    fv acc[MR];
+#pragma unroll
+    for (int m = 0; m < MR; ++m) acc[m] = 0.f;
+    auto step = [&](int k, fv b) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) b[e] = operand<NS>(b[e]);
+#pragma unroll
+        for (int m = 0; m < MR; ++m) {
+            const int row = min(m0 + m, a.M - 1);
+            const float v = operand<NS>(AK ? a.A[(int64_t)row * a.lda + k] : a.A[(int64_t)k * a.lda + row]);
+#pragma unroll
+            for (int e = 0; e < V; ++e) acc[m][e] = fmaf(v, b[e], acc[m][e]);
+        }
+    };
+    auto row_of_b = [&](int k) { return *reinterpret_cast<const fv*>(a.B + (int64_t)k * a.ldb + n); };
+    constexpr int U = 4;  // rows of B in flight
+    int k = 0;
+    for (; k + U <= a.K; k += U) {
+        fv b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) b[u] = row_of_b(k + u);
+#pragma unroll
+        for (int u = 0; u < U; ++u) step(k + u, b[u]);
+    }
+    for (; k < a.K; ++k) step(k, row_of_b(k));
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+        if (m0 + m >= a.M) break;
+        fv* dst = reinterpret_cast<fv*>(a.C + (int64_t)(m0 + m) * a.N + n);
+        if (a.accumulate) acc[m] = *dst + acc[m];
+        __builtin_nontemporal_store(acc[m], dst);
+    }
+}
+
 template <int NS, int BM, int BN, int WM, int WN, int WK, int KG, bool AK, bool BK, bool FAR = false>
 hipError_t gs_launch(GsArgs a, const Work& wk, hipStream_t st, int parts = 1)
 {
@@ -553,6 +599,19 @@ hipError_t gs_pick(GsArgs a, const Work& wk, float* ws, size_t ws_bytes, hipStre
     return gs_launch<NS, 16, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
 }
 
+template <int NS, int MR, bool AK>
+hipError_t thin_launch(const GsArgs& a, const Work& wk, hipStream_t st)
+{
+    const unsigned rows = (unsigned)((a.M + MR - 1) / MR);
+    if (a.vec && (uintptr_t)a.B % 16 == 0 && a.N >= 1 << 18)
+        PSW_LAUNCH(kname("gemm_thin", NS, MR, 4, AK), wk, (gemm_thin<NS, MR, 4, AK>), dim3((unsigned)((a.N + 1023) / 1024), rows),
+                   dim3(256), 0, st, a);
+    else
+        PSW_LAUNCH(kname("gemm_thin", NS, MR, 1, AK), wk, (gemm_thin<NS, MR, 1, AK>), dim3((unsigned)((a.N + 255) / 256), rows),
+                   dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 template <bool BF, int MT, int WK>
 hipError_t rows_launch(const GsArgs& a, const Work& wk, hipStream_t st)
 {
@@ -595,6 +654,11 @@ hipError_t gemm(GsArgs a, int bf16, float* ws, size_t ws_bytes, hipStream_t st)
         if (most >= 1 && a.M <= 256 && !tiles && !past)
             return bf16 ? rows_pick<true>(a, most, wk, st) : rows_pick<false>(a, most, wk, st);
     }
+    if constexpr (!BK)  // columns enough for a workgroup of one each on half the CUs
+        if (a.M <= 32 && a.K <= 128 && a.N >= 1 << 15) {
+            if (a.M <= 4) return bf16 ? thin_launch<1, 4, AK>(a, wk, st) : thin_launch<3, 4, AK>(a, wk, st);
+            return bf16 ? thin_launch<1, 16, AK>(a, wk, st) : thin_launch<3, 16, AK>(a, wk, st);
+        }
     return bf16 ? gs_pick<1, AK, BK>(a, wk, ws, ws_bytes, st) : gs_pick<3, AK, BK>(a, wk, ws, ws_bytes, st);
 }
 

@@ -204,6 +204,8 @@ FC = [
     (20, 70, 9000),      # the input's gradient over a deep k, in parts whose sums meet: few tiles
     (130, 1100, 2100),   # ... more of them
     (128, 4100, 530),    # ... 130 of 64 x 64, the last part short
+    (5, 33001, 20),      # few rows, few k, many columns: one a thread
+    (3, 262148, 17),     # ... four a thread, a second block of rows in dw
     (3, 5, 1048600),     # rows past the larger tiles' 31-bit offsets
 ]
 
