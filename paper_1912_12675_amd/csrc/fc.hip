@@ -230,17 +230,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
     }
 
     const int mrow = m0 + wm * MT * 16 + j, ncol = n0 + wn * NTL * 16 + 4 * g;
+    bool some = false;
     if constexpr (NS == 3) {
-        // sums that came out as NaN (an infinity or NaN among their operands):
-        // again in plain fp32; left alone below
-        float t = 0.f;
+        // sums to form again (split.h); left alone below
+        Again redo;
 #pragma unroll
         for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) t = fmaf(acc[nt][mt][i], 0.f, t);
-        if (t != t) {
+            for (int mt = 0; mt < MT; ++mt) redo.add<NS>(acc[nt][mt]);
+        some = redo.any();
+        if (some) {
             uint64_t bad = 0;
             static_assert(MT * NTL * 4 <= 64, "one bit per sum");
 #pragma unroll
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
                 for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        bad |= (uint64_t)(acc[nt][mt][i] != acc[nt][mt][i]) << ((nt * MT + mt) * 4 + i);
+                        bad |= (uint64_t)again<NS>(acc[nt][mt][i]) << ((nt * MT + mt) * 4 + i);
 #pragma unroll 1
             for (; bad; bad &= bad - 1) {
                 const int q = __ffsll((unsigned long long)bad) - 1;
@@ -272,8 +271,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
             const int n = ncol + nt * 16;
             float* dst = C + (int64_t)m * a.N + n;
             sp_v4f v = acc[nt][mt];
-            const bool fine = NS != 3 || (v[0] == v[0] && v[1] == v[1] && v[2] == v[2] && v[3] == v[3]);
-            if (a.vec && n + 4 <= a.N && fine) {
+            if (a.vec && n + 4 <= a.N && !some) {
                 if (a.bias) v += sp_v4f{a.bias[n], a.bias[n + 1], a.bias[n + 2], a.bias[n + 3]};
                 if (a.relu)
 #pragma unroll
@@ -284,7 +282,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     float s = v[i];
-                    if (n + i >= a.N || (NS == 3 && s != s)) continue;
+                    if (n + i >= a.N || (some && again<NS>(s))) continue;
                     if (a.bias) s += a.bias[n + i];
                     if (a.relu) s = fmaxf(s, 0.f);
                     dst[i] = a.accumulate ? dst[i] + s : s;

@@ -65,8 +65,7 @@ __host__ __device__ inline Taps class_taps(int R, int pad, int os, int bwd, int 
 }
 
 // one output in plain fp32, in the order of the definition (zero outside the
-// input): the value wherever the matrix products give NaN.  A sum that has
-// become NaN stays one, so it ends there.
+// input).  A sum that has become NaN stays one, so it ends there.
 template <int NS>
 __device__ __forceinline__ float plain_sum(const GcArgs& a, int img, int m, int oh, int ow)
 {
@@ -344,39 +343,35 @@ __global__ __launch_bounds__(64 * WP * WK, NS == 3 && BM == 32 && BP == 256 && !
         *q = Pos{img0 + (p >> (a.lw + a.lh)), gi * a.os + ph, gj * a.os + pw};
         return gi < GH && gj < GW && q->img < a.n;
     };
-    {
-        // sums that came out as NaN (an infinity or NaN among their operands,
-        // or at the place that a group's unused slots read) are formed again
-        // in plain fp32 and stored here; the loop below leaves them alone
-        float t = 0.f;
+    Again redo;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NTL; ++nt) redo.add<NS>(acc[mt][nt]);
+    const bool some = redo.any();
+    // these sums are formed again (split.h; a group's unused slots read a
+    // real pixel) and stored here; the loop below leaves them alone
+    if (some) {
+        uint64_t bad = 0;
+        static_assert(MT * NTL * 4 <= 64, "one bit per sum");
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) t = fmaf(acc[mt][nt][i], 0.f, t);
-        if (t != t) {
-            uint64_t bad = 0;
-            static_assert(MT * NTL * 4 <= 64, "one bit per sum");
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        bad |= (uint64_t)(acc[mt][nt][i] != acc[mt][nt][i]) << ((mt * NTL + nt) * 4 + i);
+                for (int i = 0; i < 4; ++i)
+                    bad |= (uint64_t)again<NS>(acc[mt][nt][i]) << ((mt * NTL + nt) * 4 + i);
 #pragma unroll 1
-            for (; bad; bad &= bad - 1) {
-                const int k = __ffsll((unsigned long long)bad) - 1;
-                const int m = m0 + (k >> 2) / NTL * 16 + 4 * g + (k & 3);
-                Pos q;
-                if (!pos_at((wp * NTL + (k >> 2) % NTL) * 16 + j, &q) || m >= a.M) continue;
-                float v = plain_sum<NS>(a, q.img, m, q.oh, q.ow);
-                float* dst = a.y + ((q.img * a.M + m) * a.OH + q.oh) * a.OW + q.ow;
-                if (a.bias) v += a.bias[m];
-                if (a.relu) v = fmaxf(v, 0.f);
-                *dst = a.accumulate ? *dst + v : v;
-            }
+        for (; bad; bad &= bad - 1) {
+            const int k = __ffsll((unsigned long long)bad) - 1;
+            const int m = m0 + (k >> 2) / NTL * 16 + 4 * g + (k & 3);
+            Pos q;
+            if (!pos_at((wp * NTL + (k >> 2) % NTL) * 16 + j, &q) || m >= a.M) continue;
+            float v = plain_sum<NS>(a, q.img, m, q.oh, q.ow);
+            float* dst = a.y + ((q.img * a.M + m) * a.OH + q.oh) * a.OW + q.ow;
+            if (a.bias) v += a.bias[m];
+            if (a.relu) v = fmaxf(v, 0.f);
+            *dst = a.accumulate ? *dst + v : v;
         }
     }
 #pragma unroll
@@ -397,7 +392,7 @@ __global__ __launch_bounds__(64 * WP * WK, NS == 3 && BM == 32 && BP == 256 && !
             for (int i = 0; i < 4; ++i) {
                 const int m = m0 + mt * 16 + 4 * g + i;
                 float v = acc[mt][nt][i];
-                if (m >= a.M || v != v) continue;
+                if (m >= a.M || (some && again<NS>(v))) continue;
                 if (a.bias) v += a.bias[m];
                 if (a.relu) v = fmaxf(v, 0.f);
                 if (a.accumulate) v += old[mt][i];

@@ -249,45 +249,40 @@ __global__ __launch_bounds__(256, 2) void conv_split_wgrad(GwArgs a)
                         if (RG == 1 || r0 + r < a.R) o[r * S + s] = acc[mt][(ct * RG + r) * S + s][i];
             }
         }
-    {
-        // sums that came out as NaN (an infinity or NaN among their operands,
-        // or where a chunk reaches past dy's plane and its zeros meet x) are
-        // formed again in plain fp32; one that has become NaN stays so
-        float t = 0.f;
+    // sums to form again (split.h; where a chunk reaches past dy's plane its
+    // zeros meet x); one that has become NaN stays so
+    Again redo;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int q = 0; q < TAPS; ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) t = fmaf(acc[mt][q][i], 0.f, t);
-        if (t != t) {
+        for (int q = 0; q < TAPS; ++q) redo.add<NS>(acc[mt][q]);
+    if (redo.any()) {
 #pragma unroll 1
-            for (int q = 0; q < MT * TAPS * 4; ++q) {
-                const int i = q & 3, tt = (q >> 2) % TAPS, mt = (q >> 2) / TAPS;
-                const int k = k0 + (wm * MT + mt) * 16 + 4 * g + i, c = c0 + tt / (RG * S) * 16 + j;
-                const int r = r0 + tt / S % RG, s = tt % S;
-                if (k >= a.K || c >= a.C || r >= a.R) continue;
-                float* o = out + (((size_t)k * a.C + c) * a.R + r) * S + s;
-                if (*o == *o) continue;
-                float v = 0.f;
-                for (int ch = ch_begin; ch < ch_end && v == v; ++ch) {
-                    int oct, p0, q0;
-                    chunk_at(ch, &oct, &p0, &q0);
-                    for (int u = 0; u < PX; ++u) {
-                        const int qq = q0 + (u & (TW - 1)), pp = p0 + ((u >> a.lw) & (TH - 1));
-                        const int ih = pp * a.st + r - a.pad, iw = qq * a.st + s - a.pad;
-                        const bool in = ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
-                        if (pp >= a.P || qq >= a.Q) continue;
-                        for (int e = 0; e < 8; ++e) {
-                            const int img = (oct + (u >> (a.lw + a.lh))) * 8 + e;
-                            if (img >= a.n) break;
-                            const float xv = in ? a.x[((img * a.C + c) * a.H + ih) * a.W + iw] : 0.f;
-                            v = fmaf(operand<NS>(a.dy[(img * a.K + k) * PQ + pp * a.Q + qq]), operand<NS>(xv), v);
-                        }
+        for (int q = 0; q < MT * TAPS * 4; ++q) {
+            const int i = q & 3, tt = (q >> 2) % TAPS, mt = (q >> 2) / TAPS;
+            const int k = k0 + (wm * MT + mt) * 16 + 4 * g + i, c = c0 + tt / (RG * S) * 16 + j;
+            const int r = r0 + tt / S % RG, s = tt % S;
+            if (k >= a.K || c >= a.C || r >= a.R) continue;
+            float* o = out + (((size_t)k * a.C + c) * a.R + r) * S + s;
+            if (!again<NS>(*o)) continue;
+            float v = 0.f;
+            for (int ch = ch_begin; ch < ch_end && v == v; ++ch) {
+                int oct, p0, q0;
+                chunk_at(ch, &oct, &p0, &q0);
+                for (int u = 0; u < PX; ++u) {
+                    const int qq = q0 + (u & (TW - 1)), pp = p0 + ((u >> a.lw) & (TH - 1));
+                    const int ih = pp * a.st + r - a.pad, iw = qq * a.st + s - a.pad;
+                    const bool in = ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
+                    if (pp >= a.P || qq >= a.Q) continue;
+                    for (int e = 0; e < 8; ++e) {
+                        const int img = (oct + (u >> (a.lw + a.lh))) * 8 + e;
+                        if (img >= a.n) break;
+                        const float xv = in ? a.x[((img * a.C + c) * a.H + ih) * a.W + iw] : 0.f;
+                        v = fmaf(operand<NS>(a.dy[(img * a.K + k) * PQ + pp * a.Q + qq]), operand<NS>(xv), v);
                     }
                 }
-                *o = v;
             }
+            *o = v;
         }
     }
 }

@@ -10,9 +10,15 @@
 // same product (2.5 PFLOP/s against 157 TFLOP/s).  The error against 64 bits
 // is a third to a half of the fp32 instructions' (256 -> 256 3x3 at 14x14: 2.6e-7
 // against 5.9e-7), since the small products are summed apart (mfma_split).
-// The split of an infinity, a NaN or a float that rounds to infinity in
-// bfloat16 holds a NaN, so every sum such an operand enters comes out as
-// NaN; the kernels form those sums again in plain fp32 (their epilogues).
+// Where a sum of parts is not the sum of the operands it is formed again in
+// plain fp32 by the kernels' epilogues (`again`):
+//  - it is not finite: the split of an infinity, a NaN or a float that rounds
+//    to infinity in bfloat16 holds a NaN, and a product of two parts rounded up
+//    can pass the largest float where the operands' product does not;
+//  - it is below 2^-100: an operand's third part is exact down to bfloat16's
+//    smallest number, 2^-133, so of operands below 2^-110 low bits are lost, by
+//    at most 2^-134 each.  A sum of at least 2^-100 does not see that, and one
+//    of a training step never gets there.
 //
 // bf16 mode is the same with the first part only: operands rounded to
 // nearest even, one product.  The kernels pad a block's products with zeros
@@ -40,6 +46,30 @@ __device__ __forceinline__ float operand(float v)
 {
     return NS == 1 ? (float)(__bf16)v : v;
 }
+
+// The sums to form again: for single ones, and whether there are any.
+template <int NS>
+__device__ __forceinline__ bool again(float v)
+{
+    if constexpr (NS == 1) return v != v;
+    // the bits without the sign, from infinity's up and round to zero's and on to 2^-100's
+    const uint32_t u = (__float_as_uint(v) << 1) - 0xff000000u;
+    return u < 0x01000000u + (27u << 24) && u != 0x01000000u;
+}
+struct Again {
+    float t = 0.f;              // NaN once a sum was not finite
+    uint32_t least = ~0u;       // the smallest sum that is not zero: twice its bits, less one
+    template <int NS>
+    __device__ __forceinline__ void add(const sp_v4f& v)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            t = fmaf(v[i], 0.f, t);
+            if (NS == 3) least = min(least, (__float_as_uint(v[i]) << 1) - 1u);
+        }
+    }
+    __device__ __forceinline__ bool any() const { return t != t || least < (27u << 24) - 1u; }
+};
 
 // parts[0] = h, parts[1] = m, parts[2] = l of eight floats (NS = 1: h alone)
 template <int NS>

@@ -141,16 +141,16 @@ def test_conv_not_finite(P, case, bf16):
 
 
 def fp32_error(L):
-    """Relative error (2-norm) of a sum of L products of zero mean that an fp32 matrix instruction forms, four
-    products to a rounding: each rounding errs 2.5e-8 of the running sum (half an ulp, uniform), whose square
-    grows with its length, so sqrt(L / 4 / 2) of those; and the result's own rounding."""
+    """Relative error (2-norm) of a sum of L products of zero mean with a rounding every four: each rounding errs
+    2.5e-8 of the running sum (half an ulp, uniform), whose square grows with its length, so sqrt(L / 4 / 2) of
+    those, and the result's own.  The fp32 matrix instructions round at each product: twice that."""
     return 2.5e-8 * (math.sqrt(L / 8) + 1)
 
 
 @pytest.mark.parametrize("case", [(64, 256, 14, 14, 256, 3, 3, 1, 1), (16, 1, 28, 28, 6, 5, 5, 1, 2),
                                   (64, 128, 16, 16, 192, 1, 1, 1, 0)], ids=lambda c: "x".join(map(str, c)))
 def test_conv_error_is_fp32s(P, case):
-    """Products in three bfloat16 parts: no further from 64 bits than the fp32 matrix instructions' sums."""
+    """Products in three bfloat16 parts: nearer to 64 bits than the fp32 matrix instructions' sums."""
     print("conv error", case, flush=True)
     N, C, H, W, K, R, S, st, pad = case
     g = torch.Generator(device="cuda").manual_seed(5)
@@ -179,6 +179,54 @@ def test_fc_error_is_fp32s(P, case):
     for got, want, L in ((y, x.double() @ w.double().t(), fin), (dx, dy.double() @ w.double(), out),
                          (dw, dy.double().t() @ x.double(), n)):
         assert float((got - want).norm() / want.norm()) <= fp32_error(L)
+
+
+@pytest.mark.parametrize("scale", [1e-28, 1e-33, 1e-36])
+def test_tiny_operands(P, scale):
+    """Operands whose third bfloat16 part is at or past that format's smallest number: still fp32's error (twice
+    that of a rounding every four products, since these sums are formed one product at a time)."""
+    print("tiny", scale, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    x, w, dy = rnd(9, 40, 12, 12), rnd(70, 40, 3, 3) * 0.1, rnd(9, 70, 10, 10)
+    cols = lambda t: torch.nn.functional.unfold(t.double(), 3)  # noqa: E731
+    err = lambda got, want: float((got - want).norm() / want.norm())  # noqa: E731
+    y, dx, dw = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w)
+    P.psw_conv_fwd(x * scale, w, y, 1, 0)
+    assert err(y.view(9, 70, -1), w.double().view(70, -1) @ cols(x * scale)) <= 2 * fp32_error(360)
+    P.psw_conv_bwd_weight(x * scale, dy, dw, 1, 0)
+    want = (dy.double().view(9, 70, -1) @ cols(x * scale).transpose(1, 2).contiguous()).sum(0).view(w.shape)
+    assert err(dw, want) <= 2 * fp32_error(900)
+    P.psw_conv_bwd_data(x.shape, w, dy * scale, dx, 1, 0)
+    back = w.double().view(70, -1).t().contiguous() @ (dy * scale).double().view(9, 70, -1)
+    assert err(dx, torch.nn.functional.fold(back, (12, 12), 3)) <= 2 * fp32_error(630)
+    fx, fw, fdy = rnd(300, 700), rnd(200, 700) * 0.1, rnd(300, 200)
+    y, dx, dw = torch.empty_like(fdy), torch.empty_like(fx), torch.empty_like(fw)
+    P.psw_fc_fwd(fx * scale, fw, y)
+    assert err(y, (fx * scale).double() @ fw.double().t()) <= 2 * fp32_error(700)
+    P.psw_fc_bwd(fx, fw, fdy * scale, dw, dx=dx)
+    assert err(dx, (fdy * scale).double() @ fw.double()) <= 2 * fp32_error(200)
+    assert err(dw, (fdy * scale).double().t() @ fx.double()) <= 2 * fp32_error(300)
+
+
+def test_products_near_the_largest_float(P):
+    """3.3895e38 * 1.00391 is a float; the product of the two rounded to bfloat16 is not."""
+    big, f = 3.3895e38, 1.00391
+    x, w = torch.zeros(2, 12, 5, 5), torch.full((20, 12, 1, 1), f)
+    x[1, 3, 2, 2] = big
+    y = torch.empty(2, 20, 5, 5, device="cuda")
+    P.psw_conv_fwd(x.cuda(), w.cuda(), y, 1, 0)
+    want = torch.zeros(2, 20, 5, 5)
+    want[1, :, 2, 2] = x[1, 3, 2, 2] * w[0, 0, 0, 0]
+    assert want.isfinite().all() and torch.allclose(y.cpu(), want, rtol=1e-6, atol=0)
+    dy, dw = torch.zeros(2, 20, 5, 5), torch.empty(20, 12, 1, 1, device="cuda")
+    dy[1, 4, 2, 2] = f
+    P.psw_conv_bwd_weight(x.cuda(), dy.cuda(), dw, 1, 0)
+    assert torch.allclose(dw.cpu()[4, 3, 0, 0], want[1, 0, 2, 2], rtol=1e-6) and dw.isfinite().all()
+    fx, fw, fy = torch.zeros(300, 40), torch.full((70, 40), f), torch.empty(300, 70, device="cuda")
+    fx[7, 9] = big
+    P.psw_fc_fwd(fx.cuda(), fw.cuda(), fy)
+    assert torch.allclose(fy.cpu()[7], want[1, 0, 2, 2].expand(70), rtol=1e-6) and fy.isfinite().all()
 
 
 FC = [
