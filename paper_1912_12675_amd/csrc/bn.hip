@@ -314,19 +314,20 @@ __device__ __forceinline__ Vec<V> bn_fwd_one(const BnFwdArgs& a, const Vec<V>& y
     return o;
 }
 
-// wide: block (channel, U * 256 units of it)
+// wide: block (channel, U * 256 units of it), channels first; both on the x
+// dimension of the grid, since the others end at 65,535
 template <int V, int U>
 __global__ __launch_bounds__(kBlock) void bn_fwd_apply_wide(BnFwdArgs a)
 {
     __shared__ double sh[2 * kBlock / 64];
     __shared__ float coef[2];
-    const int ch = blockIdx.x, hw = a.h * a.w, upc = hw / V, units = a.imgs * upc;
+    const int ch = blockIdx.x % a.c, blk = blockIdx.x / a.c, hw = a.h * a.w, upc = hw / V, units = a.imgs * upc;
     const bool identity = a.res && a.rc == a.c && a.rh == a.h && a.rw == a.w;
     size_t at[U];
     Vec<V> y[U], r[U];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        const int u = min((int)(blockIdx.y * U + q) * kBlock + (int)threadIdx.x, units - 1);
+        const int u = min((blk * U + q) * kBlock + (int)threadIdx.x, units - 1);
         const int img = u / upc, off = (u - img * upc) * V;
         at[q] = ((size_t)(a.img0 + img) * a.c + ch) * hw + off;
         y[q] = load_v<V>(a.y + at[q]);
@@ -338,28 +339,39 @@ __global__ __launch_bounds__(kBlock) void bn_fwd_apply_wide(BnFwdArgs a)
         s2 += a.part[((size_t)ch * a.parts + p) * 2 + 1];
     }
     block_sum2(s1, s2, sh);
-    if (threadIdx.x == 0) bn_fwd_coef(a, ch, s1, s2, blockIdx.y == 0 && a.img0 == 0, coef[0], coef[1]);
+    if (threadIdx.x == 0) bn_fwd_coef(a, ch, s1, s2, blk == 0 && a.img0 == 0, coef[0], coef[1]);
     __syncthreads();
     const float sc = coef[0], sf = coef[1];
 #pragma unroll
     for (int q = 0; q < U; ++q)
-        if ((int)(blockIdx.y * U + q) * kBlock + (int)threadIdx.x < units)
+        if ((blk * U + q) * kBlock + (int)threadIdx.x < units)
             store_v<V>(a.z + at[q], bn_fwd_one<V>(a, y[q], r[q], sc, sf));
 }
 
-// flat: a thread one unit of an image, for `per` images
+// flat: a thread one unit of an image, for `per` images.  Blocks over an
+// image first, over images next, on the x dimension of the grid.
+struct FlatAt {
+    int u, img, end;
+    __device__ __forceinline__ FlatAt(int ups, int n, int bx, int per)
+    {
+        const int xb = (int)(blockIdx.x % bx), yb = (int)(blockIdx.x / bx);
+        u = xb * kBlock + (int)threadIdx.x;
+        img = yb * per;
+        end = u < ups ? min((yb + 1) * per, n) : 0;
+    }
+};
+
 template <int V>
-__global__ __launch_bounds__(kBlock) void bn_fwd_apply_flat(BnFwdArgs a, int per)
+__global__ __launch_bounds__(kBlock) void bn_fwd_apply_flat(BnFwdArgs a, int bx, int per)
 {
     const int hw = a.h * a.w, ups = a.c * (hw / V);
-    const int u = blockIdx.x * kBlock + threadIdx.x;
-    if (u >= ups) return;
-    const int ch = u / (hw / V), off = (u - ch * (hw / V)) * V;
+    const FlatAt f(ups, a.n, bx, per);
+    if (f.img >= f.end) return;
+    const int ch = f.u / (hw / V), off = (f.u - ch * (hw / V)) * V;
     const bool identity = a.res && a.rc == a.c && a.rh == a.h && a.rw == a.w;
     const float sc = a.coef[2 * ch], sf = a.coef[2 * ch + 1];
-    const int i1 = min((int)(blockIdx.y + 1) * per, a.n);
-    for (int img = blockIdx.y * per; img < i1; ++img) {
-        const size_t at = (size_t)img * ((size_t)a.c * hw) + (size_t)u * V;
+    for (int img = f.img; img < f.end; ++img) {
+        const size_t at = (size_t)img * ((size_t)a.c * hw) + (size_t)f.u * V;
         const Vec<V> y = load_v<V>(a.y + at);
         Vec<V> r = y;
         if (a.res) r = residual<V>(a, img, ch, off, identity);
@@ -437,12 +449,12 @@ __global__ __launch_bounds__(kBlock) void bn_bwd_apply_wide(BnBwdArgs a)
 {
     __shared__ double sh[2 * kBlock / 64];
     __shared__ float coef[3];
-    const int ch = blockIdx.x, upc = a.hw / V, units = a.imgs * upc;
+    const int ch = blockIdx.x % a.c, blk = blockIdx.x / a.c, upc = a.hw / V, units = a.imgs * upc;
     size_t at[U];
     BwdIn<V> in[U];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        const int u = min((int)(blockIdx.y * U + q) * kBlock + (int)threadIdx.x, units - 1);
+        const int u = min((blk * U + q) * kBlock + (int)threadIdx.x, units - 1);
         const int img = u / upc;
         at[q] = ((size_t)(a.img0 + img) * a.c + ch) * a.hw + (size_t)(u - img * upc) * V;
         in[q].load(a, at[q]);
@@ -454,26 +466,25 @@ __global__ __launch_bounds__(kBlock) void bn_bwd_apply_wide(BnBwdArgs a)
     }
     block_sum2(s1, s2, sh);
     const float mu = a.mean[ch], is = a.invstd[ch];
-    if (threadIdx.x == 0) bn_bwd_coef(a, ch, s1, s2, blockIdx.y == 0 && a.img0 == 0, coef);
+    if (threadIdx.x == 0) bn_bwd_coef(a, ch, s1, s2, blk == 0 && a.img0 == 0, coef);
     __syncthreads();
     const float k0 = coef[0], k1 = coef[1], k2 = coef[2];
 #pragma unroll
     for (int q = 0; q < U; ++q)
-        if ((int)(blockIdx.y * U + q) * kBlock + (int)threadIdx.x < units) in[q].finish(a, at[q], mu, is, k0, k1, k2);
+        if ((blk * U + q) * kBlock + (int)threadIdx.x < units) in[q].finish(a, at[q], mu, is, k0, k1, k2);
 }
 
 template <int V>
-__global__ __launch_bounds__(kBlock) void bn_bwd_apply_flat(BnBwdArgs a, int per)
+__global__ __launch_bounds__(kBlock) void bn_bwd_apply_flat(BnBwdArgs a, int bx, int per)
 {
     const int ups = a.c * (a.hw / V);
-    const int u = blockIdx.x * kBlock + threadIdx.x;
-    if (u >= ups) return;
-    const int ch = u / (a.hw / V);
+    const FlatAt f(ups, a.n, bx, per);
+    if (f.img >= f.end) return;
+    const int ch = f.u / (a.hw / V);
     const float mu = a.mean[ch], is = a.invstd[ch];
     const float k0 = a.coef[3 * ch], k1 = a.coef[3 * ch + 1], k2 = a.coef[3 * ch + 2];
-    const int i1 = min((int)(blockIdx.y + 1) * per, a.n);
-    for (int img = blockIdx.y * per; img < i1; ++img) {
-        const size_t at = (size_t)img * ((size_t)a.c * a.hw) + (size_t)u * V;
+    for (int img = f.img; img < f.end; ++img) {
+        const size_t at = (size_t)img * ((size_t)a.c * a.hw) + (size_t)f.u * V;
         BwdIn<V> in;
         in.load(a, at);
         in.finish(a, at, mu, is, k0, k1, k2);
@@ -569,19 +580,27 @@ int wide_units(int64_t units_total)
     return 1;
 }
 
-// images of one launch of a kernel that counts units in 32 bits
-int slice_images(int n, int64_t units_per_image)
+// images of one launch: units of an image counted in 32 bits, `threads` in all
+// for an image (a grid ends at 2^32)
+int slice_images(int n, int64_t units_per_image, int64_t threads)
 {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(n, (INT32_MAX - 8 * kBlock) / units_per_image));
+    const int64_t most = std::min((INT32_MAX - 8 * kBlock) / units_per_image, (int64_t)INT32_MAX / threads);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(n, most));
 }
 
-// images per thread of the flat apply kernels
-int flat_images(int n, int64_t blocks)
-{
-    int per = 1;
-    while (per < 8 && per * 2 <= n && blocks * (n / (per * 2)) >= 1024) per *= 2;
-    return per;
-}
+// the flat apply kernels' launch: blocks over an image, images of a thread,
+// and the blocks in all
+struct FlatGrid {
+    int bx, per;
+    int64_t blocks;
+    FlatGrid(int n, int64_t ups)
+    {
+        bx = (int)((ups + kBlock - 1) / kBlock);
+        per = 1;
+        while (per < 8 && per * 2 <= n && (int64_t)bx * (n / (per * 2)) >= 1024) per *= 2;
+        blocks = (int64_t)bx * ((n + per - 1) / per);
+    }
+};
 
 }  // namespace
 
@@ -639,20 +658,19 @@ hipError_t bn_fwd(int n, int c, int h, int w, const float* y, const float* gamma
     if (is_flat(hw, v)) {
         PSW_LAUNCH(kname("bn_fwd_merge"), (Work{2.0 * c * s.parts, 16.0 * c * s.parts + 6 * kF * c}), bn_fwd_merge,
                    dim3((unsigned)((c + 3) / 4)), dim3(kBlock), 0, st, a);
-        const unsigned bx = (unsigned)((c * (hw / v) + kBlock - 1) / kBlock);
-        const int per = flat_images(n, bx);
-        const dim3 grid(bx, (unsigned)((n + per - 1) / per));
+        const FlatGrid f(n, (int64_t)c * (hw / v));
+        const dim3 grid((unsigned)f.blocks);
         if (v == 4)
-            PSW_LAUNCH(kname("bn_fwd_apply_flat", 4), wk, bn_fwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, per);
+            PSW_LAUNCH(kname("bn_fwd_apply_flat", 4), wk, bn_fwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
         else
-            PSW_LAUNCH(kname("bn_fwd_apply_flat", 1), wk, bn_fwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, per);
+            PSW_LAUNCH(kname("bn_fwd_apply_flat", 1), wk, bn_fwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
         return hipGetLastError();
     }
     const int U = wide_units((int64_t)n * (hw / v) * c);
-    for (int i0 = 0, step = slice_images(n, hw / v); i0 < n; i0 += step) {
+    for (int i0 = 0, step = slice_images(n, hw / v, (int64_t)c * (hw / v)); i0 < n; i0 += step) {
         a.img0 = i0;
         a.imgs = std::min(step, n - i0);
-        const dim3 grid((unsigned)c, (unsigned)(((int64_t)a.imgs * (hw / v) + U * kBlock - 1) / (U * kBlock)));
+        const dim3 grid((unsigned)(c * (((int64_t)a.imgs * (hw / v) + U * kBlock - 1) / (U * kBlock))));
 #define PSW_BN(V_, U_) \
     PSW_LAUNCH(kname("bn_fwd_apply_wide", V_, U_), wk, (bn_fwd_apply_wide<V_, U_>), grid, dim3(kBlock), 0, st, a)
         if (v == 4 && U == 4) PSW_BN(4, 4);
@@ -685,19 +703,18 @@ hipError_t bn_bwd(int n, int c, int h, int w, const float* dz, const float* z, c
     if (is_flat(hw, v)) {
         PSW_LAUNCH(kname("bn_bwd_merge"), (Work{2.0 * c * s.parts, 16.0 * c * s.parts + 7 * kF * c}), bn_bwd_merge,
                    dim3((unsigned)((c + 3) / 4)), dim3(kBlock), 0, st, a);
-        const unsigned bx = (unsigned)((c * (hw / v) + kBlock - 1) / kBlock);
-        const int per = flat_images(n, bx);
-        const dim3 grid(bx, (unsigned)((n + per - 1) / per));
+        const FlatGrid f(n, (int64_t)c * (hw / v));
+        const dim3 grid((unsigned)f.blocks);
         if (v == 4)
-            PSW_LAUNCH(kname("bn_bwd_apply_flat", 4), wk, bn_bwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, per);
+            PSW_LAUNCH(kname("bn_bwd_apply_flat", 4), wk, bn_bwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
         else
-            PSW_LAUNCH(kname("bn_bwd_apply_flat", 1), wk, bn_bwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, per);
+            PSW_LAUNCH(kname("bn_bwd_apply_flat", 1), wk, bn_bwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
     } else {
         const int U = std::min(wide_units((int64_t)n * (hw / v) * c), 2);  // four tensors per unit in registers
-        for (int i0 = 0, step = slice_images(n, hw / v); i0 < n; i0 += step) {
+        for (int i0 = 0, step = slice_images(n, hw / v, (int64_t)c * (hw / v)); i0 < n; i0 += step) {
             a.img0 = i0;
             a.imgs = std::min(step, n - i0);
-            const dim3 grid((unsigned)c, (unsigned)(((int64_t)a.imgs * (hw / v) + U * kBlock - 1) / (U * kBlock)));
+            const dim3 grid((unsigned)(c * (((int64_t)a.imgs * (hw / v) + U * kBlock - 1) / (U * kBlock))));
 #define PSW_BN(V_, U_) \
     PSW_LAUNCH(kname("bn_bwd_apply_wide", V_, U_), wk, (bn_bwd_apply_wide<V_, U_>), grid, dim3(kBlock), 0, st, a)
             if (v == 4 && U == 2) PSW_BN(4, 2);
@@ -710,7 +727,7 @@ hipError_t bn_bwd(int n, int c, int h, int w, const float* dz, const float* z, c
     if (dres && !identity) {
         const int vr = rw % 4 == 0 && aligned16(dres) ? 4 : 1;
         const int64_t upi = (int64_t)rc * rh * (rw / vr);  // units of an image
-        for (int i0 = 0, step = slice_images(n, upi); i0 < n; i0 += step) {
+        for (int i0 = 0, step = slice_images(n, upi, upi); i0 < n; i0 += step) {
             const int64_t units = std::min(step, n - i0) * upi;
             const Work ws2{0.0, kF * ((1.0 + res_accumulate) * units * vr + (relu ? 2.0 : 1.0) * n * rc * hw)};
             const dim3 grid((unsigned)((units + kBlock - 1) / kBlock));

@@ -406,6 +406,30 @@ def test_bn_edges(P, case, accumulate):
         close(dres, refres.numpy(), "dres")
 
 
+@pytest.mark.parametrize("case", [(1200001, 3, 1, 1), (1, 1, 8201, 8201)], ids=lambda c: "x".join(map(str, c)))
+def test_bn_blocks_past_16_bits(P, case):
+    """More blocks of images, or of a channel's units, than a grid's second dimension holds."""
+    print("bn blocks", case, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    n, c, h, w = case
+    y, dz = (torch.randn(*case, generator=g, device="cuda") for _ in range(2))
+    gamma, beta = (torch.randn(c, generator=g, device="cuda") for _ in range(2))
+    out, dy = torch.empty_like(y), torch.empty_like(y)
+    sm, si, dg, db = (torch.empty(c, device="cuda") for _ in range(4))
+    P.psw_bn_relu_fwd(y, gamma, beta, out, sm, si, relu=True)
+    v = lambda a: a.double().view(1, -1, 1, 1)  # noqa: E731
+    inv = 1 / torch.sqrt(y.double().var((0, 2, 3), unbiased=False) + 1e-5)
+    xh = (y.double() - v(y.double().mean((0, 2, 3)))) * v(inv)
+    want = (xh * v(gamma) + v(beta)).clamp(min=0)
+    assert bool((out.double() - want).abs().max() <= TOL * want.abs().max())
+    P.psw_bn_relu_bwd(dz, out, y, gamma, sm, si, dy, dg, db, relu=True)
+    gz = dz.double() * (out > 0)
+    sb, sg, m = gz.sum((0, 2, 3)), (gz * xh).sum((0, 2, 3)), n * h * w
+    want = v(gamma) * v(inv) * (gz - v(sb) / m - xh * v(sg) / m)
+    assert bool((dy.double() - want).abs().max() <= TOL * want.abs().max())
+    assert torch.allclose(dg.double(), sg, rtol=1e-5, atol=1e-3) and torch.allclose(db.double(), sb, rtol=1e-5, atol=1e-3)
+
+
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("case", [(3, 5, 8, 8, 2), (2, 3, 9, 12, 2), (2, 3, 7, 10, 2), (2, 3, 8, 7, 2), (1, 1, 2, 2, 2),
                                   (2, 4, 11, 13, 3), (5, 67, 32, 32, 2)], ids=lambda c: "x".join(map(str, c)))
