@@ -161,25 +161,28 @@ __global__ __launch_bounds__(kBlock) void chan_sums_wide(SumArgs a)
 }
 
 // flat planes: block (group of channels, part), a thread one unit of each of
-// the part's images; a channel's threads meet in LDS in order
+// its images; a channel's threads meet in LDS in order.  Where the channels
+// are fewer than a block's threads hold, the threads take `side` images at a
+// time (16 channels of 1x1, 400,000 images: 131 us forward without, 53 now).
 template <int MODE, int V>
-__global__ __launch_bounds__(kBlock) void chan_sums_flat(SumArgs a)
+__global__ __launch_bounds__(kBlock) void chan_sums_flat(SumArgs a, int group, int side)
 {
     __shared__ double sh[2][kBlock];
-    const int upc = a.hw / V, group = kBlock / upc;  // whole channels of one block
-    const int lc = (int)threadIdx.x / upc, ch = blockIdx.x * group + lc;
-    const bool live = lc < group && ch < a.c;
+    const int upc = a.hw / V, width = group * upc;  // units of one image in this block
+    const int sub = (int)threadIdx.x / width, unit = (int)threadIdx.x - sub * width;
+    const int lc = unit / upc, ch = blockIdx.x * group + lc;
+    const bool live = sub < side && ch < a.c;
     const int i0 = (int)((int64_t)a.n * blockIdx.y / a.parts), i1 = (int)((int64_t)a.n * (blockIdx.y + 1) / a.parts);
     Sums<MODE, V> s;
     if (live) {
         s.channel(a, ch);
-        const size_t at = (size_t)ch * a.hw + ((int)threadIdx.x - lc * upc) * V, step = (size_t)a.c * a.hw;
+        const size_t at = (size_t)ch * a.hw + (unit - lc * upc) * V, step = (size_t)a.c * a.hw;
         constexpr int B = 4;
-        for (int img = i0; img < i1; img += B) {
+        for (int img = i0 + sub; img < i1; img += B * side) {
             Vec<V> x[B], z[B], y[B];
 #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const size_t o = at + (size_t)min(img + b, i1 - 1) * step;
+                const size_t o = at + (size_t)min(img + b * side, i1 - 1) * step;
                 x[b] = load_v<V>(a.x + o);
                 if (MODE == GRAD) {
                     y[b] = load_v<V>(a.y + o);
@@ -188,7 +191,7 @@ __global__ __launch_bounds__(kBlock) void chan_sums_flat(SumArgs a)
             }
 #pragma unroll
             for (int b = 0; b < B; ++b)
-                if (img + b < i1) s.add(x[b], z[b], y[b], a.relu);
+                if (img + b * side < i1) s.add(x[b], z[b], y[b], a.relu);
         }
     }
     sh[0][threadIdx.x] = s.s1;
@@ -198,10 +201,11 @@ __global__ __launch_bounds__(kBlock) void chan_sums_flat(SumArgs a)
     const int mine = (int)blockIdx.x * group + t;
     if (t < group && mine < a.c) {
         double s1 = 0.0, s2 = 0.0;
-        for (int u = t * upc; u < (t + 1) * upc; ++u) {
-            s1 += sh[0][u];
-            s2 += sh[1][u];
-        }
+        for (int q = 0; q < side; ++q)
+            for (int u = q * width + t * upc; u < q * width + (t + 1) * upc; ++u) {
+                s1 += sh[0][u];
+                s2 += sh[1][u];
+            }
         double* p = a.part + ((size_t)mine * a.parts + blockIdx.y) * 2;
         p[0] = s1;
         p[1] = s2;
@@ -348,29 +352,32 @@ __global__ __launch_bounds__(kBlock) void bn_fwd_apply_wide(BnFwdArgs a)
             store_v<V>(a.z + at[q], bn_fwd_one<V>(a, y[q], r[q], sc, sf));
 }
 
-// flat: a thread one unit of an image, for `per` images.  Blocks over an
+// flat: a thread one unit of an image, for `per` images; `side` images at a
+// time where an image has fewer units than a block threads.  Blocks over an
 // image first, over images next, on the x dimension of the grid.
 struct FlatAt {
-    int u, img, end;
-    __device__ __forceinline__ FlatAt(int ups, int n, int bx, int per)
+    int u, img, end, step;
+    __device__ __forceinline__ FlatAt(int ups, int n, int bx, int side, int per)
     {
         const int xb = (int)(blockIdx.x % bx), yb = (int)(blockIdx.x / bx);
-        u = xb * kBlock + (int)threadIdx.x;
-        img = yb * per;
-        end = u < ups ? min((yb + 1) * per, n) : 0;
+        const int sub = side > 1 ? (int)threadIdx.x / ups : 0;
+        u = xb * kBlock + (int)threadIdx.x - sub * ups;
+        img = yb * per * side + sub;
+        end = u < ups && sub < side ? min((yb + 1) * per * side, n) : 0;
+        step = side;
     }
 };
 
 template <int V>
-__global__ __launch_bounds__(kBlock) void bn_fwd_apply_flat(BnFwdArgs a, int bx, int per)
+__global__ __launch_bounds__(kBlock) void bn_fwd_apply_flat(BnFwdArgs a, int bx, int side, int per)
 {
     const int hw = a.h * a.w, ups = a.c * (hw / V);
-    const FlatAt f(ups, a.n, bx, per);
+    const FlatAt f(ups, a.n, bx, side, per);
     if (f.img >= f.end) return;
     const int ch = f.u / (hw / V), off = (f.u - ch * (hw / V)) * V;
     const bool identity = a.res && a.rc == a.c && a.rh == a.h && a.rw == a.w;
     const float sc = a.coef[2 * ch], sf = a.coef[2 * ch + 1];
-    for (int img = f.img; img < f.end; ++img) {
+    for (int img = f.img; img < f.end; img += f.step) {
         const size_t at = (size_t)img * ((size_t)a.c * hw) + (size_t)f.u * V;
         const Vec<V> y = load_v<V>(a.y + at);
         Vec<V> r = y;
@@ -475,15 +482,15 @@ __global__ __launch_bounds__(kBlock) void bn_bwd_apply_wide(BnBwdArgs a)
 }
 
 template <int V>
-__global__ __launch_bounds__(kBlock) void bn_bwd_apply_flat(BnBwdArgs a, int bx, int per)
+__global__ __launch_bounds__(kBlock) void bn_bwd_apply_flat(BnBwdArgs a, int bx, int side, int per)
 {
     const int ups = a.c * (a.hw / V);
-    const FlatAt f(ups, a.n, bx, per);
+    const FlatAt f(ups, a.n, bx, side, per);
     if (f.img >= f.end) return;
     const int ch = f.u / (a.hw / V);
     const float mu = a.mean[ch], is = a.invstd[ch];
     const float k0 = a.coef[3 * ch], k1 = a.coef[3 * ch + 1], k2 = a.coef[3 * ch + 2];
-    for (int img = f.img; img < f.end; ++img) {
+    for (int img = f.img; img < f.end; img += f.step) {
         const size_t at = (size_t)img * ((size_t)a.c * a.hw) + (size_t)f.u * V;
         BwdIn<V> in;
         in.load(a, at);
@@ -540,10 +547,14 @@ int channel_splits(int n, int c)
 
 bool is_flat(int hw, int v) { return hw / v < 64; }
 
+// channels of one block of the flat sums, and images it takes side by side
+int flat_group(int c, int upc) { return std::min(kBlock / upc, c); }
+int flat_side(int c, int upc) { return kBlock / (flat_group(c, upc) * upc); }
+
 // parts of the flat kernels: about 512 workgroups, at least four images each
 int flat_parts(int n, int c, int hw, int v)
 {
-    const int group = kBlock / (hw / v), blocks = (c + group - 1) / group;
+    const int group = flat_group(c, hw / v), blocks = (c + group - 1) / group;
     int p = (512 + blocks - 1) / blocks;
     if (p > (n + 3) / 4) p = (n + 3) / 4;
     if (p < 1) p = 1;
@@ -556,12 +567,14 @@ template <int MODE>
 void launch_sums(const SumArgs& a, int v, const Work& wk, hipStream_t st)
 {
     if (is_flat(a.hw, v)) {
-        const int group = kBlock / (a.hw / v);
+        const int group = flat_group(a.c, a.hw / v), side = flat_side(a.c, a.hw / v);
         const dim3 grid((unsigned)((a.c + group - 1) / group), (unsigned)a.parts);
         if (v == 4)
-            PSW_LAUNCH(kname("chan_sums_flat", MODE, 4), wk, (chan_sums_flat<MODE, 4>), grid, dim3(kBlock), 0, st, a);
+            PSW_LAUNCH(kname("chan_sums_flat", MODE, 4), wk, (chan_sums_flat<MODE, 4>), grid, dim3(kBlock), 0, st, a, group,
+                       side);
         else
-            PSW_LAUNCH(kname("chan_sums_flat", MODE, 1), wk, (chan_sums_flat<MODE, 1>), grid, dim3(kBlock), 0, st, a);
+            PSW_LAUNCH(kname("chan_sums_flat", MODE, 1), wk, (chan_sums_flat<MODE, 1>), grid, dim3(kBlock), 0, st, a, group,
+                       side);
     } else {
         const dim3 grid((unsigned)a.c, (unsigned)a.parts);
         if (v == 4)
@@ -588,17 +601,19 @@ int slice_images(int n, int64_t units_per_image, int64_t threads)
     return (int)std::max<int64_t>(1, std::min<int64_t>(n, most));
 }
 
-// the flat apply kernels' launch: blocks over an image, images of a thread,
-// and the blocks in all
+// the flat apply kernels' launch: blocks over an image, images side by side
+// and one after another, and the blocks in all
 struct FlatGrid {
-    int bx, per;
+    int bx, side, per;
     int64_t blocks;
     FlatGrid(int n, int64_t ups)
     {
         bx = (int)((ups + kBlock - 1) / kBlock);
+        side = ups < kBlock ? kBlock / (int)ups : 1;
+        const int rows = (n + side - 1) / side;  // groups of images
         per = 1;
-        while (per < 8 && per * 2 <= n && (int64_t)bx * (n / (per * 2)) >= 1024) per *= 2;
-        blocks = (int64_t)bx * ((n + per - 1) / per);
+        while (per < 8 && per * 2 <= rows && (int64_t)bx * (rows / (per * 2)) >= 1024) per *= 2;
+        blocks = (int64_t)bx * ((rows + per - 1) / per);
     }
 };
 
@@ -661,9 +676,11 @@ hipError_t bn_fwd(int n, int c, int h, int w, const float* y, const float* gamma
         const FlatGrid f(n, (int64_t)c * (hw / v));
         const dim3 grid((unsigned)f.blocks);
         if (v == 4)
-            PSW_LAUNCH(kname("bn_fwd_apply_flat", 4), wk, bn_fwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
+            PSW_LAUNCH(kname("bn_fwd_apply_flat", 4), wk, bn_fwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, f.bx, f.side,
+                       f.per);
         else
-            PSW_LAUNCH(kname("bn_fwd_apply_flat", 1), wk, bn_fwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
+            PSW_LAUNCH(kname("bn_fwd_apply_flat", 1), wk, bn_fwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, f.bx, f.side,
+                       f.per);
         return hipGetLastError();
     }
     const int U = wide_units((int64_t)n * (hw / v) * c);
@@ -706,9 +723,11 @@ hipError_t bn_bwd(int n, int c, int h, int w, const float* dz, const float* z, c
         const FlatGrid f(n, (int64_t)c * (hw / v));
         const dim3 grid((unsigned)f.blocks);
         if (v == 4)
-            PSW_LAUNCH(kname("bn_bwd_apply_flat", 4), wk, bn_bwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
+            PSW_LAUNCH(kname("bn_bwd_apply_flat", 4), wk, bn_bwd_apply_flat<4>, grid, dim3(kBlock), 0, st, a, f.bx, f.side,
+                       f.per);
         else
-            PSW_LAUNCH(kname("bn_bwd_apply_flat", 1), wk, bn_bwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, f.bx, f.per);
+            PSW_LAUNCH(kname("bn_bwd_apply_flat", 1), wk, bn_bwd_apply_flat<1>, grid, dim3(kBlock), 0, st, a, f.bx, f.side,
+                       f.per);
     } else {
         const int U = std::min(wide_units((int64_t)n * (hw / v) * c), 2);  // four tensors per unit in registers
         for (int i0 = 0, step = slice_images(n, hw / v, (int64_t)c * (hw / v)); i0 < n; i0 += step) {

@@ -352,6 +352,9 @@ BN = [
     (3, 12, 14, 18, "third", True),        # 252 = 63 units: the largest flat plane
     (130, 5, 16, 16, None, True),
     (2, 4, 66, 66, "half", True),
+    (1001, 5, 1, 1, None, True),           # planes of one: 51 images side by side, the last group short
+    (2050, 3, 2, 2, "identity", True),     # ... 85 by fours
+    (77, 130, 1, 1, None, False),          # one image at a time, a second block part full
 ]
 
 
