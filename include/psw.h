@@ -275,9 +275,10 @@ int psw_net_bind(psw_net *net, float *ring, float *momentum, float *grad, float 
  * Streams: the forward pass and the data-gradient chain run on `stream`;
  * the weight gradients and each stage's update (issued as soon as the
  * backward pass is done with that stage) run on a stream of the library
- * (all nets of a device share it, and the forward stream of pipelined
- * runs, so that one net's streams keep their own hardware queues), joined back into `stream` before the call returns, so all work of the
- * step is ordered before whatever the caller enqueues next on `stream`. */
+ * that goes with `stream` (nets issued on one `stream` share it, and the
+ * forward stream of pipelined runs; nets on two streams do not wait for each
+ * other), joined back into `stream` before the call returns, so all work of
+ * the step is ordered before whatever the caller enqueues next on `stream`. */
 int psw_stage_step(psw_net *net, int64_t t, const int32_t *staleness, const float *lr, float mom,
                    float wd, int nesterov, const float *x, const int32_t *labels, float *loss_out,
                    int32_t *versions_out, void *stream);

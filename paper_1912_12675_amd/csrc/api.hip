@@ -86,50 +86,149 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices];  // device address of `scratch` per device, nullptr until resolved
 
-// The weight stream and the forward stream of a device's nets.  A process has
-// four hardware queues; with a pair of streams per net, the streams of a
+// The weight and the forward stream that go with a caller's stream.  A process
+// has four hardware queues; with a pair of streams per net, the streams of a
 // second or third net (a program that keeps nets of several sizes) land on
 // queues that a net's own streams use, and work that should overlap runs in
 // turn: with three nets alive, twelve pipelined ResNet-20 b128 steps took 10.6
-// ms instead of 7.4.  So all nets of a device share one pair.  A stream is in
-// issue order and every wait refers to an event recorded before it, so nets
-// issued from several threads only ever wait for work issued earlier.  Graph
-// captures, the library's and a caller's, use streams of their own.
-struct SharedStream {
-    hipStream_t stream = nullptr;
-    int users = 0;
+// ms instead of 7.4.  Nets issued on one caller stream follow one another
+// anyway, so they share a pair; nets on two caller streams have a pair each,
+// and neither waits for the other's work, however long its stream is held.
+// Past kPairs caller streams of a device the pair that was idle longest is
+// handed on (with none idle, the least recently used is shared: more order,
+// the same results).  Graph captures, the library's and a caller's, use streams
+// of their own.  A device's pairs are given back with its last net.
+constexpr int kPairs = 8;
+struct StreamPair {
+    bool taken = false;  // by `caller`
+    hipStream_t caller = nullptr;
+    const void* thread = nullptr;  // of the per-thread default stream
+    hipStream_t weight = nullptr, forward = nullptr;
+    uint64_t used = 0;  // when, by DeviceStreams::clock
 };
-enum { kWeightStream, kForwardStream };
+struct DeviceStreams {
+    StreamPair pair[kPairs];
+    int nets = 0;
+    uint64_t clock = 0;
+};
 std::mutex g_streams_mu;
-SharedStream g_streams[kMaxDevices][2];
+DeviceStreams g_streams[kMaxDevices];
 
-hipError_t take_stream(int which, int* device, hipStream_t* out)
+// Making or asking a stream is no part of a graph that this thread captures.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t err = hipThreadExchangeStreamCaptureMode(&mode);
+    ~RelaxedCapture()
+    {
+        if (err == hipSuccess) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+hipError_t make_stream(int device, hipStream_t* st)
+{
+    if (*st) return hipSuccess;
+    int current = device;
+    hipError_t e = hipGetDevice(&current);
+    if (e == hipSuccess && current != device) e = hipSetDevice(device);
+    if (e != hipSuccess) return e;
+    e = hipStreamCreateWithFlags(st, hipStreamNonBlocking);
+    if (e != hipSuccess) *st = nullptr;
+    if (current != device) (void)hipSetDevice(current);
+    return e;
+}
+
+// A net joins the current device's streams: a first pair, and every pair's
+// forward stream for pipelined runs, are made here rather than in a step.
+hipError_t join_streams(int* device)
 {
     hipError_t e = hipGetDevice(device);
     if (e != hipSuccess) return e;
     if (*device < 0 || *device >= kMaxDevices) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> lock(g_streams_mu);
-    SharedStream& s = g_streams[*device][which];
-    if (!s.stream) {
-        e = hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking);
-        if (e != hipSuccess) {
-            s.stream = nullptr;
-            return e;
-        }
+    e = make_stream(*device, &g_streams[*device].pair[0].weight);
+    if (e == hipSuccess) ++g_streams[*device].nets;
+    return e;
+}
+
+hipError_t make_forward_streams(int device)
+{
+    std::lock_guard<std::mutex> lock(g_streams_mu);
+    hipError_t e = hipSuccess;
+    for (StreamPair& p : g_streams[device].pair)
+        if (p.weight && e == hipSuccess) e = make_stream(device, &p.forward);
+    return e;
+}
+
+void leave_streams(int device)
+{
+    std::lock_guard<std::mutex> lock(g_streams_mu);
+    DeviceStreams& d = g_streams[device];
+    if (--d.nets) return;
+    for (StreamPair& p : d.pair) {
+        for (hipStream_t st : {p.weight, p.forward})
+            if (st) (void)hipStreamDestroy(st);
+        p = StreamPair{};
     }
-    ++s.users;
-    *out = s.stream;
+}
+
+bool idle(hipStream_t st)
+{
+    const bool done = !st || hipStreamQuery(st) == hipSuccess;
+    if (!done) (void)hipGetLastError();  // "not ready" is no error of a later launch
+    return done;
+}
+
+// the pair of `caller`: its index, weight stream and (pipeline) forward stream
+hipError_t streams_of(int device, hipStream_t caller, bool pipeline, int* index, hipStream_t* weight,
+                      hipStream_t* forward)
+{
+    static thread_local char here;
+    const void* thread = caller == hipStreamPerThread ? &here : nullptr;
+    std::lock_guard<std::mutex> lock(g_streams_mu);
+    DeviceStreams& d = g_streams[device];
+    int at = -1, open = -1;
+    for (int i = 0; i < kPairs; ++i) {
+        const StreamPair& p = d.pair[i];
+        if (p.taken && p.caller == caller && p.thread == thread) at = i;
+        if (!p.taken && open < 0) open = i;
+    }
+    RelaxedCapture relaxed;
+    if (relaxed.err != hipSuccess) return relaxed.err;
+    if (at < 0) at = open;
+    if (at < 0) {
+        int oldest_idle = -1, oldest = 0;
+        for (int i = 0; i < kPairs; ++i) {
+            const StreamPair& p = d.pair[i];
+            if (p.used < d.pair[oldest].used) oldest = i;
+            if ((oldest_idle < 0 || p.used < d.pair[oldest_idle].used) && idle(p.weight) && idle(p.forward))
+                oldest_idle = i;
+        }
+        at = oldest_idle >= 0 ? oldest_idle : oldest;
+    }
+    StreamPair& p = d.pair[at];
+    hipError_t e = make_stream(device, &p.weight);
+    if (e == hipSuccess && pipeline) e = make_stream(device, &p.forward);
+    if (e != hipSuccess) return e;
+    p.taken = true;
+    p.caller = caller;
+    p.thread = thread;
+    p.used = ++d.clock;
+    *index = at;
+    *weight = p.weight;
+    *forward = pipeline ? p.forward : nullptr;
     return hipSuccess;
 }
 
-void give_stream(int which, int device)
+// the streams of the pairs whose bits are set
+std::vector<hipStream_t> streams_at(int device, unsigned pairs)
 {
+    std::vector<hipStream_t> at;
     std::lock_guard<std::mutex> lock(g_streams_mu);
-    SharedStream& s = g_streams[device][which];
-    if (--s.users == 0) {
-        (void)hipStreamDestroy(s.stream);
-        s.stream = nullptr;
-    }
+    for (int i = 0; i < kPairs; ++i)
+        if (pairs >> i & 1)
+            for (hipStream_t st : {g_streams[device].pair[i].weight, g_streams[device].pair[i].forward})
+                if (st) at.push_back(st);
+    return at;
 }
 
 int scratch_of_current_device(void** out, const char* what)
@@ -438,19 +537,20 @@ struct psw_net {
     // per stage: it has conv layers, whose weight gradients run on the weight
     // stream; a stage without them is updated on the data-gradient stream
     std::vector<char> stage_has_conv;
-    // backward-weight kernels run on a second stream of the library (shared by
-    // the device's nets, default priority), forked from the caller's stream
-    // when a conv's output gradient is final and joined before the update
-    hipStream_t side = nullptr;
-    int side_dev = 0, fwd_dev = 0;
+    // During a call: backward-weight kernels run on a second stream of the
+    // library (that of the caller's stream, default priority), forked from the
+    // caller's when a conv's output gradient is final and joined before the
+    // update; the forward pass of a pipelined run on a third
+    hipStream_t side = nullptr, fwd = nullptr;
+    int device = -1;          // whose streams the net has joined
+    unsigned pairs_used = 0;  // bit i: the device's pair i has had work of this net
     // in their place while the caller's stream is being captured (made on first use)
     hipStream_t cap_side = nullptr, cap_fwd = nullptr;
     std::vector<hipEvent_t> stage_ev;       // per stage: the chain is done with the stage
     hipEvent_t join_ev = nullptr;
-    // pipelined runs (psw_pipeline_run): forward stream, further step sets,
+    // pipelined runs (psw_pipeline_run): further step sets,
     // per-stage update events indexed by version mod upd_q, per step set
     // "weight stream done with the step" events
-    hipStream_t fwd = nullptr;
     static constexpr int kMaxSets = 3;
     char* sets[kMaxSets] = {nullptr, nullptr, nullptr};  // step sets: [0] in the arena, more bound for pipelining
     int nsets = 1;
@@ -514,8 +614,7 @@ struct psw_net {
     ~psw_net()
     {
         for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
-        if (side) (void)hipStreamSynchronize(side);
-        if (fwd) (void)hipStreamSynchronize(fwd);
+        for (hipStream_t st : streams_at(device, pairs_used)) (void)hipStreamSynchronize(st);
         for (hipEvent_t e : stage_ev)
             if (e) (void)hipEventDestroy(e);
         for (hipEvent_t e : upd_ev)
@@ -524,8 +623,7 @@ struct psw_net {
             if (e) (void)hipEventDestroy(e);
         for (hipEvent_t e : {join_ev, fdone_ev, start_ev})
             if (e) (void)hipEventDestroy(e);
-        if (side) give_stream(kWeightStream, side_dev);
-        if (fwd) give_stream(kForwardStream, fwd_dev);
+        if (device >= 0) leave_streams(device);
         for (hipStream_t c : {cap_side, cap_fwd})
             if (c) (void)hipStreamDestroy(c);
     }
@@ -958,9 +1056,11 @@ int psw_net_bind(psw_net* net, float* ring, float* momentum, float* grad, float*
     net->run_mean = run_mean;
     net->run_var = run_var;
     net->arena = (char*)arena;
-    if (!net->side) {
-        hipError_t e = take_stream(kWeightStream, &net->side_dev, &net->side);
-        if (e != hipSuccess) return hip_check(e, "net_bind: side stream");
+    if (net->device < 0) {
+        int device = -1;
+        hipError_t e = join_streams(&device);
+        if (e != hipSuccess) return hip_check(e, "net_bind: weight stream");
+        net->device = device;
         net->stage_ev.assign(net->S, nullptr);
         for (auto& ev : net->stage_ev) {
             e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -1556,37 +1656,33 @@ struct RecorderScope {
     ~RecorderScope() { psw::kernel_recorder() = nullptr; }
 };
 
-// While the caller captures `st` into a graph of its own, the net's weight and
-// forward streams are streams of this net: a fork would draw the shared ones
-// into the capture, and what other nets issue on them with it.
-struct CaptureScope {
+// The net's weight and forward stream for a call on `st`: those that go with
+// it.  While the caller captures `st` into a graph of its own they are streams of
+// this net: a fork would draw the others into the capture, and what is issued
+// on them from elsewhere with it.
+struct StreamScope {
     psw_net* net;
-    hipStream_t side, fwd;
     hipError_t err = hipSuccess;
-    CaptureScope(psw_net* n, hipStream_t st) : net(n), side(n->side), fwd(n->fwd)
+    StreamScope(psw_net* n, hipStream_t st, bool pipeline) : net(n)
     {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
         if (st) err = hipStreamIsCapturing(st, &status);  // the default stream is never captured
-        if (err != hipSuccess || status != hipStreamCaptureStatusActive) return;
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // making a stream is no part of the graph
-        err = hipThreadExchangeStreamCaptureMode(&mode);
         if (err != hipSuccess) return;
-        for (hipStream_t* c : {&net->cap_side, &net->cap_fwd})
-            if (err == hipSuccess && !*c) {
-                err = hipStreamCreateWithFlags(c, hipStreamNonBlocking);
-                if (err != hipSuccess) *c = nullptr;
-            }
-        const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
-        if (err == hipSuccess) err = back;
+        if (status != hipStreamCaptureStatusActive) {
+            int pair = 0;
+            err = streams_of(net->device, st, pipeline, &pair, &net->side, &net->fwd);
+            if (err == hipSuccess) net->pairs_used |= 1u << pair;
+            return;
+        }
+        RelaxedCapture relaxed;
+        err = relaxed.err;
+        if (err == hipSuccess) err = make_stream(net->device, &net->cap_side);
+        if (err == hipSuccess) err = make_stream(net->device, &net->cap_fwd);
         if (err != hipSuccess) return;
         net->side = net->cap_side;
-        if (fwd) net->fwd = net->cap_fwd;
+        if (pipeline) net->fwd = net->cap_fwd;
     }
-    ~CaptureScope()
-    {
-        net->side = side;
-        net->fwd = fwd;
-    }
+    ~StreamScope() { net->side = net->fwd = nullptr; }
 };
 
 }  // namespace
@@ -1605,8 +1701,8 @@ int psw_stage_step(psw_net* net, int64_t t, const int32_t* staleness, const floa
     if (t != net->next_t)
         return fail(PSW_ERR_STEP_ORDER, "stage_step: expected t = %lld, got %lld", (long long)net->next_t, (long long)t);
     hipStream_t st = S(stream);
-    CaptureScope capture(net, st);
-    if (capture.err != hipSuccess) return hip_check(capture.err, "stage_step: capture");
+    StreamScope streams(net, st, false);
+    if (streams.err != hipSuccess) return hip_check(streams.err, "stage_step: streams");
     StepIO io{t, std::vector<int64_t>(net->S), net->arena, x, labels, loss_out, lr, mom, wd, nesterov, net->grad};
     for (int s = 0; s < net->S; ++s) io.rv[s] = fwd_version(t, staleness[s]);
     Issue is{net, io};
@@ -1644,8 +1740,8 @@ int psw_net_bind_pipeline(psw_net* net, void* step_set, size_t bytes)
         return fail(PSW_ERR_WORKSPACE, "net_bind_pipeline: %zu < %zu bytes", bytes, net->step_bytes);
     const int extra = (int)std::min<size_t>(bytes / net->step_bytes, psw_net::kMaxSets - 1);
     if (((uintptr_t)step_set) % 256 != 0) return fail(PSW_ERR_SHAPE, "net_bind_pipeline: must be 256-byte aligned");
-    if (!net->fwd) {
-        hipError_t e = take_stream(kForwardStream, &net->fwd_dev, &net->fwd);
+    if (!net->start_ev) {
+        hipError_t e = make_forward_streams(net->device);
         if (e != hipSuccess) return hip_check(e, "net_bind_pipeline: forward stream");
         int D = 1;
         for (int d : net->ring_depth) D = std::max(D, d);
@@ -1820,8 +1916,8 @@ int psw_pipeline_run(psw_net* net, int64_t t0, int n_steps, const int32_t* stale
         return fail(PSW_ERR_STEP_ORDER, "pipeline_run: expected t0 = %lld, got %lld", (long long)net->next_t,
                     (long long)t0);
     if (n_steps == 0) return PSW_OK;
-    CaptureScope capture(net, S(stream));
-    if (capture.err != hipSuccess) return hip_check(capture.err, "pipeline_run: capture");
+    StreamScope streams(net, S(stream), true);
+    if (streams.err != hipSuccess) return hip_check(streams.err, "pipeline_run: streams");
     net->rec.kind = PSW_PROF_OTHER;
     RecorderScope rec_scope(net->profiling ? &net->rec : nullptr);
     int64_t issued = 0;
@@ -1858,15 +1954,13 @@ int psw_pipeline_capture(psw_net* net, int n_steps, const int32_t* staleness, co
     g->period = period;
     g->n_steps = n_steps;
     // the caller's, the weight and the forward stream of the capture: its own, so
-    // that what other threads issue on the shared streams stays out of the graph
+    // that what other threads issue stays out of the graph
     hipStream_t cap[3] = {nullptr, nullptr, nullptr};
     hipError_t e = hipSuccess;
     for (hipStream_t& c : cap)
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&c, hipStreamNonBlocking);
-    const hipStream_t side = net->side, fwd = net->fwd;
     auto done = [&]() {
-        net->side = side;
-        net->fwd = fwd;
+        net->side = net->fwd = nullptr;
         for (hipStream_t c : cap)
             if (c) (void)hipStreamDestroy(c);
     };

@@ -1,6 +1,7 @@
-"""Nets of one device share the library's weight and forward streams: nets
-issued in turn from two threads on streams of their own, and a graph captured
-beside them, give what they give alone."""
+"""The library's weight and forward streams go with the caller's stream: nets on
+one share them, nets on two do not wait for each other; nets issued from two
+threads on streams of their own, and a graph captured beside them, give what
+they give alone."""
 import threading
 
 import numpy as np
@@ -36,7 +37,7 @@ def run(P, made, stream, steps_only=False):
     return net.params(T)
 
 
-def test_two_threads_share_the_streams():
+def test_two_threads():
     from paper_1912_12675_amd import psw as P
     print("streams: two threads", flush=True)
     alone = [run(P, make(P, b, s), torch.cuda.Stream()) for b, s in ((8, 1), (12, 2))]
@@ -57,6 +58,62 @@ def test_two_threads_share_the_streams():
     assert not errors, errors
     for a, b in zip(alone, got):
         assert torch.equal(a, b)
+
+
+def test_two_callers_do_not_wait_for_each_other():
+    """With one net's stream held (by a kernel that spins for a bounded time), a net on another stream finishes
+    its steps.  A process has four hardware queues, and two streams that share one do wait: some of the stream
+    pairs tried have queues apart, and one is enough."""
+    from paper_1912_12675_amd import psw as P
+    print("streams: two callers", flush=True)
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(1000)
+    start.record()
+    torch.cuda._sleep(1_000_000)
+    end.record()
+    torch.cuda.synchronize()
+    cycles = int(250.0 / max(start.elapsed_time(end), 1e-3) * 1_000_000)  # a quarter of a second
+
+    def step(m, t, stream):
+        net, wl, xs, ys = m
+        with torch.cuda.stream(stream):
+            net.step(t, [3, 2, 1, 0], wl.lr, xs[t], ys[t])
+
+    held, free = make(P, 8, 1), make(P, 8, 2)
+    torch.cuda.synchronize()
+    apart = False
+    for t in range(T):
+        a, b = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(a):
+            torch.cuda._sleep(cycles)
+            awake = a.record_event()
+        step(held, t, a)
+        step(free, t, b)
+        b.synchronize()
+        apart = apart or not awake.query()
+        torch.cuda.synchronize()
+    assert apart
+
+
+def test_more_callers_than_pairs():
+    """Steps of one net on more streams than the library keeps pairs for: pairs are handed on."""
+    from paper_1912_12675_amd import psw as P
+    print("streams: many callers", flush=True)
+    ref = run(P, make(P, 8, 1), torch.cuda.Stream(), steps_only=True)
+    net, wl, xs, ys = make(P, 8, 1)
+    other = make(P, 12, 2)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(11)]
+    for s in streams[:5]:  # pairs of other callers, one with work pending
+        run(P, make(P, 12, 2), s, steps_only=True)
+    with torch.cuda.stream(streams[5]):
+        other[0].step(0, [3, 2, 1, 0], other[1].lr, other[2][0], other[3][0])
+    for t in range(T):
+        s = streams[5 + t]
+        with torch.cuda.stream(s):
+            net.step(t, [3, 2, 1, 0], wl.lr, xs[t], ys[t])
+        s.synchronize()
+    assert torch.equal(net.params(T), ref)
 
 
 def test_streams_outlive_one_net():
