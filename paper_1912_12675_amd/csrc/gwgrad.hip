@@ -339,6 +339,17 @@ hipError_t gw_launch(GwArgs a, int max_splits, int* splits, bool dry, const Work
     a.per = (int)((a.chunks + z - 1) / z);
     a.z = (a.chunks + a.per - 1) / a.per;
     a.by_xcd = a.z >= 8;
+    // Up to three images a unit's eight are mostly absent, and the workspace
+    // bounds the parts: past so many units a thread stages in turn the implicit
+    // GEMM's slices of 16 (bf16: 32) pixels take less (fp32, one image, us: 64 -> 64
+    // at 28x28 39 against 22, 64 -> 128 at 56x56 stride 2 47 and 24, 512 -> 512 at
+    // 4x4 19 and 61; two images of the second 29 and 27, of the first 21 and 24;
+    // bf16 one image 24 -> 56 at 29x23 stride 2 31 and 26, of the first 31 and 34).
+    const int TW = 1 << a.lw, TH = 1 << a.lh, TO = PX >> (a.lw + a.lh);
+    const int64_t units = (16 * CT * TO * ((TH - 1) * a.st + RG) * ((TW - 1) * a.st + S) + 255) / 256 + BM * PX / 256;
+    const int bk = NS == 1 ? 32 : 16;
+    const int64_t depth = ((int64_t)a.n * a.P * a.Q + max_splits - 1) / max_splits, slices = (depth + bk - 1) / bk;
+    if (a.n < 4 && a.per * units > (NS == 1 ? 10 * slices + 10 * a.n : 3 * slices + 2 * a.n)) return hipErrorNotSupported;
     *splits = a.z;
     const int64_t blocks = (a.by_xcd ? (a.z + 7) / 8 * 8 : a.z) * combos;
     if (blocks > INT32_MAX) return hipErrorNotSupported;

@@ -42,7 +42,7 @@ CONV = [
     # N, C, H, W, K, R, S, stride, pad
     (1, 1, 1, 1, 1, 1, 1, 1, 0),
     (2, 3, 17, 15, 6, 5, 5, 1, 2),       # one octet of channels, 16 output channels
-    (1, 8, 32, 33, 33, 3, 3, 1, 1),      # 33 output channels: a second block of 64 is not needed, 32 is passed
+    (1, 8, 32, 33, 33, 3, 3, 1, 1),      # one octet, a block of 64 output channels
     (3, 9, 31, 8, 64, 3, 3, 1, 1),       # 9 channels: two octets, the second nearly empty
     (2, 17, 15, 16, 65, 3, 3, 1, 1),     # one past a 16-channel chunk and a 64-channel block
     (2, 31, 16, 17, 63, 3, 3, 1, 1),
@@ -59,8 +59,16 @@ CONV = [
     (2, 64, 16, 16, 96, 5, 5, 1, 2),
     (1, 512, 4, 4, 512, 3, 3, 1, 1),
     (64, 16, 32, 32, 20, 3, 3, 1, 1),    # wide tiles of 32 output channels
-    (64, 40, 32, 32, 64, 3, 3, 1, 0),    # wide tiles of 64
-    (33, 16, 30, 30, 16, 3, 3, 1, 1),    # wide tiles of 16
+    (64, 40, 32, 32, 64, 3, 3, 1, 0),    # ... of 64: two blocks, 512 in all
+    (65, 40, 32, 32, 64, 3, 3, 1, 0),    # ... and more
+    (65, 16, 30, 30, 16, 3, 3, 1, 1),    # wide tiles of 16
+    (33, 16, 30, 30, 16, 3, 3, 1, 1),    # too few for those
+    (9, 70, 13, 11, 130, 1, 1, 1, 0),    # 1x1 weight gradients of two blocks of 64 rows and of 64 channels, both ragged
+    (9, 70, 13, 11, 130, 1, 1, 2, 0),
+    (41, 20, 19, 21, 70, 5, 5, 1, 2),    # 5x5 weight gradients of 64 rows, whose steps take two sums in bf16
+    (1, 24, 29, 23, 56, 3, 3, 2, 1),     # one image: weight gradients by the implicit GEMM
+    (2, 64, 55, 57, 128, 3, 3, 2, 1),    # two: by it, and in bf16 not
+    (3, 20, 21, 23, 40, 3, 3, 1, 0),
     (1, 4, 40, 40, 4, 9, 9, 4, 4),
 ]
 
@@ -246,7 +254,10 @@ FC = [
     (130, 130, 66),
     (257, 16, 10),       # more rows than the small classifier takes
     (128, 5000, 300),
-    (300, 200, 1100),    # tiles of 128 x 128 in the weight gradient
+    (300, 200, 1100),    # rows past gemm_rows' 256
+    (130, 2900, 3000),   # tiles of 128 x 128 in the weight gradient
+    (129, 40, 33000),    # ... in the forward
+    (129, 33000, 40),    # ... in the input gradient
     (128, 96, 16400),
     (33, 70, 16400),     # few k over many columns: 64 x 64 tiles in the forward
     (20, 70, 9000),      # the input's gradient over a deep k, in parts whose sums meet: few tiles
