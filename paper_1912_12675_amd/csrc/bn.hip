@@ -197,15 +197,23 @@ __global__ __launch_bounds__(kBlock) void chan_sums_flat(SumArgs a, int group, i
     sh[0][threadIdx.x] = s.s1;
     sh[1][threadIdx.x] = s.s2;
     __syncthreads();
-    const int t = threadIdx.x;  // thread t < group: channel t of the block
-    const int mine = (int)blockIdx.x * group + t;
+    const int t = threadIdx.x;
+    for (int left = side; left > 1;) {  // the images side by side, halved in order
+        const int keep = (left + 1) / 2;
+        if (sub < left - keep) {
+            sh[0][t] += sh[0][t + keep * width];
+            sh[1][t] += sh[1][t + keep * width];
+        }
+        __syncthreads();
+        left = keep;
+    }
+    const int mine = (int)blockIdx.x * group + t;  // thread t < group: channel t of the block
     if (t < group && mine < a.c) {
         double s1 = 0.0, s2 = 0.0;
-        for (int q = 0; q < side; ++q)
-            for (int u = q * width + t * upc; u < q * width + (t + 1) * upc; ++u) {
-                s1 += sh[0][u];
-                s2 += sh[1][u];
-            }
+        for (int u = t * upc; u < (t + 1) * upc; ++u) {
+            s1 += sh[0][u];
+            s2 += sh[1][u];
+        }
         double* p = a.part + ((size_t)mine * a.parts + blockIdx.y) * 2;
         p[0] = s1;
         p[1] = s2;
@@ -547,9 +555,7 @@ int channel_splits(int n, int c)
 
 bool is_flat(int hw, int v) { return hw / v < 64; }
 
-// channels of one block of the flat sums, and images it takes side by side
-int flat_group(int c, int upc) { return std::min(kBlock / upc, c); }
-int flat_side(int c, int upc) { return kBlock / (flat_group(c, upc) * upc); }
+int flat_group(int c, int upc) { return std::min(kBlock / upc, c); }  // whole channels of a block
 
 // parts of the flat kernels: about 512 workgroups, at least four images each
 int flat_parts(int n, int c, int hw, int v)
@@ -567,7 +573,16 @@ template <int MODE>
 void launch_sums(const SumArgs& a, int v, const Work& wk, hipStream_t st)
 {
     if (is_flat(a.hw, v)) {
-        const int group = flat_group(a.c, a.hw / v), side = flat_side(a.c, a.hw / v);
+        // Fewer channels a block, and images side by side in their place, while
+        // a part's images are more than a thread should take in turn and the
+        // workgroups too few (a bias of 512 channels of 2x2 has the workspace for
+        // two parts: 14.8 us with 256 channels a block).
+        const int upc = a.hw / v, images = (a.n + a.parts - 1) / a.parts;
+        int group = flat_group(a.c, upc);
+        auto side_of = [&](int g) { return std::min(kBlock / (g * upc), images); };
+        while (group * upc > 32 && images > 4 * side_of(group) && (int64_t)(a.c + group - 1) / group * a.parts < 256)
+            group = (group + 1) / 2;
+        const int side = side_of(group);
         const dim3 grid((unsigned)((a.c + group - 1) / group), (unsigned)a.parts);
         if (v == 4)
             PSW_LAUNCH(kname("chan_sums_flat", MODE, 4), wk, (chan_sums_flat<MODE, 4>), grid, dim3(kBlock), 0, st, a, group,

@@ -366,6 +366,7 @@ BN = [
     (1001, 5, 1, 1, None, True),           # planes of one: 51 images side by side, the last group short
     (2050, 3, 2, 2, "identity", True),     # ... 85 by fours
     (77, 130, 1, 1, None, False),          # one image at a time, a second block part full
+    (1, 1, 2, 3, None, False),             # one image, one channel
 ]
 
 
