@@ -37,7 +37,7 @@ def fastcall_command(out: str) -> list:
     inc = [os.path.join(root, "include"), os.path.join(root, "include/torch/csrc/api/include"),
            sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")]
     lib = os.path.join(root, "lib")
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    return [HIPCC, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             *[a for i in inc for a in ("-isystem", i)], os.path.join(CSRC, "fastcall.cpp"), "-o", out, f"-L{lib}",
             "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{lib}"]

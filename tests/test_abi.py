@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_1912_12675_amd import synth
 
@@ -27,6 +28,20 @@ def declared_symbols():
     text = open(HEADER).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
     return sorted(set(re.findall(r"\b(psw_[a-z0-9_]+)\s*\(", text)))
+
+
+def test_calls_without_the_native_module(psw, monkeypatch):
+    """With libpsw.so alone every per-layer call is left to ctypes, after one warning."""
+    import sys
+
+    monkeypatch.setattr(psw, "_fast", None)
+    monkeypatch.setitem(sys.modules, "paper_1912_12675_amd._fastcall", None)  # the import fails
+    monkeypatch.delattr(sys.modules["paper_1912_12675_amd"], "_fastcall", raising=False)
+    t = torch.zeros(4)
+    with pytest.warns(RuntimeWarning, match="ctypes"), pytest.raises(ValueError, match="device tensors"):
+        psw.psw_relu_mask(t, t)
+    with pytest.raises(ValueError, match="device tensors"):
+        psw.psw_sgd_momentum_step(t, t, t, t, 0.1)
 
 
 def test_header_symbols_exported(psw):
