@@ -503,7 +503,7 @@ hipError_t conv_bwd_weight(const ConvShape& cs, const float* x, const float* dy,
     }
     const int z = wgrad_splits(cs, bf16);
     int zz = 0;
-    hipError_t e = conv_general_wgrad(cs, x, dy, (float*)ws, z, &zz, false, bf16, st);
+    hipError_t e = conv_general_wgrad(cs, x, dy, (float*)ws, z, &zz, bf16, st);
     if (e == hipErrorNotSupported) {
         const int BK = bf16 ? 32 : 16;
         IgArgs a = make_args(cs);

@@ -543,17 +543,34 @@ constexpr int64_t kRowsL2 = 4 << 20;  // bytes
 
 // The depth in parts of a multiple of 64 k, whose sums meet in the workspace:
 // where a wave of the one-launch tile would add up more than 16 steps of 32 k
-// and the tiles leave the chip room.  `splits` parts at most, `tiles` of 64 x 64.
-int gs_parts(const GsArgs& a, int64_t tiles, int waves, int bf16, size_t ws_bytes, int* kchunk)
-{
-    if (a.K <= 512 * waves || tiles >= 512) return 1;
-    const int64_t least = bf16 ? 128 : 64;
-    int64_t z = std::min((1024 + tiles - 1) / tiles, (a.K + least - 1) / least);
-    z = std::min(z, (int64_t)(ws_bytes / ((size_t)a.M * a.N * sizeof(float))));
-    if (z <= 1) return 1;
-    *kchunk = (int)(((a.K + z - 1) / z + 63) / 64 * 64);
-    return (a.K + *kchunk - 1) / *kchunk;
-}
+// and the tiles leave the chip room.
+struct Parts {
+    int64_t tiles;  // of 64 x 64
+    bool deep;      // few outputs over a deep k
+    bool near, far; // lane offsets: every tile's in 31 bits, not even the 64 x 64 tile's
+    int parts, kchunk;
+    Parts(const GsArgs& a, int bf16, size_t ws_bytes)
+    {
+        const int64_t ld = std::max(a.lda, a.ldb);
+        // 512 k of a row-contiguous operand or 128 rows of another are the most
+        // of any tile here, 64 of either the most of the 64 x 64 tile; past
+        // that, plain loads
+        near = ld * 512 * 4 <= INT32_MAX;
+        far = ld * 64 * 4 > INT32_MAX;
+        tiles = (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64);
+        deep = a.K > 512 && (int64_t)((a.M + 15) / 16) * ((a.N + 15) / 16) <= 256;
+        const int waves = !near || tiles >= 128 ? 1 : deep ? 16 : 4;
+        parts = 1;
+        kchunk = 0;
+        if (a.K <= 512 * waves || tiles >= 512) return;
+        const int64_t least = bf16 ? 128 : 64;
+        int64_t z = std::min((1024 + tiles - 1) / tiles, (a.K + least - 1) / least);
+        z = std::min(z, (int64_t)(ws_bytes / ((size_t)a.M * a.N * sizeof(float))));
+        if (z <= 1) return;
+        kchunk = (int)(((a.K + z - 1) / z + 63) / 64 * 64);
+        parts = (a.K + kchunk - 1) / kchunk;
+    }
+};
 
 // Tiles, each with the reason it is there (fp32, us; 128 rows unless said):
 // the largest that leaves work for the whole chip, except that
@@ -564,35 +581,28 @@ template <int NS, bool AK, bool BK>
 hipError_t gs_pick(GsArgs a, const Work& wk, float* ws, size_t ws_bytes, hipStream_t st)
 {
     auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    const int64_t ld = std::max(a.lda, a.ldb);
-    // a descriptor's lane offsets are 31 bits: 512 k of a row-contiguous operand
-    // or 128 rows of another are the most of any tile here, 64 of either the
-    // most of the 64 x 64 tile; past that, plain loads
-    const bool near = ld * 512 * 4 <= INT32_MAX, far = ld * 64 * 4 > INT32_MAX;
-    const int64_t tiles = blocks(64, 64);
-    const bool deep = a.K > 512 && blocks(16, 16) <= 256;
-    const int waves = !near || tiles >= 128 ? 1 : deep ? 16 : 4;
-    const int parts = ws ? gs_parts(a, tiles, waves, NS == 1, ws_bytes, &a.kchunk) : 1;
-    if (parts > 1 || !near) {
+    const Parts d(a, NS == 1, ws ? ws_bytes : 0);
+    if (d.parts > 1 || !d.near) {
         GsArgs p = a;
-        if (parts > 1) {
+        if (d.parts > 1) {
+            p.kchunk = d.kchunk;
             p.C = ws;
             p.part = (int64_t)a.M * a.N;
             p.vec = a.N % 4 == 0 && (uintptr_t)ws % 16 == 0;
             p.accumulate = 0;
         }
-        const hipError_t e = far ? gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK, true>(p, wk, st, parts)
-                                 : gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(p, wk, st, parts);
-        if (e != hipSuccess || parts == 1) return e;
-        return reduce_parts(ws, parts, p.part, a.C, a.accumulate, st);
+        const hipError_t e = d.far ? gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK, true>(p, wk, st, d.parts)
+                                   : gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(p, wk, st, d.parts);
+        if (e != hipSuccess || d.parts == 1) return e;
+        return reduce_parts(ws, d.parts, p.part, a.C, a.accumulate, st);
     }
     // bf16 forward of more than 64 rows whose x is larger than the L2 (see gemm())
     if constexpr (NS == 1 && AK && BK)
         if (a.M > 64 && a.M <= 256 && (int64_t)a.M * a.K * 4 > kRowsL2)
             return gs_launch<NS, 128, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
     if (blocks(128, 128) >= 512) return gs_launch<NS, 128, 128, 2, 2, 1, 1, AK, BK>(a, wk, st);
-    if (tiles >= 128) return gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(a, wk, st);
-    if (deep) return gs_launch<NS, 16, 16, 1, 1, 16, 16, AK, BK>(a, wk, st);
+    if (d.tiles >= 128) return gs_launch<NS, 64, 64, 2, 2, 1, 2, AK, BK>(a, wk, st);
+    if (d.deep) return gs_launch<NS, 16, 16, 1, 1, 16, 16, AK, BK>(a, wk, st);
     if (blocks(32, 32) >= 64) return gs_launch<NS, 32, 32, 1, 1, 4, 4, AK, BK>(a, wk, st);
     return gs_launch<NS, 16, 16, 1, 1, 4, 4, AK, BK>(a, wk, st);
 }
@@ -671,6 +681,16 @@ hipError_t fc_gemm_fwd(int n, int in, int out, const float* x, const float* w, c
     a.lda = in;  // x[n][i]
     a.ldb = in;  // w[o][i]
     return gemm<true, true>(a, bf16, nullptr, 0, st);
+}
+
+size_t fc_gemm_bwd_ws_bytes(int n, int in, int out)
+{
+    GsArgs a{};
+    a.M = n; a.N = in; a.K = out;
+    a.lda = out;
+    a.ldb = in;
+    const Parts d(a, 0, SIZE_MAX);  // bf16 takes as many or fewer
+    return d.parts > 1 ? (size_t)d.parts * n * in * sizeof(float) : 0;
 }
 
 hipError_t fc_gemm_bwd(int n, int in, int out, const float* x, const float* w, const float* dy, float* dx,

@@ -1,6 +1,7 @@
 // Backward-weight of a convolution for the shapes without a kernel of their
 // own, on the bf16 matrix cores: fp32 operands as three bfloat16 parts
-// (split.h), or rounded once in bf16 mode.
+// (split.h), or rounded once in bf16 mode.  Kernels of 1, 3 or 5 columns; other
+// widths stay on the implicit GEMM (conv.hip).
 //
 //   dW[k][c][r][s] = sum_{img,p,q} dy[img][k][p][q] x[img][c][p st + r - pad][q st + s - pad]
 //
@@ -300,7 +301,7 @@ size_t gw_lds(const GwArgs& a)
 }
 
 template <int NS, int BM, int WM, int CT, int RG, int S, int PX>
-hipError_t gw_launch(GwArgs a, int max_splits, int* splits, bool dry, const Work& wk, hipStream_t st)
+hipError_t gw_launch(GwArgs a, int max_splits, int* splits, const Work& wk, hipStream_t st)
 {
     constexpr int LP = PX == 16 ? 4 : 3;
     // chunk of PX units: fewest chunks; then the least of x, rows of a
@@ -353,44 +354,43 @@ hipError_t gw_launch(GwArgs a, int max_splits, int* splits, bool dry, const Work
     *splits = a.z;
     const int64_t blocks = (a.by_xcd ? (a.z + 7) / 8 * 8 : a.z) * combos;
     if (blocks > INT32_MAX) return hipErrorNotSupported;
-    if (dry) return hipSuccess;
     PSW_LAUNCH(kname("conv_split_wgrad", NS, BM, WM, CT, RG, S, PX), wk, (conv_split_wgrad<NS, BM, WM, CT, RG, S, PX>),
                dim3((unsigned)blocks), dim3(256), lds, st, a);
     return hipGetLastError();
 }
 
 template <int NS, int BM, int WM, int PX>
-hipError_t gw_taps(const GwArgs& a, int ms, int* sp, bool dry, const Work& wk, hipStream_t st)
+hipError_t gw_taps(const GwArgs& a, int ms, int* sp, const Work& wk, hipStream_t st)
 {
-    if (a.R == 3 && a.S == 3) return gw_launch<NS, BM, WM, 1, 3, 3, PX>(a, ms, sp, dry, wk, st);
-    if (a.S == 5) return gw_launch<NS, BM, WM, 1, 1, 5, PX>(a, ms, sp, dry, wk, st);
-    if (a.S == 3) return gw_launch<NS, BM, WM, 1, 1, 3, PX>(a, ms, sp, dry, wk, st);
-    if (a.S == 1) return gw_launch<NS, BM, WM, 4, 1, 1, PX>(a, ms, sp, dry, wk, st);
+    if (a.R == 3 && a.S == 3) return gw_launch<NS, BM, WM, 1, 3, 3, PX>(a, ms, sp, wk, st);
+    if (a.S == 5) return gw_launch<NS, BM, WM, 1, 1, 5, PX>(a, ms, sp, wk, st);
+    if (a.S == 3) return gw_launch<NS, BM, WM, 1, 1, 3, PX>(a, ms, sp, wk, st);
+    if (a.S == 1) return gw_launch<NS, BM, WM, 4, 1, 1, PX>(a, ms, sp, wk, st);
     return hipErrorNotSupported;
 }
 
 template <int NS>
-hipError_t gw_rows(const GwArgs& a, int ms, int* sp, bool dry, const Work& wk, hipStream_t st)
+hipError_t gw_rows(const GwArgs& a, int ms, int* sp, const Work& wk, hipStream_t st)
 {
-    if (a.K <= 16) return gw_taps<NS, 16, 1, 16>(a, ms, sp, dry, wk, st);
+    if (a.K <= 16) return gw_taps<NS, 16, 1, 16>(a, ms, sp, wk, st);
     // half-size tiles and chunks where 64 x 16 ones would be fewer than two per
     // CU (37 images, 24 -> 56 at 29x23, stride 2: 26 -> 16 us)
     const int64_t units = (int64_t)((a.n + 7) / 8) * a.P * a.Q / 16 * ((a.K + 63) / 64) * ((a.C + 15) / 16);
-    if (units < 512 && a.S > 1) return gw_taps<NS, 32, 2, 8>(a, ms, sp, dry, wk, st);
-    if (a.K <= 32) return gw_taps<NS, 32, 1, 16>(a, ms, sp, dry, wk, st);
+    if (units < 512 && a.S > 1) return gw_taps<NS, 32, 2, 8>(a, ms, sp, wk, st);
+    if (a.K <= 32) return gw_taps<NS, 32, 1, 16>(a, ms, sp, wk, st);
     // a 1x1 chunk has one tap to multiply per loaded value: smaller chunks, three
     // workgroups a CU (128 -> 192 at 16x16 b128 52 -> 34 us)
-    if (a.S == 1) return gw_launch<NS, 64, 2, 4, 1, 1, 8>(a, ms, sp, dry, wk, st);
-    return gw_taps<NS, 64, 2, 16>(a, ms, sp, dry, wk, st);
+    if (a.S == 1) return gw_launch<NS, 64, 2, 4, 1, 1, 8>(a, ms, sp, wk, st);
+    return gw_taps<NS, 64, 2, 16>(a, ms, sp, wk, st);
 }
 
 }  // namespace
 
 // Partial sums of dW (each K x C x R x S) for `*splits` <= max_splits parts of
 // the reduction; hipErrorNotSupported (nothing launched) for kernels without
-// a configuration.  dry: set *splits only.
+// a configuration (other than 1, 3 or 5 columns) and where the implicit GEMM is faster.
 hipError_t conv_general_wgrad(const ConvShape& cs, const float* x, const float* dy, float* part, int max_splits,
-                              int* splits, bool dry, int bf16, hipStream_t st)
+                              int* splits, int bf16, hipStream_t st)
 {
     // byte offsets are 31 bits
     if ((int64_t)cs.n * cs.c * cs.h * cs.w * 4 > INT32_MAX || (int64_t)cs.n * cs.k * cs.p * cs.q * 4 > INT32_MAX)
@@ -402,7 +402,7 @@ hipError_t conv_general_wgrad(const ConvShape& cs, const float* x, const float* 
     a.K = cs.k; a.P = cs.p; a.Q = cs.q; a.R = cs.r; a.S = cs.s;
     a.st = cs.stride; a.pad = cs.pad;
     const Work wk = conv_work(cs);
-    return bf16 ? gw_rows<1>(a, max_splits, splits, dry, wk, st) : gw_rows<3>(a, max_splits, splits, dry, wk, st);
+    return bf16 ? gw_rows<1>(a, max_splits, splits, wk, st) : gw_rows<3>(a, max_splits, splits, wk, st);
 }
 
 }  // namespace psw

@@ -264,10 +264,10 @@ hipError_t conv3x3_wgrad_group(int n, int C, int H, int W, int K, int stride, co
 hipError_t conv_general(const ConvShape& cs, int bwd, const float* x, const float* w, const float* bias, int relu,
                         float* y, int accumulate, int bf16, hipStream_t st);
 // Weight gradient of any convolution as `*splits` <= max_splits partial sums
-// part[z][k*c*r*s] (dry: only sets *splits); hipErrorNotSupported (nothing
-// launched) for kernels without a configuration.
+// part[z][k*c*r*s]; hipErrorNotSupported (nothing launched) for kernels without
+// a configuration, and where the implicit GEMM is faster (few images).
 hipError_t conv_general_wgrad(const ConvShape& cs, const float* x, const float* dy, float* part, int max_splits,
-                              int* splits, bool dry, int bf16, hipStream_t st);
+                              int* splits, int bf16, hipStream_t st);
 // out[i] (+)= sum of part[z][i] over z < splits, in a fixed order.
 hipError_t reduce_parts(const float* part, int splits, int64_t count, float* out, int accumulate, hipStream_t st);
 // in_bn (may be null): x is the raw input of a BN + ReLU whose output is not
@@ -338,6 +338,7 @@ hipError_t gavgpool_bwd(int n, int c, int h, int w, const float* dy, float* dx, 
 // The products of a layer that is not small, on the bf16 matrix cores (fc.hip).
 hipError_t fc_gemm_fwd(int n, int in, int out, const float* x, const float* w, const float* b, int relu, float* y,
                        int bf16, hipStream_t st);
+size_t fc_gemm_bwd_ws_bytes(int n, int in, int out);  // the input gradient's parts
 hipError_t fc_gemm_bwd(int n, int in, int out, const float* x, const float* w, const float* dy, float* dx,
                        int dx_accumulate, float* dw, float* db, int bf16, void* ws, size_t ws_bytes, hipStream_t st);
 hipError_t fc_fwd(int n, int in, int out, const float* x, const float* w, const float* b, int relu, float* y,

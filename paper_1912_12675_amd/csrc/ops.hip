@@ -1254,14 +1254,7 @@ hipError_t fc_fwd(int n, int in, int out, const float* x, const float* w, const 
 
 size_t fc_bwd_ws_bytes(int n, int in, int out)
 {
-    // [db partials: out x 2 doubles, padded][split-K partials of the dx GEMM]
-    const int tiles = ((n + 63) / 64) * ((in + 63) / 64);
-    int splits = tiles < 512 ? (1024 + tiles - 1) / tiles : 1;
-    const int maxs = (out + 63) / 64;
-    if (splits > maxs) splits = maxs;
-    if (splits < 1) splits = 1;
-    const size_t head = (((size_t)out * 2 * sizeof(double)) + 255) / 256 * 256;
-    return head + (size_t)splits * n * in * sizeof(float);
+    return std::max<size_t>(256, small_fc(n, in, out) ? 0 : fc_gemm_bwd_ws_bytes(n, in, out));
 }
 
 hipError_t fc_bwd(int n, int in, int out, const float* x, const float* w, const float* dy, float* dx, int dx_accumulate,
