@@ -187,28 +187,30 @@ hipError_t streams_of(int device, hipStream_t caller, bool pipeline, int* index,
     std::lock_guard<std::mutex> lock(g_streams_mu);
     DeviceStreams& d = g_streams[device];
     int at = -1, open = -1;
-    for (int i = 0; i < kPairs; ++i) {
+    for (int i = 0; i < kPairs && at < 0; ++i) {
         const StreamPair& p = d.pair[i];
         if (p.taken && p.caller == caller && p.thread == thread) at = i;
         if (!p.taken && open < 0) open = i;
     }
-    RelaxedCapture relaxed;
-    if (relaxed.err != hipSuccess) return relaxed.err;
-    if (at < 0) at = open;
-    if (at < 0) {
-        int oldest_idle = -1, oldest = 0;
-        for (int i = 0; i < kPairs; ++i) {
-            const StreamPair& p = d.pair[i];
-            if (p.used < d.pair[oldest].used) oldest = i;
-            if ((oldest_idle < 0 || p.used < d.pair[oldest_idle].used) && idle(p.weight) && idle(p.forward))
-                oldest_idle = i;
+    if (at < 0 || !d.pair[at].weight || (pipeline && !d.pair[at].forward)) {
+        RelaxedCapture relaxed;
+        if (relaxed.err != hipSuccess) return relaxed.err;
+        if (at < 0) at = open;
+        if (at < 0) {
+            int oldest_idle = -1, oldest = 0;
+            for (int i = 0; i < kPairs; ++i) {
+                const StreamPair& p = d.pair[i];
+                if (p.used < d.pair[oldest].used) oldest = i;
+                if ((oldest_idle < 0 || p.used < d.pair[oldest_idle].used) && idle(p.weight) && idle(p.forward))
+                    oldest_idle = i;
+            }
+            at = oldest_idle >= 0 ? oldest_idle : oldest;
         }
-        at = oldest_idle >= 0 ? oldest_idle : oldest;
+        hipError_t e = make_stream(device, &d.pair[at].weight);
+        if (e == hipSuccess && pipeline) e = make_stream(device, &d.pair[at].forward);
+        if (e != hipSuccess) return e;
     }
     StreamPair& p = d.pair[at];
-    hipError_t e = make_stream(device, &p.weight);
-    if (e == hipSuccess && pipeline) e = make_stream(device, &p.forward);
-    if (e != hipSuccess) return e;
     p.taken = true;
     p.caller = caller;
     p.thread = thread;
