@@ -230,35 +230,29 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
     }
 
     const int mrow = m0 + wm * MT * 16 + j, ncol = n0 + wn * NTL * 16 + 4 * g;
-    bool some = false;
     if constexpr (NS == 3) {
-        // sums to form again (split.h); left alone below
         Again redo;
 #pragma unroll
         for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) redo.add<NS>(acc[nt][mt]);
-        some = redo.any();
-        if (some) {
+        if (redo.any()) {
             uint64_t bad = 0;
             static_assert(MT * NTL * 4 <= 64, "one bit per sum");
 #pragma unroll
-            for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        bad |= (uint64_t)again<NS>(acc[nt][mt][i]) << ((nt * MT + mt) * 4 + i);
+            for (int k = 0; k < MT * NTL * 4; ++k)
+                bad |= (uint64_t)again<NS>(acc[(k >> 2) / MT][(k >> 2) % MT][k & 3]) << k;
 #pragma unroll 1
             for (; bad; bad &= bad - 1) {
-                const int q = __ffsll((unsigned long long)bad) - 1;
-                const int m = mrow + (q >> 2) % MT * 16, n = ncol + (q >> 2) / MT * 16 + (q & 3);
+                const int at = __ffsll((unsigned long long)bad) - 1;
+                const int m = mrow + (at >> 2) % MT * 16, n = ncol + (at >> 2) / MT * 16 + (at & 3);
                 if (m >= a.M || n >= a.N) continue;
-                float v = plain_dot<AK, BK>(a, m, n, kbeg, kend);
-                if (a.bias) v += a.bias[n];
-                if (a.relu) v = fmaxf(v, 0.f);
-                float* dst = C + (int64_t)m * a.N + n;
-                *dst = a.accumulate ? *dst + v : v;
+                const float v = plain_dot<AK, BK>(a, m, n, kbeg, kend);
+#pragma unroll
+                for (int k = 0; k < MT * NTL * 4; ++k) {
+                    sp_v4f& sums = acc[(k >> 2) / MT][(k >> 2) % MT];
+                    sums[k & 3] = k == at ? v : sums[k & 3];
+                }
             }
         }
     }
@@ -271,7 +265,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
             const int n = ncol + nt * 16;
             float* dst = C + (int64_t)m * a.N + n;
             sp_v4f v = acc[nt][mt];
-            if (a.vec && n + 4 <= a.N && !some) {
+            if (a.vec && n + 4 <= a.N) {
                 if (a.bias) v += sp_v4f{a.bias[n], a.bias[n + 1], a.bias[n + 2], a.bias[n + 3]};
                 if (a.relu)
 #pragma unroll
@@ -282,7 +276,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN * WK > 8 ? 4 : 2) void g
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     float s = v[i];
-                    if (n + i >= a.N || (some && again<NS>(s))) continue;
+                    if (n + i >= a.N) continue;
                     if (a.bias) s += a.bias[n + i];
                     if (a.relu) s = fmaxf(s, 0.f);
                     dst[i] = a.accumulate ? dst[i] + s : s;

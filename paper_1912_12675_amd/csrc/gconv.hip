@@ -348,30 +348,24 @@ __global__ __launch_bounds__(64 * WP * WK, NS == 3 && BM == 32 && BP == 256 && !
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NTL; ++nt) redo.add<NS>(acc[mt][nt]);
-    const bool some = redo.any();
-    // these sums are formed again (split.h; a group's unused slots read a
-    // real pixel) and stored here; the loop below leaves them alone
-    if (some) {
+    if (redo.any()) {  // split.h; a group's unused slots read a real pixel
         uint64_t bad = 0;
         static_assert(MT * NTL * 4 <= 64, "one bit per sum");
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    bad |= (uint64_t)again<NS>(acc[mt][nt][i]) << ((mt * NTL + nt) * 4 + i);
+        for (int k = 0; k < MT * NTL * 4; ++k)
+            bad |= (uint64_t)again<NS>(acc[(k >> 2) / NTL][(k >> 2) % NTL][k & 3]) << k;
 #pragma unroll 1
         for (; bad; bad &= bad - 1) {
-            const int k = __ffsll((unsigned long long)bad) - 1;
-            const int m = m0 + (k >> 2) / NTL * 16 + 4 * g + (k & 3);
+            const int at = __ffsll((unsigned long long)bad) - 1;
+            const int m = m0 + (at >> 2) / NTL * 16 + 4 * g + (at & 3);
             Pos q;
-            if (!pos_at((wp * NTL + (k >> 2) % NTL) * 16 + j, &q) || m >= a.M) continue;
-            float v = plain_sum<NS>(a, q.img, m, q.oh, q.ow);
-            float* dst = a.y + ((q.img * a.M + m) * a.OH + q.oh) * a.OW + q.ow;
-            if (a.bias) v += a.bias[m];
-            if (a.relu) v = fmaxf(v, 0.f);
-            *dst = a.accumulate ? *dst + v : v;
+            if (!pos_at((wp * NTL + (at >> 2) % NTL) * 16 + j, &q) || m >= a.M) continue;
+            const float v = plain_sum<NS>(a, q.img, m, q.oh, q.ow);
+#pragma unroll
+            for (int k = 0; k < MT * NTL * 4; ++k) {
+                sp_v4f& sums = acc[(k >> 2) / NTL][(k >> 2) % NTL];
+                sums[k & 3] = k == at ? v : sums[k & 3];
+            }
         }
     }
 #pragma unroll
@@ -392,7 +386,7 @@ __global__ __launch_bounds__(64 * WP * WK, NS == 3 && BM == 32 && BP == 256 && !
             for (int i = 0; i < 4; ++i) {
                 const int m = m0 + mt * 16 + 4 * g + i;
                 float v = acc[mt][nt][i];
-                if (m >= a.M || (some && again<NS>(v))) continue;
+                if (m >= a.M) continue;
                 if (a.bias) v += a.bias[m];
                 if (a.relu) v = fmaxf(v, 0.f);
                 if (a.accumulate) v += old[mt][i];
