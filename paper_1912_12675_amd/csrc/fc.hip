@@ -14,10 +14,11 @@
 // timing.
 //
 // Measured at 128 x 16384 x 4096 against the gemm that staged scalars (us,
-// fp32 / bf16): forward 2,238 -> 228 / 184, dx 655 -> 166, dw 258 -> 134 (268
+// fp32 / bf16): forward 2,238 -> 204 / 167, dx 655 -> 163, dw 258 -> 140 (268
 // MB of weights read, read and written: 40-50 us each at memory's rate, 110 at
-// the fp32 matrix rate).  Forward is bound by the delivery of x to every block
-// of columns, dx and dw by their stages' phases following one another.
+// the fp32 matrix rate; timed over repeated calls, a trace shows 220, 160 and 175).
+// Forward is bound by the delivery of x to every block of columns, dx and dw
+// by their stages' phases following one another.
 #include <algorithm>
 #include <type_traits>
 
@@ -568,8 +569,9 @@ struct Parts {
 
 // Tiles, each with the reason it is there (fp32, us; 128 rows unless said):
 // the largest that leaves work for the whole chip, except that
-//  - 128 x 128 pays only over many tiles: dw 4096 x 16384, k 128: 134 (64 x 64
-//    190); dx 128 x 16384, k 4096, is 128 tiles of it: 281 (64 x 64 166);
+//  - 128 x 128 pays only over many tiles: dw 4096 x 16384, k 128: 140 (64 x 64
+//    179; bf16 104 and 86, but 31 and 39 at 4096 x 4096, k 256); dx 128 x 16384, k
+//    4096, is 128 tiles of it: 281 (64 x 64 166);
 //  - few outputs over a deep k take 16 waves on k: 16 x 227, k 4096: 20.
 template <int NS, bool AK, bool BK>
 hipError_t gs_pick(GsArgs a, const Work& wk, float* ws, size_t ws_bytes, hipStream_t st)
@@ -648,11 +650,13 @@ hipError_t gemm(GsArgs a, int bf16, float* ws, size_t ws_bytes, hipStream_t st)
     // 30,000: rows 32.8, tiles 9.0; 256 x 300 -> 4096: 17.5, 11.5; 128 x 300 ->
     // 4096, 128 tiles: 9.4, 11.2).  bf16 with an x past an XCD's 4 MB of L2
     // (fp32, re-read by every block of columns) takes the LDS tile of 128 rows
-    // (16384 -> 4096, 128 rows: 184 against 192; 9216, 100 rows: 104 and 78)
+    // where its workgroups of 16 columns fill the chip (tile, rows: 256 x 8192 ->
+    // 8192 196, 340; 200 x 6000 -> 3000 79, 98; 128 x 16384 -> 4096 167, 172; 256 x
+    // 16384 -> 2048 159, 147; 128 x 8200 -> 1024 84, 43)
     if constexpr (AK && BK) {
         const int64_t most = INT32_MAX / 64 / std::max(a.lda, a.ldb);  // blocks of 16 rows in 31 bits
         const bool tiles = a.M > 32 && a.K <= 1024 && (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) >= 256;
-        const bool past = bf16 && a.N >= 1024 && a.M > 64 && (int64_t)a.M * a.K * 4 > kRowsL2;
+        const bool past = bf16 && a.N >= 2560 && a.M > 64 && (int64_t)a.M * a.K * 4 > kRowsL2;
         if (most >= 1 && a.M <= 256 && !tiles && !past)
             return bf16 ? rows_pick<true>(a, most, wk, st) : rows_pick<false>(a, most, wk, st);
     }

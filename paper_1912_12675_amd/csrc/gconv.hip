@@ -492,8 +492,10 @@ hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
     }
     // Wide tiles while they fill the chip: 32 channels rather than 64, since
     // three workgroups then share a CU's LDS and registers and one multiplies
-    // while another stages (fp32, us: 128 -> 128 at 16x16 69 against 82, 5x5 64 ->
-    // 192 104 against 145, 1x1 128 -> 192 35 against 44).
+    // while another stages (us, 32 and 64, fp32 / bf16: 128 -> 128 at 16x16 65, 89 /
+    // 41, 49; 5x5 64 -> 192 112, 134 / 58, 74; 1x1 128 -> 192 33, 39 / 24, 30; 192 ->
+    // 384 at 13x13 228, 261 / 138, 144; the other way only 256 -> 256 at 14x14 224,
+    // 211 / 136, 116).
     if (a.M <= 16 && blocks(t256, 16) >= 256) PSW_GC(t256, true, 16, 256, 4, 1, 2, 2);
     if (a.M > 16 && blocks(t256, 32) >= 256) {
         // up to two workgroups a CU leave registers for the small products' own

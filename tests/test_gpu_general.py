@@ -248,7 +248,8 @@ FC = [
     (129, 70, 2049),     # 128, 64 and 32 rows a block, each with a part block, column and step
     (65, 99, 4100),
     (40, 97, 4098),
-    (101, 10500, 1030),  # an x past 4 MB
+    (101, 10500, 2600),  # an x past 4 MB: in bf16 the tile of 128 rows
+    (101, 10500, 1030),  # ... too few columns for it
     (1, 4097, 70),       # deep reductions, one k past a stage
     (20, 2047, 66),
     (130, 130, 66),
