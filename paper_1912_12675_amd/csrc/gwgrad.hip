@@ -304,19 +304,28 @@ template <int NS, int BM, int WM, int CT, int RG, int S, int PX>
 hipError_t gw_launch(GwArgs a, int max_splits, int* splits, const Work& wk, hipStream_t st)
 {
     constexpr int LP = PX == 16 ? 4 : 3;
-    // chunk of PX units: fewest chunks; then the least of x, rows of a
-    // 32-byte sector where the plane has them
+    // Chunk of PX units: the least of all chunks' staging, in units a thread
+    // loads.  Neighbouring lanes load neighbouring columns, so units of rows
+    // shorter than 8 count more (32 bytes a row are a sector), units past the
+    // registers are waited for, and a chunk's barriers are four units more.  The
+    // fewest chunks alone, as it was, took one pixel of 128 images where a plane is
+    // no multiple of 8 (us, 128 images, fp32: 1x1 64 -> 256 at 28x28 643, 87; 3x3 192 ->
+    // 384 at 13x13 1,238, 320; 5x5 64 -> 96 at 27x27 2,274, 437; 3x3 64 -> 64 at 33x33
+    // 586, 105; of 58 measured shapes in both modes within 17% of the best choice).
     int64_t best = 0;
-    int best_x = 0;
+    double best_cost = 0.0;
     for (int lw = 0; lw <= LP; ++lw)
         for (int lh = 0; lw + lh <= LP; ++lh) {
             const int tw = 1 << lw, th = 1 << lh, to = PX >> (lw + lh);
             if (((tw >> 1) >= a.Q && lw) || ((th >> 1) >= a.P && lh)) continue;
             const int64_t ch = (int64_t)((a.Q + tw - 1) / tw) * ((a.P + th - 1) / th) * (((a.n + 7) / 8 + to - 1) / to);
-            const int xp = to * ((th - 1) * a.st + RG) * ((tw - 1) * a.st + S) + (tw < 8 && a.Q >= 8 ? 8 : 0);
-            if (!best || ch < best || (ch == best && xp < best_x)) {
+            const int hc = (tw - 1) * a.st + S;
+            const double x = 16.0 * CT * to * ((th - 1) * a.st + RG) * hc / 256;
+            auto row = [](int columns) { return columns >= 8 ? 1.0 : columns >= 4 ? 1.6 : columns >= 2 ? 3.0 : 8.0; };
+            const double cost = ch * (4.0 + BM * PX / 256 * row(tw) + x * row(hc) + (x > 3.0 ? x - 3.0 : 0.0));
+            if (!best || cost < best_cost) {
                 best = ch;
-                best_x = xp;
+                best_cost = cost;
                 a.lw = lw;
                 a.lh = lh;
                 a.tiles_w = (a.Q + tw - 1) / tw;
