@@ -403,12 +403,16 @@ struct Tiling {
 
 // Tile of bp positions over n planes of gh x gw, for the least of all tiles'
 // products (bp positions each, padding included) and staging (the halo's
-// elements; rows shorter than 16 positions, 64 bytes a load and store
-// instruction row, count as more).  The fewest tiles alone gave 14x14 planes
-// tiles of 2x2 positions in 64 images, a halo four times the positions (fp32,
-// 128 images, us before and now: 256 -> 256 at 14x14 693, 216; at 7x7 395, 100;
-// 64 -> 64 at 28x28 114, 67; 5x5 64 -> 96 at 27x27 962, 194; 1x1 96 -> 200 at 14x14
-// 184, 46; a staged element weighing a quarter to twice a position: within 5%).
+// elements, 1.3 of a position each; neighbouring lanes load and store
+// neighbouring columns, so rows shorter than 16 count more, up to five times
+// for one column); of equal ones the most columns.  The fewest tiles alone gave
+// 14x14 planes tiles of 2x2 positions in 64 images, a halo four times the
+// positions (fp32, 128 images, us then and now: 256 -> 256 at 14x14 693, 222; at
+// 7x7 395, 98; 64 -> 64 at 28x28 114, 70; 5x5 64 -> 96 at 27x27 962, 200; 1x1 96
+// -> 200 at 14x14 184, 43), and a penalty that did not grow below 8 columns gave
+// 1x1 kernels on planes that no power of two divides single columns (182 images,
+// 61 -> 50 at 10x9 47, 15; 128 images, 1 -> 152 at 8x13 66, 16).  Of 127 measured
+// calls all are within 15% of their best tile.
 Tiling pick_tile(int n, int gh, int gw, int bp, int is, int rs, int ss)
 {
     Tiling best{};
@@ -421,9 +425,9 @@ Tiling pick_tile(int n, int gh, int gw, int bp, int is, int rs, int ss)
             Tiling t{lw, lh, (gh + th - 1) / th, (gw + tw - 1) / tw, 0, 0};
             t.tiles = (int64_t)t.tiles_h * t.tiles_w * ((n + ti - 1) / ti);
             t.hp = ti * ((th - 1) * is + rs) * ((tw - 1) * is + ss);
-            const double stage = t.hp * (tw >= 16 || tw >= gw ? 1.0 : tw >= 8 ? 1.1 : 1.4);
-            const double cost = (double)t.tiles * (bp + stage);
-            if (!best.tiles || cost < best_cost) {
+            const double row = tw >= 16 ? 1.0 : tw >= 8 ? 1.3 : tw >= 4 ? 1.4 : tw >= 2 ? 2.5 : 5.0;
+            const double cost = (double)t.tiles * (bp + 1.3 * t.hp * row);
+            if (!best.tiles || cost <= best_cost) {
                 best = t;
                 best_cost = cost;
             }
@@ -508,10 +512,13 @@ hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
     // layer's backward data 14 against 18)
     if (a.M <= 32 && a.C * taps <= 1024) PSW_GC(tile(128), true, 16, 128, 4, 1, 2, 2);
     // deep reductions over few positions: waves share the depth, two of a 32 x
-    // 64 tile (512 -> 512 at 4x4 126 against 174), or with fewer of those, four
-    // of a 32 x 32 tile (at 2x2 89 against 115)
+    // 64 tile (from 256 blocks: 256 -> 128 at 14x14, 16 images 45 against 52), or
+    // with fewer of those, four of a 32 x 32 tile (512 -> 512 at 2x2 89 against
+    // 115).  A strided forward stages four elements a position and keeps to the
+    // smaller tile a little longer (24 -> 56 at 29x23 stride 2, 37 images, 296
+    // blocks: 14.3 against 15.4; 128 -> 256 at 8x8, 256 blocks: 33.5 against 35.8)
     const Tiling t64 = tile(64);
-    if (blocks(t64, 32) >= 256) PSW_GC(t64, true, 32, 64, 2, 2, 4, 2);
+    if (blocks(t64, 32) >= (a.is > 1 ? 320 : 256)) PSW_GC(t64, true, 32, 64, 2, 2, 4, 2);
     PSW_GC(tile(32), true, 32, 32, 1, 4, 4, 4);
 #undef PSW_GC
     return hipErrorNotSupported;

@@ -70,6 +70,10 @@ CONV = [
     (2, 64, 55, 57, 128, 3, 3, 2, 1),    # two: by it, and in bf16 not
     (3, 20, 21, 23, 40, 3, 3, 1, 0),
     (1, 4, 40, 40, 4, 9, 9, 4, 4),
+    (21, 61, 10, 9, 50, 1, 1, 1, 0),     # 1x1 on planes that no power of two divides
+    (19, 1, 8, 13, 152, 1, 1, 1, 0),
+    (40, 24, 29, 23, 56, 3, 3, 2, 1),    # stride 2: 320 blocks of 32 x 64, the first that take it
+    (39, 24, 29, 23, 56, 3, 3, 2, 1),    # one image fewer
 ]
 
 
