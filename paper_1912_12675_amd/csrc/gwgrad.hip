@@ -22,9 +22,9 @@
 // in a fixed order.
 //
 // Measured with the reduction, batch 128, against the implicit GEMM (fp32):
-// 3x3 64 -> 64 at 32x32 336 -> 81 us, 256 -> 256 at 8x8 299 -> 78 us (123
-// TFLOP/s), 512 -> 512 at 4x4 364 -> 108 us, 5x5 64 -> 192 at 16x16 597 -> 148
-// us; bf16 mode 464 -> 59, 395 -> 48, 425 -> 79, 767 -> 85 us.
+// 3x3 64 -> 64 at 32x32 336 -> 77 us, 256 -> 256 at 8x8 299 -> 64 us (151
+// TFLOP/s), 512 -> 512 at 4x4 364 -> 62 us, 5x5 64 -> 192 at 16x16 597 -> 138
+// us; bf16 mode 464 -> 56, 395 -> 39, 425 -> 37, 767 -> 78 us.
 #include "internal.h"
 #include "split.h"
 
