@@ -40,6 +40,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import sys
 from collections import defaultdict
 
@@ -112,17 +113,22 @@ def pmc_values(path: str, counter: str):
 
 
 def kernel_sources(kernel: str):
-    """Source files (relative to the repository) that define a library kernel."""
+    """Source files (relative to the repository) that define a library kernel:
+    the .hip file with its __global__ definition and the headers that it names."""
     base = "paper_1912_12675_amd/csrc/"
-    if kernel.startswith(("conv3x3_direct", "conv3x3_dgrad_s2")):
-        f = "direct.hip"
-    elif kernel.startswith("conv3x3_wgrad"):
-        f = "wgrad.hip"
-    elif kernel.startswith(("igemm_kernel", "reduce_splits")):
-        f = "conv.hip"
-    else:
-        f = "ops.hip"
-    return [base + f, base + "internal.h"]
+    name = kernel.split("<")[0]
+    found = []
+    for f in sorted(os.listdir(os.path.join(ROOT, base))):
+        if not f.endswith(".hip"):
+            continue
+        with open(os.path.join(ROOT, base, f)) as fh:
+            text = fh.read()
+        if re.search(r"__global__[^;{]*\bvoid\s+" + re.escape(name) + r"\(", text):
+            headers = re.findall(r'#include "(\w+\.h)"', text)
+            found.append([base + f] + [base + h for h in headers])
+    if len(found) != 1:
+        raise SystemExit(f"expected one source that defines {name!r}, found {[f[0] for f in found]}")
+    return found[0]
 
 
 def source_hash(files) -> str:
