@@ -489,10 +489,32 @@ hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
             return launch_cfg<NS, __VA_ARGS__, NS == 3 && OWN_>(p, t_, wk, st);            \
     } while (0)
     const Tiling t256 = tile(256);
-    if (a.C <= 8) {  // an image net's first layer (forward): one octet, four taps per matrix step
-        if (a.M <= 16) PSW_GC(t256, true, 16, 256, 4, 1, 1, 2);
-        if (a.M <= 32) PSW_GC(t256, false, 32, 256, 4, 1, 1, 2);
-        PSW_GC(t256, false, 64, 256, 4, 1, 1, 2);
+    // An image net's first layer (forward) or few output channels (backward): one
+    // octet, four taps per matrix step.  Little work, so the tile is the widest
+    // that still gives every CU a workgroup (us fp32 by the implicit GEMM, by 256
+    // positions of up to 64 channels for all, now: 5x5 1 -> 6 at 28x28, 16 images
+    // 8.2, 11.9, 7.3; 6 -> 16 at 14x14 26.6, 11.7, 7.5; 2 -> 54 at 13x11 stride 2, 128
+    // images 11.6, 20.9, 7.4; 3 -> 32 at 28x28 18.9, 20.3, 17.4; 1x1 4 -> 152 at 8x13
+    // 11.7, 16.1, 10.8; 7x7 3 -> 64 at 32x32 stride 2 38.9, 36.9, 19.1).  Wider ones
+    // where there are several a CU (64 x 256 against 32 x 128: 3 -> 64 5x5 at 32x32
+    // 34.0, 35.6; 16 x 256 against 16 x 128: 9x9 1 -> 16 at 64x64, 64 images 37.7, 39.3)
+    // and two fit a CU's LDS (3 -> 64 7x7 at 224x224 stride 2, 32 images 258, 158).
+    // Of a tile that fills the LDS, few (3 -> 64 11x11 stride 4, 23x23 of 16 images
+    // 49, the implicit GEMM 80; 27x27 of 32 images 117, 82).
+    if (a.C <= 8) {
+        const size_t half = kLdsMax / 2;
+        const Tiling t128 = tile(128), t64 = tile(64);
+        if (a.M <= 16) {
+            if (blocks(t256, 16) >= (taps <= 4 ? 256 : 1024)) PSW_GC(t256, true, 16, 256, 4, 1, 1, 4);
+            if (blocks(t128, 16) >= 256) PSW_GC(t128, true, 16, 128, 4, 1, 1, 4);
+        } else {
+            if (a.M > 32 && blocks(t256, 32) >= 1024 && lds_bytes<NS, 64, 256, 4, 1, 1, 2>(p, t256) <= half)
+                PSW_GC(t256, false, 64, 256, 4, 1, 1, 2);
+            if (blocks(t128, 32) >= 256 && lds_bytes<NS, 32, 128, 4, 1, 1, 2>(p, t128) <= half)
+                PSW_GC(t128, true, 32, 128, 4, 1, 1, 2);
+        }
+        if (blocks(t64, 16) <= 1024 || lds_bytes<NS, 16, 64, 4, 1, 1, 4>(p, t64) <= half)
+            PSW_GC(t64, true, 16, 64, 4, 1, 1, 4);
     }
     // Wide tiles while they fill the chip: 32 channels rather than 64, since
     // three workgroups then share a CU's LDS and registers and one multiplies

@@ -74,6 +74,15 @@ CONV = [
     (19, 1, 8, 13, 152, 1, 1, 1, 0),
     (40, 24, 29, 23, 56, 3, 3, 2, 1),    # stride 2: 320 blocks of 32 x 64, the first that take it
     (39, 24, 29, 23, 56, 3, 3, 2, 1),    # one image fewer
+    (3, 1, 28, 28, 6, 5, 5, 1, 2),       # one octet of channels: 16 output channels of 64 positions
+    (37, 5, 28, 27, 16, 5, 5, 1, 2),     # ... of 128
+    (257, 3, 32, 31, 13, 3, 3, 1, 1),    # ... of 256
+    (130, 8, 21, 19, 15, 1, 1, 1, 0),    # ... with few taps
+    (86, 6, 21, 19, 50, 3, 3, 2, 1),     # 32 output channels of 128
+    (65, 3, 64, 62, 70, 3, 3, 1, 1),     # 64 of 256
+    (17, 3, 64, 64, 40, 11, 11, 4, 2),   # a halo that leaves room for one workgroup a CU
+    (86, 3, 64, 64, 40, 11, 11, 4, 2),   # ... and more tiles than those pay for
+    (2, 5, 40, 40, 20, 13, 13, 3, 6),
 ]
 
 
