@@ -378,6 +378,7 @@ hipError_t gw_taps(const GwArgs& a, int ms, int* sp, const Work& wk, hipStream_t
     if (a.R == 3 && a.S == 3) return gw_launch<NS, BM, WM, 1, 3, 3, PX>(a, ms, sp, wk, st);
     if (a.S == 5) return gw_launch<NS, BM, WM, 1, 1, 5, PX>(a, ms, sp, wk, st);
     if (a.S == 3) return gw_launch<NS, BM, WM, 1, 1, 3, PX>(a, ms, sp, wk, st);
+    if (a.S == 1 && a.C <= 16) return gw_launch<NS, BM, WM, 1, 1, 1, PX>(a, ms, sp, wk, st);
     if (a.S == 1) return gw_launch<NS, BM, WM, 4, 1, 1, PX>(a, ms, sp, wk, st);
     return hipErrorNotSupported;
 }
@@ -392,8 +393,10 @@ hipError_t gw_rows(const GwArgs& a, int ms, int* sp, const Work& wk, hipStream_t
     if (units < 512 && a.S > 1) return gw_taps<NS, 32, 2, 8>(a, ms, sp, wk, st);
     if (a.K <= 32) return gw_taps<NS, 32, 1, 16>(a, ms, sp, wk, st);
     // a 1x1 chunk has one tap to multiply per loaded value: smaller chunks, three
-    // workgroups a CU (128 -> 192 at 16x16 b128 52 -> 34 us)
-    if (a.S == 1) return gw_launch<NS, 64, 2, 4, 1, 1, 8>(a, ms, sp, wk, st);
+    // workgroups a CU (128 -> 192 at 16x16 b128 52 -> 34 us).  Up to 16 channels one
+    // block of them (fp32, us, four blocks and one: 16 images 4 -> 6 at 21x11 stride 2
+    // 15.0, 8.9; 16 -> 32 at 14x14 15.5, 10.7; 128 images 4 -> 40 at 20x17 18.4, 13.1)
+    if (a.S == 1 && a.C > 16) return gw_launch<NS, 64, 2, 4, 1, 1, 8>(a, ms, sp, wk, st);
     return gw_taps<NS, 64, 2, 16>(a, ms, sp, wk, st);
 }
 

@@ -65,6 +65,9 @@ CONV = [
     (33, 16, 30, 30, 16, 3, 3, 1, 1),    # too few for those
     (9, 70, 13, 11, 130, 1, 1, 1, 0),    # 1x1 weight gradients of two blocks of 64 rows and of 64 channels, both ragged
     (9, 70, 13, 11, 130, 1, 1, 2, 0),
+    (9, 16, 13, 11, 130, 1, 1, 1, 0),    # ... of one block of 16 channels
+    (11, 3, 13, 11, 29, 1, 1, 2, 0),
+    (4, 17, 14, 13, 15, 1, 1, 1, 0),     # ... of one channel past it
     (41, 20, 19, 21, 70, 5, 5, 1, 2),    # 5x5 weight gradients of 64 rows, whose steps take two sums in bf16
     (1, 24, 29, 23, 56, 3, 3, 2, 1),     # one image: weight gradients by the implicit GEMM
     (2, 64, 55, 57, 128, 3, 3, 2, 1),    # two: by it, and in bf16 not
