@@ -495,12 +495,17 @@ hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
     // positions of up to 64 channels for all, now: 5x5 1 -> 6 at 28x28, 16 images
     // 8.2, 11.9, 7.3; 6 -> 16 at 14x14 26.6, 11.7, 7.5; 2 -> 54 at 13x11 stride 2, 128
     // images 11.6, 20.9, 7.4; 3 -> 32 at 28x28 18.9, 20.3, 17.4; 1x1 4 -> 152 at 8x13
-    // 11.7, 16.1, 10.8; 7x7 3 -> 64 at 32x32 stride 2 38.9, 36.9, 19.1).  Wider ones
-    // where there are several a CU (64 x 256 against 32 x 128: 3 -> 64 5x5 at 32x32
-    // 34.0, 35.6; 16 x 256 against 16 x 128: 9x9 1 -> 16 at 64x64, 64 images 37.7, 39.3)
-    // and two fit a CU's LDS (3 -> 64 7x7 at 224x224 stride 2, 32 images 258, 158).
-    // Of a tile that fills the LDS, few (3 -> 64 11x11 stride 4, 23x23 of 16 images
-    // 49, the implicit GEMM 80; 27x27 of 32 images 117, 82).
+    // 11.7, 16.1, 10.8; 7x7 3 -> 64 at 32x32 stride 2 38.9, 36.9, 19.1).  By the lines:
+    // - 16 channels: of 64 positions and of 128, the first at 112 blocks of the
+    //   second 7.3, 8.3, at 896 (5x5 1 -> 16 at 28x28) 16.2, 13.1; of 128 and of 256
+    //   at 512 blocks of the second 13.1, 14.9, at 1024 (9x9 at 64x64) 39.3, 37.7,
+    //   and in 1x1 kernels, which stage no second group of weights, at 448 9.7, 9.3
+    // - 16 of 64 and 32 of 128 at 128 blocks of the second 7.4, 9.7, at 512 14.0, 10.3
+    // - 32 of 128 and 64 of 256 at 1024 blocks of 32 x 256 35.6, 34.0 (5x5 3 -> 64 at
+    //   32x32); past half a CU's LDS, one workgroup a CU, 158, 258 (7x7 3 -> 64 at
+    //   224x224 stride 2, 32 images)
+    // - a tile of 64 that takes more than half the LDS and the implicit GEMM: 768
+    //   blocks 49, 80 (11x11 3 -> 64 at 96x96 stride 4), 1792 (112x112) 117, 82
     if (a.C <= 8) {
         const size_t half = kLdsMax / 2;
         const Tiling t128 = tile(128), t64 = tile(64);
