@@ -498,7 +498,7 @@ hipError_t launch_ns(Plan& p, const Work& wk, hipStream_t st)
     // 11.7, 16.1, 10.8; 7x7 3 -> 64 at 32x32 stride 2 38.9, 36.9, 19.1).  By the lines:
     // - 16 channels: of 64 positions and of 128, the first at 112 blocks of the
     //   second 7.3, 8.3, at 896 (5x5 1 -> 16 at 28x28) 16.2, 13.1; of 128 and of 256
-    //   at 512 blocks of the second 13.1, 14.9, at 1024 (9x9 at 64x64) 39.3, 37.7,
+    //   at 512 blocks of the second 13.1, 15.0, at 1024 (9x9 at 64x64) 39.3, 37.7,
     //   and in 1x1 kernels, which stage no second group of weights, at 448 9.7, 9.3
     // - 16 of 64 and 32 of 128 at 128 blocks of the second 7.4, 9.7, at 512 14.0, 10.3
     // - 32 of 128 and 64 of 256 at 1024 blocks of 32 x 256 35.6, 34.0 (5x5 3 -> 64 at
